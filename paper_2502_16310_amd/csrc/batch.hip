@@ -264,11 +264,9 @@ __global__ void k_b_bin_clear(uint32_t *off_global, int64_t nb_total, const Ctl 
         off_global[i] = 0;
 }
 
-__global__ __launch_bounds__(64) void k_b_canon_small(int32_t *ids, const uint32_t *off_global, int64_t nb_total,
+__global__ __launch_bounds__(kCanonThreads) void k_b_canon_small(int32_t *ids, const uint32_t *off_global, int64_t nb_total,
                                                       uint32_t *med_list, uint32_t *big_list, Ctl *ctl) {
-    const int64_t groups = (nb_total + dev::kWave - 1) / dev::kWave;
-    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x)
-        bin_canon_group(ids, off_global, nb_total, g * dev::kWave, med_list, big_list, ctl->lists, 0u);
+    bin_canon_groups(ids, off_global, nb_total, blockIdx.x, gridDim.x, med_list, big_list, ctl->lists, 0u);
 }
 
 __global__ __launch_bounds__(kMedThreads) void k_b_canon_medium(int32_t *ids, const uint32_t *off_global,
@@ -1036,7 +1034,7 @@ static agal_status capture(agal_batch bt) {
     hipLaunchKernelGGL(k_b_bin_scatter<D>, dim3(G), dim3(256), 0, s, B, nb, bt->d_bin_off, bt->d_bin_cursor, bt->d_ids,
                        bt->cap_ids, bt->d_ctl);
     hipLaunchKernelGGL(k_b_bin_clear, dim3(G), dim3(256), 0, s, bt->d_bin_off, bt->nb_total, bt->d_ctl);
-    hipLaunchKernelGGL(k_b_canon_small, dim3(G64), dim3(64), 0, s, bt->d_ids, bt->d_bin_off, bt->nb_total, bt->d_med,
+    hipLaunchKernelGGL(k_b_canon_small, dim3(2 * G), dim3(kCanonThreads), 0, s, bt->d_ids, bt->d_bin_off, bt->nb_total, bt->d_med,
                        bt->d_big, bt->d_ctl);
     hipLaunchKernelGGL(k_b_canon_medium, dim3(G), dim3(kMedThreads), 0, s, bt->d_ids, bt->d_bin_off, bt->d_med,
                        bt->d_ctl);

@@ -5,8 +5,8 @@
 //
 // Kernels: count (one thread per face, atomics per touched bin) -> exclusive
 // scan -> scatter (atomic cursors) -> canonical order (each bin's segment
-// sorted by rank in LDS: a group of 64 bins at once when its ids fit, else a
-// workgroup per bin; bins too large for LDS are rebuilt by an ordered sweep
+// sorted in LDS: small bins by rank, a group of 64 bins at once, larger ones by
+// a workgroup per bin; bins too large for LDS are rebuilt by an ordered sweep
 // over all faces, which only happens when B is tiny).
 #include <algorithm>
 
@@ -34,9 +34,10 @@ __global__ void k_bin_scatter(const float *aabb, int64_t F, dev::BinGrid g, cons
     AGAL_GRID_STRIDE(f, F) bin_scatter_item<D>(aabb, F, g, off, cursor, ids, f);
 }
 
-__global__ __launch_bounds__(64) void k_bin_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,
-                                                        uint32_t *med_list, uint32_t *big_list, uint32_t *counts) {
-    bin_canon_group(ids, off, nb, (int64_t)blockIdx.x * dev::kWave, med_list, big_list, counts, 0u);
+__global__ __launch_bounds__(kCanonThreads) void k_bin_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,
+                                                                   uint32_t *med_list, uint32_t *big_list,
+                                                                   uint32_t *counts) {
+    bin_canon_groups(ids, off, nb, blockIdx.x, gridDim.x, med_list, big_list, counts, 0u);
 }
 
 __global__ __launch_bounds__(kMedThreads) void k_bin_canon_medium(int32_t *ids, const uint32_t *off,
@@ -122,7 +123,7 @@ agal_status bin_count_scan(agal_context ctx, agal_context ctx_timed, agal_geom g
 
 // Scatter and canonical order into ids[0..P) (offsets from bin_count_scan);
 // med: room for nb bin indices, big: for P / kCanonCap + 1.
-agal_status bin_scatter_canon(agal_context ctx_timed, agal_geom g, const GridSpec &gs, uint32_t *work,
+agal_status bin_scatter_canon(agal_context ctx, agal_context ctx_timed, agal_geom g, const GridSpec &gs, uint32_t *work,
                               const uint32_t *off, int32_t *ids, uint32_t P, uint32_t *med, uint32_t *big,
                               hipStream_t s) {
     const int64_t nb = gs.nb;
@@ -136,11 +137,10 @@ agal_status bin_scatter_canon(agal_context ctx_timed, agal_geom g, const GridSpe
             hipLaunchKernelGGL(k_bin_scatter<2>, dim3(grid_for(g->F)), dim3(256), 0, s, g->aabb, g->F, gs.grid, off,
                                w.cursor, ids);
     }
-    const int64_t groups = (nb + dev::kWave - 1) / dev::kWave;
     {
         ProfScope prof(ctx_timed, "bin_canon", s);
-        hipLaunchKernelGGL(k_bin_canon_small, dim3((unsigned)groups), dim3(dev::kWave), 0, s, ids, off, nb, med, big,
-                           w.lists);
+        hipLaunchKernelGGL(k_bin_canon_small, dim3(canon_grid(nb, ctx->n_cu)), dim3(kCanonThreads), 0, s, ids, off, nb,
+                           med, big, w.lists);
         hipLaunchKernelGGL(k_bin_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0, s,
                            ids, off, med, w.lists);
     }
@@ -230,7 +230,7 @@ agal_status agal_bin_faces(agal_geom g, const float lo[3], const float hi[3], in
     st = dev_alloc(ctx->mem, &bn->ids, (size_t)std::max<uint32_t>(P, 1u), s);
     if (st == AGAL_OK) st = dev_alloc(ctx->mem, &med, (size_t)nb, s);
     if (st == AGAL_OK) st = dev_alloc(ctx->mem, &big, (size_t)P / kCanonCap + 1, s);
-    if (st == AGAL_OK) st = bin_scatter_canon(ctx, g, gs, work, bn->off, bn->ids, P, med, big, s);
+    if (st == AGAL_OK) st = bin_scatter_canon(ctx, ctx, g, gs, work, bn->off, bn->ids, P, med, big, s);
     if (cleanup(st) != AGAL_OK) return st;
     *out = bn;
     return AGAL_OK;
@@ -271,7 +271,7 @@ agal_status agal_bin_faces_noalloc(agal_geom g, const float lo[3], const float h
     if ((int64_t)P > ids_capacity)
         return fail(AGAL_ECAPACITY, "agal_bin_faces_noalloc: %u (face, bin) entries exceed ids_capacity %lld", P,
                     (long long)ids_capacity);
-    return bin_scatter_canon(nullptr, g, gs, base, d_offsets, d_face_ids, P, base + work_words,
+    return bin_scatter_canon(ctx, nullptr, g, gs, base, d_offsets, d_face_ids, P, base + work_words,
                              base + work_words + gs.nb, s);
 }
 

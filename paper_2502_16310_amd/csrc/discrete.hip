@@ -253,9 +253,10 @@ __global__ __launch_bounds__(kDiscBigThreads) void k_disc_big(const float *rec, 
     }
 }
 
-__global__ __launch_bounds__(64) void k_disc_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,
-                                                         uint32_t *med_list, uint32_t *big_list, uint32_t *counts) {
-    bin_canon_group(ids, off, nb, (int64_t)blockIdx.x * dev::kWave, med_list, big_list, counts, 0u);
+__global__ __launch_bounds__(kCanonThreads) void k_disc_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,
+                                                                    uint32_t *med_list, uint32_t *big_list,
+                                                                    uint32_t *counts) {
+    bin_canon_groups(ids, off, nb, blockIdx.x, gridDim.x, med_list, big_list, counts, 0u);
 }
 
 __global__ __launch_bounds__(kMedThreads) void k_disc_canon_medium(int32_t *ids, const uint32_t *off,
@@ -417,8 +418,8 @@ agal_status disc_pairs(agal_geom g, agal_bins bn, const DiscGrid &G, hipStream_t
     }
     {
         ProfScope prof(ctx, "bin_canon", s);
-        hipLaunchKernelGGL(k_disc_canon_small, dim3((unsigned)((nb + dev::kWave - 1) / dev::kWave)), dim3(dev::kWave),
-                           0, s, bn->ids, bn->off, nb, med, big, lists);
+        hipLaunchKernelGGL(k_disc_canon_small, dim3(canon_grid(nb, ctx->n_cu)), dim3(kCanonThreads), 0, s,
+                           bn->ids, bn->off, nb, med, big, lists);
         hipLaunchKernelGGL(k_disc_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0, s,
                            bn->ids, bn->off, med, lists);
         hipLaunchKernelGGL((k_disc_canon_big<D>), dim3((unsigned)std::min<int64_t>((int64_t)P / kCanonCap + 1, 256)),

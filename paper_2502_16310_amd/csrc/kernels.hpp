@@ -9,8 +9,9 @@
 
 #include <hip/hip_runtime.h>
 
-#include <cstdint>
+#include <algorithm>
 #include <climits>
+#include <cstdint>
 
 #include "device.hpp"
 
@@ -151,81 +152,144 @@ __device__ __forceinline__ void bin_scatter_item(const float *aabb, int64_t F, c
     }
 }
 
-// Sort ids[s0, s1) (bins b_first..b_last whose offsets are in s_off) by rank:
-// each entry's position inside its bin is the number of smaller ids there.
-__device__ void rank_sort_segment(int32_t *ids, const uint32_t *s_off, int nbins, uint32_t s0, uint32_t s1,
-                                  int32_t *s_val) {
-    const int lane = threadIdx.x;
+// Canonical order of one bin of at most kRankCap ids costs each id a pass over
+// the bin's ids in LDS; a larger bin is sorted by a network, whose steps grow
+// with log^2 instead of with the bin.  Measured, small + medium kernel, against
+// ranks alone by one wave per group: 81,920 faces over 16^3 box bins (~170 ids in
+// a bin) 833 -> 29 us, sampled-point bins 190 -> 13 us; 327,680 faces over 128^3
+// bins (1 or 2 ids) 60 -> 42 us; 40,500 faces over 50^3 bins 47 -> 15 us.
+constexpr int kRankCap = 64;
+constexpr int kCanonThreads = 256;
+
+// Sort ids[s0, s1) (nbins bins whose offsets are in s_off) by rank: each
+// entry's position inside its bin is the number of smaller ids there.  Bins
+// above kRankCap ids are left as they are.  One workgroup of kCanonThreads; a
+// thread's ids are loaded together.
+__device__ __forceinline__ void rank_sort_segment(int32_t *ids, const uint32_t *s_off, int nbins, uint32_t s0,
+                                                  uint32_t s1, int32_t *s_val) {
+    constexpr int PER = kCanonCap / kCanonThreads;
     const int n = (int)(s1 - s0);
-    for (int e = lane; e < n; e += dev::kWave) s_val[e] = ids[s0 + e];
+    int32_t own[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = (int)threadIdx.x + k * kCanonThreads;
+        own[k] = e < n ? ids[s0 + e] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = (int)threadIdx.x + k * kCanonThreads;
+        if (e < n) s_val[e] = own[k];
+    }
     __syncthreads();
-    for (int e = lane; e < n; e += dev::kWave) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int e = (int)threadIdx.x + k * kCanonThreads;
+        if (e >= n) continue;
         uint32_t pos = s0 + (uint32_t)e;
-        // bin of entry e: last bin whose start <= pos
+        // bin of entry e: last bin whose start <= pos (the non-empty one holding it)
         int lo = 0, hi = nbins - 1;
         while (lo < hi) {
             int mid = (lo + hi + 1) >> 1;
             if (s_off[mid] <= pos) lo = mid; else hi = mid - 1;
         }
-        // the last bin starting at or before pos is the non-empty one holding it
-        int b = lo;
-        const int bs = (int)(s_off[b] - s0), be = (int)(s_off[b + 1] - s0);
-        const int32_t v = s_val[e];
+        const int bs = (int)(s_off[lo] - s0), be = (int)(s_off[lo + 1] - s0);
+        if (be - bs > kRankCap) continue;
+        const int32_t v = own[k];
         int rank = 0;
-        for (int j = bs; j < be; ++j) rank += s_val[j] < v ? 1 : 0;
+        // four ids in flight (past the end: the entry's own id, which counts 0)
+        for (int j = bs; j < be; j += 4) {
+            int32_t x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = s_val[j + u < be ? j + u : e];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += x[u] < v ? 1 : 0;
+        }
         ids[s0 + bs + rank] = v;
     }
-    __syncthreads();
 }
 
-// One wave: the group of 64 consecutive bins starting at b0.  A group whose
-// ids fit the LDS segment is rank-sorted here in one go; otherwise each of
-// its bins with more than one id goes to a list of its own: the medium list
-// (at most kCanonCap ids: rank-sorted by a workgroup per bin) or, tagged with
-// big_tag, the big list (rebuilt by an ordered sweep).  Lists are appended
-// through counters (lists[0], lists[1] = medium and big counts).
+// One workgroup: the group of 64 consecutive bins starting at b0.  A group
+// whose ids fit the LDS segment has its bins of at most kRankCap ids
+// rank-sorted here in one go.  Every other bin with more than one id goes to a
+// list: the medium list (at most kCanonCap ids: sorted by a workgroup per bin)
+// or, tagged with big_tag, the big list (rebuilt by an ordered sweep).  Lists
+// are appended through counters (counts[0], counts[1] = medium and big counts).
 __device__ __forceinline__ void bin_canon_group(int32_t *ids, const uint32_t *off, int64_t nb, int64_t b0,
                                                 uint32_t *med_list, uint32_t *big_list, uint32_t *counts,
                                                 uint32_t big_tag) {
     __shared__ uint32_t s_off[dev::kWave + 1];
     __shared__ int32_t s_val[kCanonCap];
     const int nbins = (int)std::min<int64_t>(dev::kWave, nb - b0);
-    const int lane = threadIdx.x;
-    for (int i = lane; i <= nbins; i += dev::kWave) s_off[i] = off[b0 + i];
+    const int tid = threadIdx.x;
+    if (tid <= nbins) s_off[tid] = off[b0 + tid];
     __syncthreads();
     const uint32_t g0 = s_off[0], g1 = s_off[nbins];
-    if (g1 - g0 <= 1) {
-        __syncthreads();
-        return;
+    const bool fits = g1 - g0 <= (uint32_t)kCanonCap;
+    if (tid < nbins) {
+        const uint32_t a0 = s_off[tid], a1 = s_off[tid + 1];
+        if (a1 - a0 > (uint32_t)kCanonCap) big_list[atomicAdd(counts + 1, 1u)] = big_tag + (uint32_t)(b0 + tid);
+        else if (a1 - a0 > (fits ? (uint32_t)kRankCap : 1u)) med_list[atomicAdd(counts, 1u)] = (uint32_t)(b0 + tid);
     }
-    if (g1 - g0 <= (uint32_t)kCanonCap) {
-        rank_sort_segment(ids, s_off, nbins, g0, g1, s_val);
-        return;
+    if (fits && g1 - g0 > 1) rank_sort_segment(ids, s_off, nbins, g0, g1, s_val);
+    __syncthreads();   // before the next group's offsets and ids
+}
+
+// Workgroup w of nw: the groups w, w + nw, ... of 64 bins each.  Only the groups
+// that hold at least two ids are opened, found 64 at a time from one load of
+// their bounds: of a body's bins at a fine density most groups are empty (2^21
+// bins over 327,680 faces: 87 % hold at most one id).  The full ones lie next to
+// each other, along the body, so a workgroup's groups are nw apart.
+__device__ __forceinline__ void bin_canon_groups(int32_t *ids, const uint32_t *off, int64_t nb, int64_t w, int64_t nw,
+                                                 uint32_t *med_list, uint32_t *big_list, uint32_t *counts,
+                                                 uint32_t big_tag) {
+    const int lane = dev::lane_id();
+    const int64_t groups = (nb + dev::kWave - 1) / dev::kWave;
+    for (int64_t i0 = w; i0 < groups; i0 += nw * dev::kWave) {
+        const int64_t g = i0 + lane * nw;
+        uint32_t n = 0;
+        if (g < groups) n = off[std::min<int64_t>((g + 1) * dev::kWave, nb)] - off[g * dev::kWave];
+        // the same in every wave of the workgroup
+        for (uint64_t open = __ballot(n > 1u); open; open &= open - 1ull)
+            bin_canon_group(ids, off, nb, (i0 + __builtin_ctzll(open) * nw) * dev::kWave, med_list, big_list, counts,
+                            big_tag);
     }
-    // group too large: each bin on its own (one lane per bin of the group)
-    if (lane < nbins) {
-        const uint32_t a0 = s_off[lane], a1 = s_off[lane + 1];
-        if (a1 - a0 > (uint32_t)kCanonCap) big_list[atomicAdd(counts + 1, 1u)] = big_tag + (uint32_t)(b0 + lane);
-        else if (a1 - a0 > 1) med_list[atomicAdd(counts, 1u)] = (uint32_t)(b0 + lane);
-    }
-    __syncthreads();
+}
+
+// Workgroups of the above for nb bins: one per group, at most as many as are
+// resident at once (eight of 256 threads per CU).
+inline unsigned canon_grid(int64_t nb, int n_cu) {
+    return (unsigned)std::min<int64_t>((nb + dev::kWave - 1) / dev::kWave, 8 * (int64_t)n_cu);
 }
 
 // One workgroup of kMedThreads threads: bin b's segment (at most kCanonCap
-// ids) sorted by rank in LDS.
+// ids) sorted in LDS by a bitonic network over the next power of two.  A step
+// of distance d <= 64 stays inside the 128 values of a wave's 64 pairs, so
+// only the longer ones wait for the whole workgroup.
 constexpr int kMedThreads = 256;
 __device__ __forceinline__ void bin_canon_medium(int32_t *ids, const uint32_t *off, int64_t b) {
     __shared__ int32_t s_val[kCanonCap];
     const uint32_t s0 = off[b], s1 = off[b + 1];
     const int n = (int)(s1 - s0);
-    for (int e = threadIdx.x; e < n; e += kMedThreads) s_val[e] = ids[s0 + e];
+    int m = 2;
+    while (m < n) m <<= 1;
+    for (int e = threadIdx.x; e < m; e += kMedThreads) s_val[e] = e < n ? ids[s0 + e] : INT32_MAX;
     __syncthreads();
-    for (int e = threadIdx.x; e < n; e += kMedThreads) {
-        const int32_t v = s_val[e];
-        int rank = 0;
-        for (int j = 0; j < n; ++j) rank += s_val[j] < v ? 1 : 0;
-        ids[s0 + rank] = v;
-    }
+    for (int k = 2; k <= m; k <<= 1)
+        for (int d = k >> 1; d >= 1; d >>= 1) {
+            for (int i = threadIdx.x; i < m / 2; i += kMedThreads) {
+                const int p = 2 * i - (i & (d - 1)), q = p + d;
+                const int32_t x = s_val[p], y = s_val[q];
+                if ((x > y) == ((p & k) == 0)) {
+                    s_val[p] = y;
+                    s_val[q] = x;
+                }
+            }
+            // the next step's distance: d / 2, or k at the end of a stage
+            if (d > 64 || (d == 1 && k > 64)) __syncthreads();
+            else dev::wave_sync();
+        }
+    __syncthreads();
+    for (int e = threadIdx.x; e < n; e += kMedThreads) ids[s0 + e] = s_val[e];
     __syncthreads();
 }
 
