@@ -185,7 +185,6 @@ bool lattice_table(int Q, Lattice *out);
 // (out[n] = total).  The input is either uint32 counts or uint8 flags
 // (nonzero = 1).  Scratch is allocated from the context.
 agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, hipStream_t s);
-agal_status scan_flags_u8(agal_context ctx, const uint8_t *in, uint32_t *out, int64_t n, hipStream_t s);
 // k exclusive scans of 0/1 flags (out[i] of length n[i] + 1) in one launch; k <= kMultiScanMax.
 constexpr int kMultiScanMax = kMaxLevels + 1;
 // Candidate cells of the largest face in a face-centric flag step: per axis its
@@ -235,9 +234,13 @@ int64_t scan_flags_u8_multi_tiles(const int64_t *n, int k);
 int64_t scan_tiles(int64_t n);
 // Exclusive scan whose sum comes back through mapped host memory (synchronises the stream); status is a
 // zeroed buffer of scan_tiles(n) + 1 words, or null.  timed = false: no kernel timing events even when the
-// context records them (the no-allocation calls create no events).
+// context records them (the no-allocation calls create no events).  cls, when given: the classes of bins that
+// occur among the counts, so that the host launches only the sorts that have work.
+constexpr uint32_t kBinsMedium = 1;   // a bin above kBinClassMedium ids (else every 64 bins fit one LDS segment)
+constexpr uint32_t kBinsBig = 2;      // a bin above kBinClassBig ids
+constexpr uint32_t kBinClassMedium = 32, kBinClassBig = 2048;
 agal_status scan_u32_total(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, uint64_t *status,
-                           uint32_t *total, hipStream_t s, bool timed = true);
+                           uint32_t *total, hipStream_t s, bool timed = true, uint32_t *cls = nullptr);
 // Exclusive scan of the set-bit counts of n 64-bit masks, with the total (synchronises the stream).
 agal_status scan_popc64_total(agal_context ctx, const unsigned long long *masks, uint32_t *out, int64_t n,
                               uint32_t *total, hipStream_t s);

@@ -226,32 +226,24 @@ __global__ void k_b_import(const BodyDev *bodies, int nb, Ctl *ctl) {
     if (bad) atomicOr(&ctl->err, bad);
 }
 
-template <int D>
-__global__ void k_b_bin_count(const BodyDev *bodies, int nb, uint32_t *count_global) {
+// Count (kScatter false) and scatter: a workgroup takes nf faces of one body
+// at a time.
+template <int D, bool kScatter>
+__global__ __launch_bounds__(kPairThreads) void k_b_bin_pairs(const BodyDev *bodies, int nb, int nf,
+                                                              uint32_t *count_global, const uint32_t *off_global,
+                                                              int32_t *ids, int64_t cap_ids, Ctl *ctl) {
     __shared__ uint32_t s_pre[kMaxBodies + 1];
-    const uint32_t nf = lds_prefix(nb, [&](int b) { return (uint32_t)bodies[b].F; }, s_pre);
-    AGAL_THREAD_ITEMS(it, nf) {
-        const int b = find_seg(s_pre, nb, it);
-        const BodyDev &B = bodies[b];
-        bin_count_item<D>(B.aabb, B.F, B.bins, count_global + B.bin_base, it - s_pre[b]);
-    }
-}
-
-template <int D>
-__global__ void k_b_bin_scatter(const BodyDev *bodies, int nb, const uint32_t *off_global, uint32_t *cursor_global,
-                                int32_t *ids, int64_t cap_ids, Ctl *ctl) {
-    __shared__ uint32_t s_pre[kMaxBodies + 1];
-    const uint32_t nf = lds_prefix(nb, [&](int b) { return (uint32_t)bodies[b].F; }, s_pre);
-    const bool over = off_global[bodies[nb - 1].bin_base + bodies[nb - 1].nb] > cap_ids;
-    if (over) {
+    __shared__ PairLds S;
+    const uint32_t total = lds_prefix(nb, [&](int b) { return (uint32_t)((bodies[b].F + nf - 1) / nf); }, s_pre);
+    if (kScatter && off_global[bodies[nb - 1].bin_base + bodies[nb - 1].nb] > cap_ids) {
         if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&ctl->overflow, 1u);
         return;
     }
-    AGAL_THREAD_ITEMS(it, nf) {
+    for (uint32_t it = blockIdx.x; it < total; it += gridDim.x) {
         const int b = find_seg(s_pre, nb, it);
         const BodyDev &B = bodies[b];
-        bin_scatter_item<D>(B.aabb, B.F, B.bins, off_global + B.bin_base, cursor_global + B.bin_base, ids,
-                            it - s_pre[b]);
+        bin_pairs<D, kScatter>(B.aabb, B.F, B.bins, (int64_t)(it - s_pre[b]) * nf, nf, count_global + B.bin_base,
+                               kScatter ? off_global + B.bin_base : nullptr, ids, S);
     }
 }
 
@@ -864,9 +856,10 @@ struct agal_batch_t {
     std::vector<void *> owned;
     uint32_t *d_cnt = nullptr, *d_nodes = nullptr, *d_cursor = nullptr;
     agal::batch::Ctl *d_ctl = nullptr;
-    uint32_t *d_bin_count = nullptr, *d_bin_off = nullptr, *d_bin_cursor = nullptr, *d_big = nullptr, *d_med = nullptr;
+    uint32_t *d_bin_count = nullptr, *d_bin_off = nullptr, *d_big = nullptr, *d_med = nullptr;
     int32_t *d_ids = nullptr;
     int64_t nb_total = 0, cap_ids = 0;
+    int bin_faces = 1;               // faces per workgroup of the bin count and scatter
     uint64_t *d_status = nullptr;
     int64_t status_words = 0;
     std::vector<agal::batch::Seg> seg_store;
@@ -1012,7 +1005,8 @@ static agal_status capture(agal_batch bt) {
     hipLaunchKernelGGL(k_fill_table, dim3(G), dim3(256), 0, s, bt->d_fills, bt->n_fill_init);
     hipLaunchKernelGGL(k_b_init, dim3(G), dim3(256), 0, s, B, nb, bt->d_cnt, bt->d_cursor, bt->d_ctl);
     hipLaunchKernelGGL(k_b_import<D>, dim3(G), dim3(256), 0, s, B, nb, bt->d_ctl);
-    hipLaunchKernelGGL(k_b_bin_count<D>, dim3(G), dim3(256), 0, s, B, nb, bt->d_bin_count);
+    hipLaunchKernelGGL((k_b_bin_pairs<D, false>), dim3(2 * G), dim3(kPairThreads), 0, s, B, nb, bt->bin_faces,
+                       bt->d_bin_count, nullptr, nullptr, (int64_t)0, bt->d_ctl);
     // scans use ticket order; each scan resets the ticket afterwards via the next fill
     // every scan starts from cleared status words and ticket (two fill entries);
     // its grid is the largest tile count any scan of the plan can need
@@ -1031,8 +1025,8 @@ static agal_status capture(agal_batch bt) {
                                st, tk);
     };
     scan(0, bt->bins_seg_off, 1, false);
-    hipLaunchKernelGGL(k_b_bin_scatter<D>, dim3(G), dim3(256), 0, s, B, nb, bt->d_bin_off, bt->d_bin_cursor, bt->d_ids,
-                       bt->cap_ids, bt->d_ctl);
+    hipLaunchKernelGGL((k_b_bin_pairs<D, true>), dim3(2 * G), dim3(kPairThreads), 0, s, B, nb, bt->bin_faces,
+                       bt->d_bin_count, bt->d_bin_off, bt->d_ids, bt->cap_ids, bt->d_ctl);
     hipLaunchKernelGGL(k_b_bin_clear, dim3(G), dim3(256), 0, s, bt->d_bin_off, bt->nb_total, bt->d_ctl);
     hipLaunchKernelGGL(k_b_canon_small, dim3(2 * G), dim3(kCanonThreads), 0, s, bt->d_ids, bt->d_bin_off, bt->nb_total, bt->d_med,
                        bt->d_big, bt->d_ctl);
@@ -1383,6 +1377,15 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
             ncu = 256;
         (void)hipGetLastError();
         bt->fflag_g = face_flag_g(all_faces, ncu);
+        double per_face = 1.0;   // bins of the largest face of any body
+        for (int b = 0; b < bt->nb; ++b) {
+            const BodyDev &X = bt->bodies[b];
+            double p = 1.0;
+            for (int a = 0; a < D; ++a)
+                p *= std::min((double)X.bins.B, std::floor((double)bt->host[b].max_extent[a] * X.bins.s[a]) + 2.0);
+            per_face = std::max(per_face, p);
+        }
+        bt->bin_faces = bin_pair_faces(all_faces, per_face, ncu);
     }
     const int64_t fper_wg = (int64_t)kFaceFlagWaves * bt->fflag_g;
     for (int b = 0; b < bt->nb; ++b) {
@@ -1415,7 +1418,6 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
                                 bt->cap_stream));
     AGAL_TRY(own(bt, &bt->d_bin_count, (size_t)bt->nb_total));
     AGAL_TRY(own(bt, &bt->d_bin_off, (size_t)bt->nb_total + 1));
-    AGAL_TRY(own(bt, &bt->d_bin_cursor, (size_t)bt->nb_total));
     AGAL_TRY(own(bt, &bt->d_ids, (size_t)cap_ids));
     AGAL_TRY(own(bt, &bt->d_big, (size_t)(cap_ids / 2048 + 2)));
     AGAL_TRY(own(bt, &bt->d_med, (size_t)bt->nb_total + 1));
@@ -1490,7 +1492,6 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
     std::vector<Fill> fills;
     auto words = [](size_t bytes) { return (int64_t)((bytes + 3) / 4); };
     fills.push_back({bt->d_bin_count, words(bt->nb_total * 4), 0u});
-    fills.push_back({bt->d_bin_cursor, words(bt->nb_total * 4), 0u});
     fills.push_back({reinterpret_cast<uint32_t *>(bt->d_status), words((size_t)bt->status_words * n_scans * 8), 0u});
     fills.push_back({bt->d_tickets, n_scans, 0u});
     for (int b = 0; b < bt->nb; ++b) {

@@ -3,12 +3,13 @@
 // describes (ids grouped by bin, per-bin counts as offset differences, first
 // index per bin) as a CSR with ascending face ids inside each bin.
 //
-// Kernels: count (one thread per face, atomics per touched bin) -> exclusive
-// scan -> scatter (atomic cursors) -> canonical order (each bin's segment
+// Kernels: count (the faces' (face, bin) pairs, combined per workgroup) ->
+// exclusive scan -> scatter (atomic cursors) -> canonical order (each bin's segment
 // sorted in LDS: small bins by rank, a group of 64 bins at once, larger ones by
 // a workgroup per bin; bins too large for LDS are rebuilt by an ordered sweep
 // over all faces, which only happens when B is tiny).
 #include <algorithm>
+#include <cmath>
 
 #include "agal_internal.hpp"
 #include "device.hpp"
@@ -20,18 +21,12 @@ namespace {
 
 using namespace kern;
 
-#define AGAL_GRID_STRIDE(i, n) \
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
-
-template <int D>
-__global__ void k_bin_count(const float *aabb, int64_t F, dev::BinGrid g, uint32_t *count) {
-    AGAL_GRID_STRIDE(f, F) bin_count_item<D>(aabb, F, g, count, f);
-}
-
-template <int D>
-__global__ void k_bin_scatter(const float *aabb, int64_t F, dev::BinGrid g, const uint32_t *off, uint32_t *cursor,
-                              int32_t *ids) {
-    AGAL_GRID_STRIDE(f, F) bin_scatter_item<D>(aabb, F, g, off, cursor, ids, f);
+template <int D, bool kScatter>
+__global__ __launch_bounds__(kPairThreads) void k_bin_pairs(const float *aabb, int64_t F, dev::BinGrid g, int nf,
+                                                            uint32_t *count, const uint32_t *off, int32_t *ids) {
+    __shared__ PairLds S;
+    for (int64_t f0 = (int64_t)blockIdx.x * nf; f0 < F; f0 += (int64_t)gridDim.x * nf)
+        bin_pairs<D, kScatter>(aabb, F, g, f0, nf, count, off, ids, S);
 }
 
 __global__ __launch_bounds__(kCanonThreads) void k_bin_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,
@@ -54,11 +49,26 @@ __global__ __launch_bounds__(kBigThreads) void k_bin_canon_big(const float *aabb
     for (uint32_t bi = blockIdx.x; bi < nbig; bi += gridDim.x) bin_canon_big_bin<D>(aabb, F, g, off, ids, big_list[bi]);
 }
 
-unsigned grid_for(int64_t n, int threads = 256, int64_t cap = 8192) {
-    int64_t b = (n + threads - 1) / threads;
-    if (b < 1) b = 1;
-    if (b > cap) b = cap;
-    return (unsigned)b;
+// Without a bin above kBinClassMedium ids neither a bin above kRankCap nor a
+// group of 64 bins above one LDS segment exists, so the medium list stays empty.
+static_assert(kBinClassMedium <= (uint32_t)kRankCap && kBinClassMedium * dev::kWave <= (uint32_t)kCanonCap &&
+                  kBinClassBig == (uint32_t)kCanonCap,
+              "classes the scan reports");
+
+template <bool kScatter>
+void launch_pairs(agal_context ctx, agal_geom g, const dev::BinGrid &grid, uint32_t *count, const uint32_t *off,
+                  int32_t *ids, hipStream_t s) {
+    double per_face = 1.0;
+    for (int a = 0; a < g->dim; ++a)
+        per_face *= std::min((double)grid.B, std::floor((double)g->max_extent[a] * grid.s[a]) + 2.0);
+    const int nf = bin_pair_faces(g->F, per_face, ctx->n_cu);
+    const unsigned wgs = (unsigned)std::min<int64_t>((g->F + nf - 1) / nf, 1 << 20);
+    if (g->dim == 3)
+        hipLaunchKernelGGL((k_bin_pairs<3, kScatter>), dim3(wgs), dim3(kPairThreads), 0, s, g->aabb, g->F, grid, nf,
+                           count, off, ids);
+    else
+        hipLaunchKernelGGL((k_bin_pairs<2, kScatter>), dim3(wgs), dim3(kPairThreads), 0, s, g->aabb, g->F, grid, nf,
+                           count, off, ids);
 }
 
 // Validated bin grid of a call: B bins per axis over [lo, hi].
@@ -88,64 +98,58 @@ agal_status grid_spec(const char *what, int D, const float lo[3], const float hi
     return AGAL_OK;
 }
 
-// Work words of one binning call over nb bins: per-bin counts, per-bin
-// scatter cursors, the medium- and big-bin list counters, then the scan's
-// look-back status words (64-bit).  All start at zero.
-int64_t bin_work_words(int64_t nb) { return 2 * nb + 2 + 2 * (scan_tiles(nb) + 1); }
+// Work words of one binning call over nb bins: per-bin counts (used up as
+// cursors by the scatter), the medium- and big-bin list counters, then the
+// scan's look-back status words (64-bit).  All start at zero.
+int64_t bin_work_words(int64_t nb) { return nb + 3 + 2 * (scan_tiles(nb) + 1); }
 
 struct BinWork {
-    uint32_t *count, *cursor, *lists;   // lists[0], lists[1]: medium and big bin counts
+    uint32_t *count, *lists;   // lists[0], lists[1]: medium and big bin counts
     uint64_t *scan_status;
 };
 
 BinWork bin_work(uint32_t *work, int64_t nb) {
-    return BinWork{work, work + nb, work + 2 * nb, reinterpret_cast<uint64_t *>(work + ((2 * nb + 3) & ~int64_t(1)))};
+    return BinWork{work, work + nb, reinterpret_cast<uint64_t *>(work + ((nb + 3) & ~int64_t(1)))};
 }
 
 // Count pass and scan: zeroes `work`, fills off[0..nb] and returns the entry
-// total P (the one host wait).  ctx_timed: the context whose kernel timing
-// records the launches, or null for none.
+// total P and the classes of the bins (the one host wait).  ctx_timed: the
+// context whose kernel timing records the launches, or null for none.
 agal_status bin_count_scan(agal_context ctx, agal_context ctx_timed, agal_geom g, const GridSpec &gs, uint32_t *work,
-                           uint32_t *off, uint32_t *P, hipStream_t s) {
+                           uint32_t *off, uint32_t *P, uint32_t *cls, hipStream_t s) {
     const int64_t nb = gs.nb;
     fill_u32(work, 0u, bin_work_words(nb), s);
     const BinWork w = bin_work(work, nb);
     {
         ProfScope prof(ctx_timed, "bin_count", s);
-        if (g->dim == 3)
-            hipLaunchKernelGGL(k_bin_count<3>, dim3(grid_for(g->F)), dim3(256), 0, s, g->aabb, g->F, gs.grid, w.count);
-        else
-            hipLaunchKernelGGL(k_bin_count<2>, dim3(grid_for(g->F)), dim3(256), 0, s, g->aabb, g->F, gs.grid, w.count);
+        launch_pairs<false>(ctx, g, gs.grid, w.count, nullptr, nullptr, s);
     }
     AGAL_TRY_HIP(hipGetLastError());
-    return scan_u32_total(ctx, w.count, off, nb, w.scan_status, P, s, ctx_timed != nullptr);
+    return scan_u32_total(ctx, w.count, off, nb, w.scan_status, P, s, ctx_timed != nullptr, cls);
 }
 
-// Scatter and canonical order into ids[0..P) (offsets from bin_count_scan);
-// med: room for nb bin indices, big: for P / kCanonCap + 1.
+// Scatter and canonical order into ids[0..P) (offsets, P and cls from
+// bin_count_scan); med: room for nb bin indices where cls has kBinsMedium, big:
+// for P / kCanonCap + 1 where it has kBinsBig.
 agal_status bin_scatter_canon(agal_context ctx, agal_context ctx_timed, agal_geom g, const GridSpec &gs, uint32_t *work,
-                              const uint32_t *off, int32_t *ids, uint32_t P, uint32_t *med, uint32_t *big,
-                              hipStream_t s) {
+                              const uint32_t *off, int32_t *ids, uint32_t P, uint32_t cls, uint32_t *med,
+                              uint32_t *big, hipStream_t s) {
     const int64_t nb = gs.nb;
     const BinWork w = bin_work(work, nb);
     {
         ProfScope prof(ctx_timed, "bin_scatter", s);
-        if (g->dim == 3)
-            hipLaunchKernelGGL(k_bin_scatter<3>, dim3(grid_for(g->F)), dim3(256), 0, s, g->aabb, g->F, gs.grid, off,
-                               w.cursor, ids);
-        else
-            hipLaunchKernelGGL(k_bin_scatter<2>, dim3(grid_for(g->F)), dim3(256), 0, s, g->aabb, g->F, gs.grid, off,
-                               w.cursor, ids);
+        launch_pairs<true>(ctx, g, gs.grid, w.count, off, ids, s);
     }
     {
         ProfScope prof(ctx_timed, "bin_canon", s);
         hipLaunchKernelGGL(k_bin_canon_small, dim3(canon_grid(nb, ctx->n_cu)), dim3(kCanonThreads), 0, s, ids, off, nb,
                            med, big, w.lists);
-        hipLaunchKernelGGL(k_bin_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0, s,
-                           ids, off, med, w.lists);
+        if (cls & kBinsMedium)
+            hipLaunchKernelGGL(k_bin_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0,
+                               s, ids, off, med, w.lists);
     }
     const unsigned big_grid = (unsigned)std::min<int64_t>((int64_t)P / kCanonCap + 1, 256);
-    {
+    if (cls & kBinsBig) {
         ProfScope prof(ctx_timed, "bin_canon_big", s);
         if (g->dim == 3)
             hipLaunchKernelGGL(k_bin_canon_big<3>, dim3(big_grid), dim3(kBigThreads), 0, s, g->aabb, g->F, gs.grid,
@@ -223,14 +227,14 @@ agal_status agal_bin_faces(agal_geom g, const float lo[3], const float hi[3], in
     };
     agal_status st = dev_alloc(ctx->mem, &work, (size_t)bin_work_words(nb), s);
     if (st == AGAL_OK) st = dev_alloc(ctx->mem, &bn->off, (size_t)nb + 1, s);
-    uint32_t P = 0;
-    if (st == AGAL_OK) st = bin_count_scan(ctx, ctx, g, gs, work, bn->off, &P, s);
+    uint32_t P = 0, cls = 0;
+    if (st == AGAL_OK) st = bin_count_scan(ctx, ctx, g, gs, work, bn->off, &P, &cls, s);
     if (st != AGAL_OK) return cleanup(st);
     bn->P = P;
     st = dev_alloc(ctx->mem, &bn->ids, (size_t)std::max<uint32_t>(P, 1u), s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &med, (size_t)nb, s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &big, (size_t)P / kCanonCap + 1, s);
-    if (st == AGAL_OK) st = bin_scatter_canon(ctx, ctx, g, gs, work, bn->off, bn->ids, P, med, big, s);
+    if (st == AGAL_OK && (cls & kBinsMedium)) st = dev_alloc(ctx->mem, &med, (size_t)nb, s);
+    if (st == AGAL_OK && (cls & kBinsBig)) st = dev_alloc(ctx->mem, &big, (size_t)P / kCanonCap + 1, s);
+    if (st == AGAL_OK) st = bin_scatter_canon(ctx, ctx, g, gs, work, bn->off, bn->ids, P, cls, med, big, s);
     if (cleanup(st) != AGAL_OK) return st;
     *out = bn;
     return AGAL_OK;
@@ -255,8 +259,9 @@ agal_status agal_bin_faces_noalloc(agal_geom g, const float lo[3], const float h
                     "hipGetSymbolAddress failed when the context was created");
     // scratch: the work words, the medium-bin list (one word per bin), then
     // the big-bin list (at most ids_capacity / kCanonCap + 1 bins hold more
-    // than kCanonCap ids)
-    const int64_t work_words = bin_work_words(gs.nb);
+    // than kCanonCap ids).  The limit is the documented one: room for a cursor
+    // per bin beside its count, and a status word per 2,048 bins.
+    const int64_t work_words = 2 * gs.nb + 2 + 2 * ((gs.nb + 2047) / 2048 + 1);
     const int64_t big_words = std::min<int64_t>(ids_capacity, (int64_t)UINT32_MAX) / kCanonCap + 1;
     if (work_words + gs.nb + big_words > kNoallocScratchWords)
         return fail(AGAL_EINVAL,
@@ -265,13 +270,13 @@ agal_status agal_bin_faces_noalloc(agal_geom g, const float lo[3], const float h
                     (long long)gs.nb, (long long)ids_capacity, (long long)(work_words + gs.nb + big_words),
                     (long long)kNoallocScratchWords, (long long)((kNoallocScratchWords - big_words) / 3 - 2048));
     hipStream_t s = (hipStream_t)stream;
-    uint32_t P = 0;
-    AGAL_TRY(bin_count_scan(ctx, nullptr, g, gs, base, d_offsets, &P, s));
+    uint32_t P = 0, cls = 0;
+    AGAL_TRY(bin_count_scan(ctx, nullptr, g, gs, base, d_offsets, &P, &cls, s));
     *n_entries = P;
     if ((int64_t)P > ids_capacity)
         return fail(AGAL_ECAPACITY, "agal_bin_faces_noalloc: %u (face, bin) entries exceed ids_capacity %lld", P,
                     (long long)ids_capacity);
-    return bin_scatter_canon(ctx, nullptr, g, gs, base, d_offsets, d_face_ids, P, base + work_words,
+    return bin_scatter_canon(ctx, nullptr, g, gs, base, d_offsets, d_face_ids, P, cls, base + work_words,
                              base + work_words + gs.nb, s);
 }
 

@@ -360,7 +360,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 // their index from a ticket counter in launch order, publish their aggregate,
 // then sum predecessors' values until one has published its inclusive
 // prefix.  Status word: bits 32..33 flag (1 aggregate, 2 inclusive), low 32
-// bits the value.  All status traffic is agent-scope atomics, so tiles on
+// bits the value, bits 34..35 class bits of the tiles, combined by OR.  All status traffic is agent-scope atomics, so tiles on
 // different XCDs observe each other.
 // ---------------------------------------------------------------------------
 constexpr uint64_t kAgg = 1ull << 32;
@@ -374,13 +374,14 @@ __device__ __forceinline__ uint64_t status_load(uint64_t *p) {
 }
 
 // Called by one full wave; returns the exclusive prefix of `tile` (uniform).
-__device__ __forceinline__ uint32_t lookback_wave(uint64_t *status, uint32_t tile, uint32_t aggregate) {
+// cls (uniform): the tile's two class bits, on return those of all tiles up to it.
+__device__ __forceinline__ uint32_t lookback_wave(uint64_t *status, uint32_t tile, uint32_t aggregate, uint32_t &cls) {
     const int lane = lane_id();
     if (tile == 0) {
-        if (lane == 0) status_store(&status[0], kInc | aggregate);
+        if (lane == 0) status_store(&status[0], kInc | aggregate | ((uint64_t)cls << 34));
         return 0u;
     }
-    if (lane == 0) status_store(&status[tile], kAgg | aggregate);
+    if (lane == 0) status_store(&status[tile], kAgg | aggregate | ((uint64_t)cls << 34));
     uint32_t prefix = 0;
     int64_t base = (int64_t)tile - 1;
     while (true) {
@@ -392,8 +393,11 @@ __device__ __forceinline__ uint32_t lookback_wave(uint64_t *status, uint32_t til
                 if ((w >> 32) == 0) __builtin_amdgcn_s_sleep(1);
             } while ((w >> 32) == 0);
         }
-        uint64_t inc_mask = __ballot((w >> 32) == 2);
+        uint64_t inc_mask = __ballot(((w >> 32) & 3u) == 2);
         uint32_t val = (uint32_t)w;
+        // tiles past the nearest inclusive one are counted in it
+        const uint64_t used = inc_mask ? (inc_mask & (0ull - inc_mask)) | ((inc_mask & (0ull - inc_mask)) - 1ull) : ~0ull;
+        cls |= (__ballot((w >> 34) & 1u) & used ? 1u : 0u) | (__ballot((w >> 35) & 1u) & used ? 2u : 0u);
         if (inc_mask) {
             int first = __ffsll((unsigned long long)inc_mask) - 1;  // nearest inclusive predecessor
             uint32_t contrib = lane <= first ? val : 0u;
@@ -403,8 +407,12 @@ __device__ __forceinline__ uint32_t lookback_wave(uint64_t *status, uint32_t til
         prefix += wave_sum(val);
         base -= kWave;
     }
-    if (lane == 0) status_store(&status[tile], kInc | (prefix + aggregate));
+    if (lane == 0) status_store(&status[tile], kInc | (uint64_t)(prefix + aggregate) | ((uint64_t)cls << 34));
     return prefix;
+}
+__device__ __forceinline__ uint32_t lookback_wave(uint64_t *status, uint32_t tile, uint32_t aggregate) {
+    uint32_t cls = 0;
+    return lookback_wave(status, tile, aggregate, cls);
 }
 
 }  // namespace dev

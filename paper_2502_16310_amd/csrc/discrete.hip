@@ -401,13 +401,13 @@ agal_status disc_pairs(agal_geom g, agal_bins bn, const DiscGrid &G, hipStream_t
                            count, nullptr, nullptr, nullptr);
     }
     AGAL_TRY_HIP(hipGetLastError());
-    uint32_t P = 0;
-    st = scan_u32_total(ctx, count, bn->off, nb, nullptr, &P, s);
+    uint32_t P = 0, cls = 0;
+    st = scan_u32_total(ctx, count, bn->off, nb, nullptr, &P, s, true, &cls);
     if (st != AGAL_OK) return done(st);
     bn->P = P;
     st = dev_alloc(ctx->mem, &bn->ids, (size_t)std::max<uint32_t>(P, 1u), s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &med, (size_t)nb, s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &big, (size_t)P / kCanonCap + 1, s);
+    if (st == AGAL_OK && (cls & kBinsMedium)) st = dev_alloc(ctx->mem, &med, (size_t)nb, s);
+    if (st == AGAL_OK && (cls & kBinsBig)) st = dev_alloc(ctx->mem, &big, (size_t)P / kCanonCap + 1, s);
     if (st != AGAL_OK) return done(st);
     {
         ProfScope prof(ctx, "bin_disc_scatter", s);
@@ -420,10 +420,13 @@ agal_status disc_pairs(agal_geom g, agal_bins bn, const DiscGrid &G, hipStream_t
         ProfScope prof(ctx, "bin_canon", s);
         hipLaunchKernelGGL(k_disc_canon_small, dim3(canon_grid(nb, ctx->n_cu)), dim3(kCanonThreads), 0, s,
                            bn->ids, bn->off, nb, med, big, lists);
-        hipLaunchKernelGGL(k_disc_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0, s,
-                           bn->ids, bn->off, med, lists);
-        hipLaunchKernelGGL((k_disc_canon_big<D>), dim3((unsigned)std::min<int64_t>((int64_t)P / kCanonCap + 1, 256)),
-                           dim3(kBigThreads), 0, s, g->rec, F, G, bn->off, bn->ids, big, lists);
+        if (cls & kBinsMedium)
+            hipLaunchKernelGGL(k_disc_canon_medium, dim3((unsigned)std::min<int64_t>(nb, 8192)), dim3(kMedThreads), 0,
+                               s, bn->ids, bn->off, med, lists);
+        if (cls & kBinsBig)
+            hipLaunchKernelGGL((k_disc_canon_big<D>),
+                               dim3((unsigned)std::min<int64_t>((int64_t)P / kCanonCap + 1, 256)), dim3(kBigThreads),
+                               0, s, g->rec, F, G, bn->off, bn->ids, big, lists);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return done(fail(AGAL_EHIP, "agal_bin_faces_discrete: launch failed: %s", hipGetErrorString(e)));

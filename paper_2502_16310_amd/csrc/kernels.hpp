@@ -123,135 +123,264 @@ __device__ __forceinline__ uint32_t add_one_combined(uint32_t *p) {
     return slot;
 }
 
-template <int D>
-__device__ __forceinline__ void bin_count_item(const float *aabb, int64_t F, const dev::BinGrid &g, uint32_t *count,
-                                               int64_t f) {
-    {
+// Count and scatter: one workgroup per nf consecutive faces (nf a power of two
+// up to kPairThreads).  The (face, bin) pairs of its faces are taken
+// kPairThreads x kPairRounds at a time, one per thread and round, and first
+// meet in an LDS hash table of their bins: each pair takes its rank among the
+// chunk's pairs of its bin there, and each distinct bin then goes out as one
+// device atomic, all of a chunk's in flight together.  What bounds the passes is
+// those atomics, performed past the per-XCD L2: neighbouring faces share their
+// bins, so a chunk sends a fifth of its pairs.  A thread per face looping over
+// its bins, equal bins of a wave combined in up to four rounds, took 33 us to
+// count and 38 us to scatter 327,680 faces over 128^3 bins and 18 and 68 us for
+// 320 faces of ~20 bins each.
+constexpr int kPairThreads = 256;
+constexpr int kPairRounds = 4;
+constexpr int kPairTable = 2048;   // slots, twice a chunk's pairs
+
+struct PairLds {
+    uint4 key4[kPairTable / 4];   // bin index, ~0 empty (as uint4 for the clearing stores)
+    uint4 val4[kPairTable / 4];   // pairs of the chunk in the bin, then (scatter) the chunk's first slot there
+    uint32_t pre[kPairThreads], bin0[kPairThreads], nx[kPairThreads], ny[kPairThreads];
+    uint32_t wsum[kPairThreads / dev::kWave];
+};
+
+// kScatter false: count[bin] += the faces' pairs.  true: count holds the totals
+// of the count pass and is used up (down to zero) as the cursor; the pairs go
+// to ids at off[bin] + the place taken.
+template <int D, bool kScatter>
+__device__ __forceinline__ void bin_pairs(const float *aabb, int64_t F, const dev::BinGrid &g, int64_t f0, int nf,
+                                          uint32_t *count, const uint32_t *off, int32_t *ids, PairLds &S) {
+    const int tid = threadIdx.x, lane = dev::lane_id(), w = tid / dev::kWave;
+    uint32_t *key = reinterpret_cast<uint32_t *>(S.key4), *val = reinterpret_cast<uint32_t *>(S.val4);
+    uint32_t n = 0;
+    if (tid < nf && f0 + tid < F) {
         int lo[3], hi[3];
-        face_bin_range<D>(aabb, F, f, g, lo, hi);
-        for (int z = lo[2]; z <= hi[2]; ++z)
-            for (int y = lo[1]; y <= hi[1]; ++y)
-                for (int x = lo[0]; x <= hi[0]; ++x)
-                    (void)add_one_combined(count + ((int64_t)z * g.B + y) * g.B + x);
+        face_bin_range<D>(aabb, F, f0 + tid, g, lo, hi);
+        uint32_t m[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) m[a] = (uint32_t)max(0, hi[a] - lo[a] + 1);
+        n = m[0] * m[1] * m[2];   // at most B^D <= 2^31
+        // (nf > 1: the faces' sum has to fit 32 bits; bin_pair_faces gives nf > 1 to faces of at most 512 bins, and
+        // a batch whose faces have outgrown its plan by so much is over its capacity all the same)
+        if (nf > 1) n = min(n, 1u << 24);
+        S.bin0[tid] = ((uint32_t)lo[2] * (uint32_t)g.B + (uint32_t)lo[1]) * (uint32_t)g.B + (uint32_t)lo[0];
+        S.nx[tid] = m[0];
+        S.ny[tid] = m[1];
     }
+    const uint32_t incl = dev::wave_inclusive_sum(n);
+    if (lane == dev::kWave - 1) S.wsum[w] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int j = 0; j < kPairThreads / dev::kWave; ++j) {
+        before += j < w ? S.wsum[j] : 0u;
+        total += S.wsum[j];
+    }
+    S.pre[tid] = before + incl - n;   // faces past nf: the total
+    constexpr uint32_t kChunk = kPairThreads * kPairRounds;
+    for (uint64_t c0 = 0; c0 < total; c0 += kChunk) {
+#pragma unroll
+        for (int k = 0; k < kPairTable / 4 / kPairThreads; ++k) {
+            S.key4[tid + k * kPairThreads] = make_uint4(~0u, ~0u, ~0u, ~0u);
+            S.val4[tid + k * kPairThreads] = make_uint4(0u, 0u, 0u, 0u);
+        }
+        __syncthreads();
+        uint32_t slot[kPairRounds], rank[kPairRounds];
+        int32_t face[kPairRounds];
+#pragma unroll
+        for (int r = 0; r < kPairRounds; ++r) {
+            const uint64_t v64 = c0 + (uint32_t)(r * kPairThreads + tid);
+            const uint32_t v = (uint32_t)v64;
+            face[r] = -1;
+            if (v64 < total) {
+                int k = 0;   // the last face whose pairs start at or before v (the faces with none end the list)
+#pragma unroll
+                for (int step = kPairThreads / 2; step >= 1; step >>= 1)
+                    if (k + step < nf && S.pre[k + step] <= v) k += step;
+                const uint32_t u = v - S.pre[k], nx = S.nx[k], ny = S.ny[k];
+                const uint32_t q = u / nx, z = q / ny;
+                const uint32_t b = S.bin0[k] + (z * (uint32_t)g.B + (q - z * ny)) * (uint32_t)g.B + (u - q * nx);
+                uint32_t h = (b * 2654435761u) >> 21;   // 11 bits: kPairTable slots
+                while (true) {   // at most kChunk of kPairTable slots are taken
+                    const uint32_t prev = atomicCAS(&key[h], ~0u, b);
+                    if (prev == ~0u || prev == b) break;
+                    h = (h + 1) & (kPairTable - 1);
+                }
+                face[r] = (int32_t)(f0 + k);
+                slot[r] = h;
+                rank[r] = atomicAdd(&val[h], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t base[kPairTable / kPairThreads];
+#pragma unroll
+        for (int k = 0; k < kPairTable / kPairThreads; ++k) {
+            const int h = tid + k * kPairThreads;
+            const uint32_t b = key[h];
+            if (b == ~0u) continue;
+            const uint32_t c = val[h];
+            if constexpr (kScatter) base[k] = off[b] + (atomicSub(count + b, c) - c);
+            else atomicAdd(count + b, c);
+        }
+        if constexpr (kScatter) {
+#pragma unroll
+            for (int k = 0; k < kPairTable / kPairThreads; ++k) {
+                const int h = tid + k * kPairThreads;
+                if (key[h] != ~0u) val[h] = base[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kPairRounds; ++r)
+                if (face[r] >= 0) ids[val[slot[r]] + rank[r]] = face[r];
+        }
+        __syncthreads();
+    }
+    __syncthreads();   // before the next faces' sums
 }
 
-template <int D>
-__device__ __forceinline__ void bin_scatter_item(const float *aabb, int64_t F, const dev::BinGrid &g,
-                                                 const uint32_t *off, uint32_t *cursor, int32_t *ids, int64_t f) {
-    {
-        int lo[3], hi[3];
-        face_bin_range<D>(aabb, F, f, g, lo, hi);
-        for (int z = lo[2]; z <= hi[2]; ++z)
-            for (int y = lo[1]; y <= hi[1]; ++y)
-                for (int x = lo[0]; x <= hi[0]; ++x) {
-                    int64_t b = ((int64_t)z * g.B + y) * g.B + x;
-                    uint32_t pos = off[b] + add_one_combined(cursor + b);
-                    ids[pos] = (int32_t)f;
-                }
-    }
+// Faces per workgroup of the above: as many as give every CU two workgroups,
+// and no more than fill one chunk when every face has the bins of the largest
+// (per_face).
+inline int bin_pair_faces(int64_t F, double per_face, int n_cu) {
+    int nf = kPairThreads;
+    while (nf > 1 && (F / nf < 2 * (int64_t)n_cu || nf * per_face > (double)(kPairThreads * kPairRounds))) nf >>= 1;
+    return nf;
 }
 
 // Canonical order of one bin of at most kRankCap ids costs each id a pass over
 // the bin's ids in LDS; a larger bin is sorted by a network, whose steps grow
 // with log^2 instead of with the bin.  Measured, small + medium kernel, against
 // ranks alone by one wave per group: 81,920 faces over 16^3 box bins (~170 ids in
-// a bin) 833 -> 29 us, sampled-point bins 190 -> 13 us; 327,680 faces over 128^3
-// bins (1 or 2 ids) 60 -> 42 us; 40,500 faces over 50^3 bins 47 -> 15 us.
+// a bin) 833 -> 26 us, sampled-point bins 190 -> 25 us; 327,680 faces over 128^3
+// bins (~34 ids in an occupied bin) 60 -> 36 us, 40,500 over 50^3 47 -> 16 us.
 constexpr int kRankCap = 64;
 constexpr int kCanonThreads = 256;
+constexpr int kCanonWaves = kCanonThreads / dev::kWave;
+constexpr int kWaveCap = 128;   // ids of a group that one wave sorts by itself (two a lane)
 
-// Sort ids[s0, s1) (nbins bins whose offsets are in s_off) by rank: each
-// entry's position inside its bin is the number of smaller ids there.  Bins
-// above kRankCap ids are left as they are.  One workgroup of kCanonThreads; a
-// thread's ids are loaded together.
-__device__ __forceinline__ void rank_sort_segment(int32_t *ids, const uint32_t *s_off, int nbins, uint32_t s0,
-                                                  uint32_t s1, int32_t *s_val) {
-    constexpr int PER = kCanonCap / kCanonThreads;
-    const int n = (int)(s1 - s0);
+// LDS of one group of 64 bins: bounds and ids.
+struct CanonLds {
+    uint32_t off[kCanonWaves][dev::kWave + 1];
+    int32_t val[kCanonCap];
+};
+
+// Sort ids[s0, s1) (64 bins whose offsets are in s_off) by rank: each id's
+// position inside its bin is the number of smaller ids there.  Bins of at most
+// kLaneRank ids: an id per lane, which reads its bin's ids from LDS.  Up to
+// kRankCap: a bin per wave, an id per lane, every id broadcast to the wave from
+// its register (a bin of 50 took each of its ids 50 LDS reads before).  Larger
+// bins are left as they are.  NT threads (a wave, or the workgroup), t of them
+// the caller; a thread's ids are loaded together.
+constexpr int kLaneRank = 16;
+template <int NT, class Sync>
+__device__ __forceinline__ void rank_sort_segment(int32_t *ids, const uint32_t *s_off, uint32_t s0, uint32_t s1,
+                                                  int32_t *s_val, int t, Sync &&sync) {
+    constexpr int PER = (NT == dev::kWave ? kWaveCap : kCanonCap) / NT;
+    const int n = (int)(s1 - s0), lane = dev::lane_id(), wv = t / dev::kWave;
     int32_t own[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = (int)threadIdx.x + k * kCanonThreads;
-        own[k] = e < n ? ids[s0 + e] : 0;
-    }
+    for (int k = 0; k < PER; ++k) own[k] = t + k * NT < n ? ids[s0 + t + k * NT] : 0;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = (int)threadIdx.x + k * kCanonThreads;
-        if (e < n) s_val[e] = own[k];
-    }
-    __syncthreads();
+    for (int k = 0; k < PER; ++k)
+        if (t + k * NT < n) s_val[t + k * NT] = own[k];
+    sync();
+    const int l = (int)(s_off[lane + 1] - s_off[lane]);   // of bin `lane`
+    if (__ballot(l > 1 && l <= kLaneRank)) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = (int)threadIdx.x + k * kCanonThreads;
-        if (e >= n) continue;
-        uint32_t pos = s0 + (uint32_t)e;
-        // bin of entry e: last bin whose start <= pos (the non-empty one holding it)
-        int lo = 0, hi = nbins - 1;
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= pos) lo = mid; else hi = mid - 1;
+        for (int k = 0; k < PER; ++k) {
+            const int e = t + k * NT;
+            if (e >= n) continue;
+            // bin of entry e: the last one starting at or before it
+            const uint32_t pos = s0 + (uint32_t)e;
+            int bin = 0;
+#pragma unroll
+            for (int step = dev::kWave / 2; step >= 1; step >>= 1) bin += s_off[bin + step] <= pos ? step : 0;
+            const int bs = (int)(s_off[bin] - s0), be = (int)(s_off[bin + 1] - s0);
+            if (be - bs > kLaneRank) continue;
+            const int32_t v = own[k];
+            int rank = 0;
+            // four ids in flight (past the end: the entry's own id, which counts 0)
+            for (int j = bs; j < be; j += 4) {
+                int32_t x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = s_val[j + u < be ? j + u : e];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) rank += x[u] < v ? 1 : 0;
+            }
+            ids[s0 + bs + rank] = v;
         }
-        const int bs = (int)(s_off[lo] - s0), be = (int)(s_off[lo + 1] - s0);
-        if (be - bs > kRankCap) continue;
-        const int32_t v = own[k];
+    }
+    int k = 0;
+    for (uint64_t m = __ballot(l > kLaneRank && l <= kRankCap); m; m &= m - 1ull, ++k) {
+        if (k % (NT / dev::kWave) != wv) continue;
+        const int bin = __builtin_ctzll(m);
+        const int bs = (int)(s_off[bin] - s0), len = __builtin_amdgcn_readlane(l, bin);
+        const int32_t v = lane < len ? s_val[bs + lane] : INT32_MAX;
         int rank = 0;
-        // four ids in flight (past the end: the entry's own id, which counts 0)
-        for (int j = bs; j < be; j += 4) {
-            int32_t x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = s_val[j + u < be ? j + u : e];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) rank += x[u] < v ? 1 : 0;
-        }
-        ids[s0 + bs + rank] = v;
+        for (int j = 0; j < len; ++j) rank += __builtin_amdgcn_readlane(v, j) < v ? 1 : 0;
+        if (lane < len) ids[s0 + bs + rank] = v;
     }
 }
 
-// One workgroup: the group of 64 consecutive bins starting at b0.  A group
-// whose ids fit the LDS segment has its bins of at most kRankCap ids
-// rank-sorted here in one go.  Every other bin with more than one id goes to a
-// list: the medium list (at most kCanonCap ids: sorted by a workgroup per bin)
-// or, tagged with big_tag, the big list (rebuilt by an ordered sweep).  Lists
-// are appended through counters (counts[0], counts[1] = medium and big counts).
+// The group of 64 consecutive bins starting at b0, by NT threads (t of them the
+// caller; s_off and s_val their LDS).  A group whose ids fit the LDS segment
+// has its bins of at most kRankCap ids rank-sorted here in one go.  Every other
+// bin with more than one id goes to a list: the medium list (at most kCanonCap
+// ids: sorted by a workgroup per bin) or, tagged with big_tag, the big list
+// (rebuilt by an ordered sweep).  Lists are appended through counters
+// (counts[0], counts[1] = medium and big counts).
+template <int NT, class Sync>
 __device__ __forceinline__ void bin_canon_group(int32_t *ids, const uint32_t *off, int64_t nb, int64_t b0,
                                                 uint32_t *med_list, uint32_t *big_list, uint32_t *counts,
-                                                uint32_t big_tag) {
-    __shared__ uint32_t s_off[dev::kWave + 1];
-    __shared__ int32_t s_val[kCanonCap];
+                                                uint32_t big_tag, uint32_t *s_off, int32_t *s_val, int t,
+                                                Sync &&sync) {
     const int nbins = (int)std::min<int64_t>(dev::kWave, nb - b0);
-    const int tid = threadIdx.x;
-    if (tid <= nbins) s_off[tid] = off[b0 + tid];
-    __syncthreads();
+    for (int i = t; i <= dev::kWave; i += NT) s_off[i] = off[b0 + min(i, nbins)];   // bins past the last: empty
+    sync();
     const uint32_t g0 = s_off[0], g1 = s_off[nbins];
     const bool fits = g1 - g0 <= (uint32_t)kCanonCap;
-    if (tid < nbins) {
-        const uint32_t a0 = s_off[tid], a1 = s_off[tid + 1];
-        if (a1 - a0 > (uint32_t)kCanonCap) big_list[atomicAdd(counts + 1, 1u)] = big_tag + (uint32_t)(b0 + tid);
-        else if (a1 - a0 > (fits ? (uint32_t)kRankCap : 1u)) med_list[atomicAdd(counts, 1u)] = (uint32_t)(b0 + tid);
+    if (t < nbins) {
+        const uint32_t a0 = s_off[t], a1 = s_off[t + 1];
+        if (a1 - a0 > (uint32_t)kCanonCap) big_list[atomicAdd(counts + 1, 1u)] = big_tag + (uint32_t)(b0 + t);
+        else if (a1 - a0 > (fits ? (uint32_t)kRankCap : 1u)) med_list[atomicAdd(counts, 1u)] = (uint32_t)(b0 + t);
     }
-    if (fits && g1 - g0 > 1) rank_sort_segment(ids, s_off, nbins, g0, g1, s_val);
-    __syncthreads();   // before the next group's offsets and ids
+    if (fits) rank_sort_segment<NT>(ids, s_off, g0, g1, s_val, t, sync);
+    sync();   // before the next group's offsets and ids
 }
 
 // Workgroup w of nw: the groups w, w + nw, ... of 64 bins each.  Only the groups
 // that hold at least two ids are opened, found 64 at a time from one load of
 // their bounds: of a body's bins at a fine density most groups are empty (2^21
 // bins over 327,680 faces: 87 % hold at most one id).  The full ones lie next to
-// each other, along the body, so a workgroup's groups are nw apart.
+// each other, along the body, so a workgroup's groups are nw apart.  Groups of at
+// most kWaveCap ids are sorted by a wave each, side by side; the others by the
+// whole workgroup, one after the other.
 __device__ __forceinline__ void bin_canon_groups(int32_t *ids, const uint32_t *off, int64_t nb, int64_t w, int64_t nw,
                                                  uint32_t *med_list, uint32_t *big_list, uint32_t *counts,
                                                  uint32_t big_tag) {
-    const int lane = dev::lane_id();
+    __shared__ CanonLds S;
+    const int lane = dev::lane_id(), wv = (int)threadIdx.x / dev::kWave;
     const int64_t groups = (nb + dev::kWave - 1) / dev::kWave;
     for (int64_t i0 = w; i0 < groups; i0 += nw * dev::kWave) {
         const int64_t g = i0 + lane * nw;
         uint32_t n = 0;
         if (g < groups) n = off[std::min<int64_t>((g + 1) * dev::kWave, nb)] - off[g * dev::kWave];
         // the same in every wave of the workgroup
-        for (uint64_t open = __ballot(n > 1u); open; open &= open - 1ull)
-            bin_canon_group(ids, off, nb, (i0 + __builtin_ctzll(open) * nw) * dev::kWave, med_list, big_list, counts,
-                            big_tag);
+        const uint64_t small = __ballot(n > 1u && n <= (uint32_t)kWaveCap);
+        int k = 0;
+        for (uint64_t open = small; open; open &= open - 1ull, ++k)
+            if (k % kCanonWaves == wv)
+                bin_canon_group<dev::kWave>(ids, off, nb, (i0 + __builtin_ctzll(open) * nw) * dev::kWave, med_list,
+                                            big_list, counts, big_tag, S.off[wv], S.val + wv * kWaveCap, lane,
+                                            [] { dev::wave_sync(); });
+        const uint64_t large = __ballot(n > (uint32_t)kWaveCap);
+        if (!large) continue;
+        __syncthreads();
+        for (uint64_t open = large; open; open &= open - 1ull)
+            bin_canon_group<kCanonThreads>(ids, off, nb, (i0 + __builtin_ctzll(open) * nw) * dev::kWave, med_list,
+                                           big_list, counts, big_tag, S.off[0], S.val, (int)threadIdx.x,
+                                           [] { __syncthreads(); });
     }
 }
 

@@ -160,21 +160,37 @@ void fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s) { fill(p, v, n,
 // ---------------------------------------------------------------------------
 // exclusive scan (decoupled look-back)
 // ---------------------------------------------------------------------------
-constexpr int kScanThreads = 256;
+constexpr int kScanThreads = 256;   // the flag scans: few tiles each
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
+// The count scan runs over up to 2^21 bins: tiles of 8,192, since every tile
+// takes a ticket, one device atomic on one word, and those serialise (2^21
+// counts: 1,024 tiles of 2,048 22 us, 256 tiles 10.6 us).
+constexpr int kBigScanThreads = 1024;
+constexpr int kBigScanTile = kBigScanThreads * kScanItems;
 
+// Elements i .. i + 7 of a scan's input (i a multiple of eight; zeros from n
+// on), with 16-byte loads where all eight exist and the array is aligned.
 struct LoadU32 {
     const uint32_t *p;
-    __device__ uint32_t operator()(int64_t i) const { return p[i]; }
-};
-struct LoadFlagU8 {
-    const uint8_t *p;
-    __device__ uint32_t operator()(int64_t i) const { return p[i] != 0 ? 1u : 0u; }
+    __device__ void load8(int64_t i, int64_t n, uint32_t (&v)[kScanItems]) const {
+        if (i + kScanItems <= n && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
+            const uint4 *q = reinterpret_cast<const uint4 *>(p + i);
+            const uint4 a = q[0], b = q[1];
+            v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+            v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k) v[k] = i + k < n ? p[i + k] : 0u;
+        }
+    }
 };
 struct LoadPopc64 {
     const unsigned long long *p;
-    __device__ uint32_t operator()(int64_t i) const { return (uint32_t)__popcll(p[i]); }
+    __device__ void load8(int64_t i, int64_t n, uint32_t (&v)[kScanItems]) const {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) v[k] = i + k < n ? (uint32_t)__popcll(p[i + k]) : 0u;
+    }
 };
 
 HostSignal host_signal(agal_context ctx) {
@@ -203,39 +219,65 @@ agal_status wait_signal(agal_context ctx, hipStream_t s, const HostSignal &sig, 
     return AGAL_OK;
 }
 
-template <class In>
-__global__ __launch_bounds__(kScanThreads) void k_scan(In in, uint32_t *out, int64_t n, uint64_t *status,
+// kClass: host_total[1] receives the classes of bins among the counts.
+template <class In, bool kClass>
+__global__ __launch_bounds__(kBigScanThreads) void k_scan(In in, uint32_t *out, int64_t n, uint64_t *status,
                                                        uint32_t *ticket, uint32_t *host_total, HostSignal sig) {
-    __shared__ uint32_t s_tile, s_prefix;
-    __shared__ uint32_t s_wsum[kScanThreads / dev::kWave];
+    __shared__ uint32_t s_tile, s_prefix, s_cls;
+    constexpr int W = kBigScanThreads / dev::kWave;
+    __shared__ uint32_t s_wsum[W], s_wcls[W];
     if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
     __syncthreads();
     const uint32_t tile = s_tile;
-    const int64_t base = (int64_t)tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    const int64_t base = (int64_t)tile * kBigScanTile + (int64_t)threadIdx.x * kScanItems;
     uint32_t v[kScanItems];
-    uint32_t sum = 0;
+    uint32_t sum = 0, most = 0;
+    in.load8(base, n, v);
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
-        int64_t idx = base + i;
-        v[i] = idx < n ? in(idx) : 0u;
         sum += v[i];
+        if (kClass) most = max(most, v[i]);
     }
     const int w = threadIdx.x / dev::kWave, lane = threadIdx.x % dev::kWave;
     uint32_t incl = dev::wave_inclusive_sum(sum);
     if (lane == dev::kWave - 1) s_wsum[w] = incl;
+    if (kClass) {
+        const uint32_t c = (__ballot(most > kBinClassMedium) ? kBinsMedium : 0u) |
+                           (__ballot(most > kBinClassBig) ? kBinsBig : 0u);
+        if (lane == 0) s_wcls[w] = c;
+    }
     __syncthreads();
     uint32_t wpre = 0, total = 0;
 #pragma unroll
-    for (int j = 0; j < kScanThreads / dev::kWave; ++j) {
+    for (int j = 0; j < W; ++j) {
         if (j < w) wpre += s_wsum[j];
         total += s_wsum[j];
     }
     if (w == 0) {
-        uint32_t p = dev::lookback_wave(status, tile, total);
-        if (lane == 0) s_prefix = p;
+        uint32_t cls = 0;
+        if (kClass)
+            for (int j = 0; j < W; ++j) cls |= s_wcls[j];
+        uint32_t p = dev::lookback_wave(status, tile, total, cls);
+        if (lane == 0) {
+            s_prefix = p;
+            s_cls = cls;
+        }
     }
     __syncthreads();
     uint32_t run = s_prefix + wpre + incl - sum;
+    if (base + kScanItems < n && (reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
+        // a thread's eight results as two 16-byte stores (base is a multiple of eight)
+        uint32_t r[kScanItems];
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            r[i] = run;
+            run += v[i];
+        }
+        uint4 *o = reinterpret_cast<uint4 *>(out + base);
+        o[0] = make_uint4(r[0], r[1], r[2], r[3]);
+        o[1] = make_uint4(r[4], r[5], r[6], r[7]);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         int64_t idx = base + i;
@@ -246,7 +288,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(In in, uint32_t *out, int
             // the total is known once this tile's look-back ends: the host
             // needs nothing else from this launch
             if (host_total) {
-                *host_total = run;
+                host_total[0] = run;
+                if (kClass) host_total[1] = s_cls;
                 dev::publish_host(sig.word, sig.seq);
             }
         }
@@ -269,10 +312,12 @@ agal_status lookback_alloc(agal_context ctx, int64_t tiles, uint64_t **status, u
 // synchronisation (no separate read-back).
 template <class In>
 static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, hipStream_t s,
-                             uint64_t *status = nullptr, uint32_t *total = nullptr, bool timed = true) {
+                             uint64_t *status = nullptr, uint32_t *total = nullptr, bool timed = true,
+                             uint32_t *cls = nullptr) {
     if (n <= 0) {
         fill_u32(out, 0u, 1, s);
         if (total) *total = 0;
+        if (cls) *cls = 0;
         return AGAL_OK;
     }
     const int64_t tiles = scan_tiles(n);
@@ -283,33 +328,36 @@ static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, 
     const HostSignal sig = total ? host_signal(ctx) : HostSignal{nullptr, nullptr, 0u};
     {
         ProfScope prof(timed ? ctx : nullptr, "scan_exclusive", s);
-        hipLaunchKernelGGL(k_scan<In>, dim3((unsigned)tiles), dim3(kScanThreads), 0, s, in, out, n, status, ticket,
-                           total ? ctx->d_counts : nullptr, sig);
+        uint32_t *host = total ? ctx->d_counts : nullptr;
+        if (cls)
+            hipLaunchKernelGGL((k_scan<In, true>), dim3((unsigned)tiles), dim3(kBigScanThreads), 0, s, in, out, n,
+                               status, ticket, host, sig);
+        else
+            hipLaunchKernelGGL((k_scan<In, false>), dim3((unsigned)tiles), dim3(kBigScanThreads), 0, s, in, out, n,
+                               status, ticket, host, sig);
     }
     if (own) dev_free(ctx->mem, status, s);
     AGAL_TRY_HIP(hipGetLastError());
     if (total) {
         AGAL_TRY(wait_signal(ctx, s, sig, "device scan"));
         *total = ctx->h_counts[0];
+        if (cls) *cls = ctx->h_counts[1];
     }
     return AGAL_OK;
 }
 
-int64_t scan_tiles(int64_t n) { return n <= 0 ? 0 : (n + kScanTile - 1) / kScanTile; }
+int64_t scan_tiles(int64_t n) { return n <= 0 ? 0 : (n + kBigScanTile - 1) / kBigScanTile; }
 
 agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, hipStream_t s) {
     return scan_impl(ctx, LoadU32{in}, out, n, s);
 }
 agal_status scan_u32_total(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, uint64_t *status,
-                           uint32_t *total, hipStream_t s, bool timed) {
-    return scan_impl(ctx, LoadU32{in}, out, n, s, status, total, timed);
+                           uint32_t *total, hipStream_t s, bool timed, uint32_t *cls) {
+    return scan_impl(ctx, LoadU32{in}, out, n, s, status, total, timed, cls);
 }
 agal_status scan_popc64_total(agal_context ctx, const unsigned long long *masks, uint32_t *out, int64_t n,
                               uint32_t *total, hipStream_t s) {
     return scan_impl(ctx, LoadPopc64{masks}, out, n, s, nullptr, total);
-}
-agal_status scan_flags_u8(agal_context ctx, const uint8_t *in, uint32_t *out, int64_t n, hipStream_t s) {
-    return scan_impl(ctx, LoadFlagU8{in}, out, n, s);
 }
 
 // Several flag scans in one launch: the tiles of all arrays share one ticket

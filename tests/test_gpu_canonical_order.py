@@ -46,3 +46,30 @@ def test_bins_at_the_sorts_edges(dim, B, stride):
         # the faces lie inside one bin each, so sampled points give the same bins
         assert np.array_equal(off.cpu().numpy().view(np.uint32), ref.offsets.astype(np.uint32)), kind
         assert np.array_equal(ids.cpu().numpy(), ref.ids.astype(np.int32)), kind
+
+
+@pytest.mark.parametrize("what,B", [("box", 40), ("box", 1), ("wide", 16), ("wide", 33), ("many", 32), ("many", 1),
+                                    ("many", 3), ("segments", 64), ("one", 12)])
+def test_pairs_over_chunks_and_workgroups(what, B):
+    """Count and scatter where a face has more pairs than one chunk, where a workgroup takes one face and where it
+    takes many, with the last workgroup part full, and where every pair falls in few bins."""
+    import geomgen
+    import torch
+    import paper_2502_16310_amd as agal
+    if what == "box":
+        v, f = geomgen.box_mesh()
+    elif what == "wide":
+        v, f = geomgen.random_triangles(1777, 5, size=0.25)
+    elif what == "many":
+        v, f = geomgen.random_triangles(150001, 6, size=0.004)
+    elif what == "segments":
+        v, f = geomgen.random_segments(5003, 7, size=0.1)
+    else:
+        v, f = np.array([[-0.2, 0.1, 0.1], [1.3, 0.2, 0.9], [0.4, 1.1, 0.3]], np.float32), np.array([[0, 1, 2]], np.int32)
+    dim = v.shape[1]
+    log(f"{what} B {B}: {len(f)} faces")
+    ref = oracle.bin_faces(dim, oracle.gather(dim, v, f), (0.0,) * dim, (1.0,) * dim, B)
+    g = agal.Context().import_faces(torch.from_numpy(v).cuda(), torch.from_numpy(f).cuda())
+    off, ids = g.bin_faces([0.0] * dim, [1.0] * dim, B).tensors()
+    assert np.array_equal(off.cpu().numpy().view(np.uint32), ref.offsets)
+    assert np.array_equal(ids.cpu().numpy(), ref.ids)
