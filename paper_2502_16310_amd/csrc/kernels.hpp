@@ -835,20 +835,69 @@ __device__ __forceinline__ void flag_wave(const FlagArgs<D> &A, int64_t first) {
     }
 }
 
+// How far from its bounding box a face can be near_l2 at distance R, squared
+// (+inf: no bound is claimed).  near_l2 decides on rounded sums, so it may call
+// a point near that is a little beyond R: on an edge of length l the rounded
+// cross and dot products move the distance by at most 2^-19 (R + l); on the
+// face itself the normal's rounding tilts the plane and moves the three sides
+// by up to 2^-20 of the point's distance, at a corner that over the sine of its
+// angle.  With |n| >= 1e-2 l_max^2 (every angle's sine is at least that) all of
+// it stays below 1e-3 (R + l_max), which the bound adds.  Slivers below that,
+// edges too short or too long for their squares' and fourth powers' range, and
+// huge R get no bound.  Where it is finite, near_l2 also accepts every point
+// within R (1 - 2^-15) of the first corner: the first edge's test comes down to
+// that corner, to the other end when that is nearer, or to the line between,
+// which is nearer still.  r: the face's record.
+template <int D>
+__device__ __forceinline__ float near_reach2(const float *r, float R) {
+    float m2 = 0.0f;
+    bool fine = R <= 1e8f;
+#pragma unroll
+    for (int k = 0; k < (D == 3 ? 3 : 1); ++k) {
+        const float *a = r + D * k, *b = r + D * ((k + 1) % D);
+        float e2 = 0.0f;
+#pragma unroll
+        for (int j = 0; j < D; ++j) e2 += (b[j] - a[j]) * (b[j] - a[j]);
+        m2 = fmaxf(m2, e2);
+    }
+    fine = fine && m2 >= 1e-10f && m2 <= 1e10f;
+    if constexpr (D == 3) {
+        float e1[3], e2[3], n[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            e1[a] = r[3 + a] - r[a];
+            e2[a] = r[6 + a] - r[a];
+        }
+        dev::cross3_(e1, e2, n);
+        fine = fine && dev::dot3_(n, n) >= 1e-4f * (m2 * m2);
+    }
+    const float reach = 1.002f * R + 0.002f * sqrtf(m2);
+    return fine ? reach * reach : __builtin_inff();   // a NaN coordinate: not fine
+}
+
 // Own-bin flag pass, the paper's face detection as printed (Sec. II-C-2 with
 // Algorithm 1, bins of Sec. II-C-3): a cell looks only at the faces of the one
 // bin that holds its centre (bin index function of the binning) and is
 // flagged when its centre lies within Euclidean distance h of one of them
 // (near_l2).  One wave: blocks first .. first + 64/4^D - 1 (one lane per
 // cell).  The wave takes the distinct own bins of its lanes one after the
-// other; each bin's faces are staged 64 at a time (one record per lane, in
-// LDS) and the lanes of that bin test them, each stopping at its first near
-// face.  Writes every cell flag and the block's pass mark (0 or 1).
+// other and each bin's faces 64 at a time, a face per lane (the next 64
+// records and the ids after those in flight), and goes through the bin's cells
+// that are not flagged yet.  What bounds the pass is VALU issue in the tests:
+// near_l2 takes ~200 instructions, and a wave has to try every face of its bin
+// for a cell that is near none.  So kOwnCells cells at a time take two short
+// tests first: a face whose first corner is clearly within h flags the cell
+// (near_l2 accepts it), a face whose box is beyond near_reach2 is out (near_l2
+// would refuse it), and near_l2 runs only for a cell where neither settles it.
+// 81,920 faces in 16^3 bins (up to 1,000 a bin), h = 0.05, two passes: 1,121 us
+// with a cell per lane and near_l2 for every face; 366 with the box test before
+// it; 136 with a face per lane; 121 with the corner test.
+// Writes every cell flag and the block's pass mark (0 or 1).
+constexpr int kOwnCells = 4;
 template <int D>
 __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t first) {
     constexpr int CELLS = D == 3 ? 64 : 16;
     constexpr int RF = dev::kRecFloats<D>;
-    __shared__ float s_v[64][D * D];
     const int lane = dev::lane_id();
     const int64_t blk = first + lane / CELLS;
     const bool valid = blk < A.n;
@@ -863,51 +912,79 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
 #pragma unroll
     for (int a = 0; a < D; ++a) ib[a] = dev::bin_of(m[a], A.bins.lo[a], A.bins.s[a], A.bins.B);
     const int mybin = (ib[2] * A.bins.B + ib[1]) * A.bins.B + ib[0];   // B^D < 2^31 (checked when binning)
-    bool flagged = false;
-    bool done = !valid;
-    while (true) {
-        const uint64_t open = __ballot(!done);
-        if (!open) break;
-        const int leader = __builtin_ctzll(open);
-        const int bin = __builtin_amdgcn_readlane(mybin, leader);
-        const bool mine = !done && mybin == bin;
+    const float sure2 = 0.9999f * (A.h * A.h);
+    uint64_t flagged = 0;   // lanes (cells) flagged, wave-uniform
+    for (uint64_t open = __ballot(valid); open;) {
+        const int bin = __builtin_amdgcn_readlane(mybin, __builtin_ctzll(open));
+        uint64_t cells = __ballot(mybin == bin) & open;   // this bin's cells not flagged yet
+        open &= ~cells;
         const uint32_t s0 = A.bins.off[bin], s1 = A.bins.off[bin + 1];
-        for (uint32_t c0 = s0; c0 < s1; c0 += dev::kWave) {
-            if (!__ballot(mine && !flagged)) break;   // every cell of this bin decided
-            const uint32_t e = c0 + (uint32_t)lane;
-            if (e < s1) {
-                const int32_t f = A.bins.ids[e];
-                float r[RF];
-                if (f >= 0 && (int64_t)f < A.bins.F) {
-                    dev::load_rec<D>(A.faces.rec, f, r);
-                } else {
+        // id of list entry e (-1 past the bin's end, and for an id that is no face), and its record (NaN: never near)
+        auto id_at = [&](uint64_t e) -> int32_t {
+            if (e >= s1) return -1;
+            const int32_t f = A.bins.ids[e];
+            return f >= 0 && (int64_t)f < A.bins.F ? f : -1;
+        };
+        auto rec_at = [&](int32_t f, float (&r)[RF]) {
+            if (f >= 0) {
+                dev::load_rec<D>(A.faces.rec, f, r);
+            } else {
 #pragma unroll
-                    for (int k = 0; k < RF; ++k) r[k] = __builtin_nanf("");   // never near
-                }
-#pragma unroll
-                for (int k = 0; k < D * D; ++k) s_v[lane][k] = r[k];
+                for (int k = 0; k < RF; ++k) r[k] = __builtin_nanf("");
             }
-            dev::wave_sync();
-            const int nf = (int)min(s1 - c0, (uint32_t)dev::kWave);
-            if (mine && !flagged)
-                for (int j = 0; j < nf; ++j) {
-                    float v[D * D];
+        };
+        float rn[RF];
+        int32_t f = id_at((uint64_t)s0 + (uint32_t)lane), fn = id_at((uint64_t)s0 + dev::kWave + (uint32_t)lane);
+        rec_at(f, rn);
+        for (uint64_t c0 = s0; c0 < s1 && cells; c0 += dev::kWave) {
+            float r[RF];
 #pragma unroll
-                    for (int k = 0; k < D * D; ++k) v[k] = s_v[j][k];
-                    if (dev::near_l2<D>(v, m, A.h)) {
-                        flagged = true;
-                        break;
+            for (int k = 0; k < RF; ++k) r[k] = rn[k];
+            const bool has = f >= 0;
+            f = fn;
+            rec_at(f, rn);
+            fn = id_at(c0 + 2 * dev::kWave + (uint32_t)lane);
+            const float reach2 = near_reach2<D>(r, A.h);
+            const bool clear = has && reach2 < __builtin_inff();   // the short acceptance holds where the bound does
+            for (uint64_t left = cells; left;) {
+                int c[kOwnCells];
+                bool sure[kOwnCells], maybe[kOwnCells];
+                float mc[kOwnCells][3];
+#pragma unroll
+                for (int u = 0; u < kOwnCells; ++u) {
+                    c[u] = left ? __builtin_ctzll(left) : c[0];   // the last few: one cell several times
+                    left &= left - 1ull;
+                    float d2 = 0.0f, w2 = 0.0f;
+                    mc[u][2] = 0.0f;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) {
+                        mc[u][a] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m[a]), c[u]));
+                        const float d = fmaxf(fmaxf(r[D * D + a] - mc[u][a], mc[u][a] - r[D * D + D + a]), 0.0f);
+                        d2 += d * d;
+                        const float w = mc[u][a] - r[a];
+                        w2 += w * w;
                     }
+                    sure[u] = clear && w2 <= sure2;
+                    maybe[u] = has && !(d2 > reach2);   // (a NaN on either side keeps the face)
                 }
-            dev::wave_sync();
+#pragma unroll
+                for (int u = 0; u < kOwnCells; ++u) {
+                    bool near = __ballot(sure[u]) != 0ull;
+                    if (!near && __ballot(maybe[u])) {
+                        bool hit = false;
+                        if (maybe[u]) hit = dev::near_l2<D>(r, mc[u], A.h);
+                        near = __ballot(hit) != 0ull;
+                    }
+                    if (near) flagged |= 1ull << c[u];
+                }
+            }
+            cells &= ~flagged;
         }
-        done = done || mine;
     }
-    if (valid) A.cf[blk * CELLS + cell] = flagged ? 1 : 0;
-    const uint64_t fm = __ballot(valid && flagged);
+    if (valid) A.cf[blk * CELLS + cell] = (flagged >> lane) & 1ull ? 1 : 0;
     if (valid && cell == 0) {
-        uint64_t bm = fm;
-        if constexpr (CELLS < 64) bm = (fm >> (lane & ~(CELLS - 1))) & ((1ull << CELLS) - 1);
+        uint64_t bm = flagged;
+        if constexpr (CELLS < 64) bm = (flagged >> (lane & ~(CELLS - 1))) & ((1ull << CELLS) - 1);
         A.pmark[blk] = bm ? 1 : 0;
     }
 }

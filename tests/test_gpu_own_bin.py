@@ -61,3 +61,24 @@ def test_own_bin_segments_2d(orc):
     v, f = geomgen.random_segments(200, 10, 0.05, 0.95, 0.1)
     wl = geomgen.Workload("rseg", 2, v, f, (5, 3, 1), 3, 9, 9)
     _check(orc, wl, 9, [0.02, 0.01, 0.005])
+
+
+@pytest.mark.parametrize("dim,kind,B", [(3, "needles", 2), (3, "needles", 5), (3, "dots", 3), (2, "needles", 3), (3, "mixed", 1)])
+def test_own_bin_box_rejection(orc, dim, kind, B):
+    """Faces on both sides of the box rejection's limits: needles (no bound is claimed for slivers), specks far below
+    the distance, and a mix with degenerate faces; bins of more and fewer than 64 faces."""
+    rng = np.random.default_rng(8)
+    n = 333
+    c = rng.uniform(0.25, 0.75, (n, 1, dim))
+    e = rng.normal(size=(n, 1, dim)) * (0.15 if kind != "dots" else 1e-6)
+    t = rng.uniform(-0.5, 0.5, (n, dim, 1)) if kind != "dots" else rng.normal(size=(n, dim, 1))
+    wide = 10.0 ** rng.uniform(-7, -1, (n, 1, 1)) if kind == "mixed" else 1e-4
+    v = c + e * t + rng.normal(size=(n, dim, dim)) * wide * (0.0 if kind == "dots" else 1.0)
+    if kind == "mixed":
+        v[::7, 1] = v[::7, 0]
+        v[::11] = v[::11, :1]
+    v = v.reshape(-1, dim).astype(np.float32)
+    f = np.arange(len(v), dtype=np.int32).reshape(n, dim)
+    roots = (6, 6, 6) if dim == 3 else (6, 6, 1)
+    wl = geomgen.Workload(f"{kind}{dim}d", dim, v, f, roots, 2, B, 19 if dim == 3 else 9)
+    _check(orc, wl, B, [0.04, 0.015])
