@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -76,6 +77,40 @@ inline void dev_free(const Allocator &a, T *&p, hipStream_t s) {
     p = nullptr;
 }
 
+// Several arrays in one allocation, each on a 256-byte boundary: add() every
+// array, then get() the block that owns them.  A call through the allocator
+// callbacks costs the host 3 to 4 us (a Python callback and torch's allocator),
+// as much as several small kernels run for, so a call that needs a dozen arrays
+// at one point asks once.
+class Slab {
+  public:
+    template <class T>
+    void add(T **p, size_t count) {
+        req_.push_back({p, total_});
+        total_ = (total_ + (count ? count : 1) * sizeof(T) + 255) & ~size_t(255);
+    }
+    // *base: the allocation to release (null on failure, the arrays untouched)
+    agal_status get(const Allocator &a, void **base, hipStream_t s) {
+        char *b = nullptr;
+        *base = nullptr;
+        AGAL_TRY(dev_alloc(a, &b, total_, s));
+        *base = b;
+        for (const Req &r : req_) {
+            void *p = b + r.at;
+            std::memcpy(r.p, &p, sizeof p);
+        }
+        return AGAL_OK;
+    }
+
+  private:
+    struct Req {
+        void *p;   // the pointer variable to set
+        size_t at;
+    };
+    std::vector<Req> req_;
+    size_t total_ = 0;
+};
+
 uint64_t next_handle_id();
 
 }  // namespace agal
@@ -114,6 +149,7 @@ struct agal_geom_t {
     hipStream_t stream = nullptr;
     int dim = 0;
     int64_t F = 0, Nv = 0;
+    void *base = nullptr;      // owns the arrays below
     float *coords = nullptr;   // (dim*dim) x F
     float *aabb = nullptr;     // (2*dim) x F
     float *rec = nullptr;      // F x (16 in 3D, 8 in 2D): corners, min, max
@@ -137,10 +173,11 @@ struct agal_bins_t {
 namespace agal {
 struct Level {
     int64_t n = 0;
+    void *base = nullptr;      // owns the arrays below
     uint32_t *keys = nullptr;
     uint8_t *leaf = nullptr;
     uint8_t *mark = nullptr;   // export mark: 1 flagged, 2 balance
-    uint8_t *cf = nullptr;     // per-cell flags (levels that were tested)
+    uint8_t *cf = nullptr;     // per-cell flags (every level but the finest)
 };
 }  // namespace agal
 
@@ -165,6 +202,7 @@ struct agal_links_t {
     float lo[3] = {0, 0, 0};
     float dx[3] = {0, 0, 0};
     int64_t n = 0;
+    void *base = nullptr;      // owns the arrays below
     uint64_t *key = nullptr;
     float *q = nullptr;
     int32_t *face = nullptr;
@@ -181,10 +219,9 @@ struct Lattice {
 };
 bool lattice_table(int Q, Lattice *out);
 
-// Device-wide exclusive scan of `n` 0/1-or-count values into out[0..n]
-// (out[n] = total).  The input is either uint32 counts or uint8 flags
-// (nonzero = 1).  Scratch is allocated from the context.
-agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, hipStream_t s);
+// Device-wide exclusive scan of `n` counts into out[0..n] (out[n] = total).
+// (status: a zeroed buffer of scan_tiles(n) + 1 words.)
+agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, uint64_t *status, hipStream_t s);
 // k exclusive scans of 0/1 flags (out[i] of length n[i] + 1) in one launch; k <= kMultiScanMax.
 constexpr int kMultiScanMax = kMaxLevels + 1;
 // Candidate cells of the largest face in a face-centric flag step: per axis its
@@ -224,16 +261,16 @@ struct MultiScanArgs {
     uint32_t *host_total;    // mapped host memory: k totals, then *extra
     HostSignal sig;
 };
-// totals[0..k-1] = sum of each array, totals[k] = *extra; synchronises the stream.  status_zeroed: null, or
-// scan_flags_u8_multi_tiles(n, k) + 1 zeroed 64-bit words the caller provides.
+// totals[0..k-1] = sum of each array, totals[k] = *extra; synchronises the stream.  status:
+// scan_flags_u8_multi_tiles(n, k) + 1 zeroed 64-bit words.
 agal_status scan_flags_u8_multi(agal_context ctx, const uint8_t *const *in, uint32_t *const *out, const int64_t *n,
                                 int k, const uint32_t *extra, uint32_t *totals, hipStream_t s,
-                                uint64_t *status_zeroed = nullptr);
+                                uint64_t *status);
 int64_t scan_flags_u8_multi_tiles(const int64_t *n, int k);
 // Tiles of a scan of n elements; a caller-provided status buffer holds tiles + 1 zeroed 64-bit words.
 int64_t scan_tiles(int64_t n);
 // Exclusive scan whose sum comes back through mapped host memory (synchronises the stream); status is a
-// zeroed buffer of scan_tiles(n) + 1 words, or null.  timed = false: no kernel timing events even when the
+// zeroed buffer of scan_tiles(n) + 1 words.  timed = false: no kernel timing events even when the
 // context records them (the no-allocation calls create no events).  cls, when given: the classes of bins that
 // occur among the counts, so that the host launches only the sorts that have work.
 constexpr uint32_t kBinsMedium = 1;   // a bin above kBinClassMedium ids (else every 64 bins fit one LDS segment)
@@ -243,7 +280,7 @@ agal_status scan_u32_total(agal_context ctx, const uint32_t *in, uint32_t *out, 
                            uint32_t *total, hipStream_t s, bool timed = true, uint32_t *cls = nullptr);
 // Exclusive scan of the set-bit counts of n 64-bit masks, with the total (synchronises the stream).
 agal_status scan_popc64_total(agal_context ctx, const unsigned long long *masks, uint32_t *out, int64_t n,
-                              uint32_t *total, hipStream_t s);
+                              uint64_t *status, uint32_t *total, hipStream_t s);
 // Takes the device address of the binning scratch array for `device` (the
 // current device) once; later calls return at once.  Called by
 // agal_context_create.
@@ -268,13 +305,12 @@ struct LinkListPlan {
 };
 agal_status link_list_plan(agal_geom g, agal_forest fo, hipStream_t s, LinkListPlan *out);
 
-// Look-back scratch: status words + ticket for `tiles` tiles, cleared.
-agal_status lookback_alloc(agal_context ctx, int64_t tiles, uint64_t **status, uint32_t **ticket, hipStream_t s);
-
 // Fill kernels (used instead of hipMemsetAsync so the calls stay capturable).
 void fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s);
 void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 void fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s);
+// n0 words of p0 set to v0 and n1 of p1 to v1, in one launch.
+void fill2_u32(uint32_t *p0, uint32_t v0, int64_t n0, uint32_t *p1, uint32_t v1, int64_t n1, hipStream_t s);
 
 // Records HIP events around the launches in its scope when the context's
 // profiling is on; results are aggregated by agal_profile_read.

@@ -378,20 +378,23 @@ agal_status disc_pairs(agal_geom g, agal_bins bn, const DiscGrid &G, hipStream_t
     agal_context ctx = g->ctx;
     const int64_t nb = bn->nb, F = g->F;
     uint32_t *count = nullptr, *cursor = nullptr, *big_faces = nullptr, *med = nullptr, *big = nullptr;
+    void *base = nullptr;
     auto done = [&](agal_status st) {
-        dev_free(ctx->mem, count, s);
-        dev_free(ctx->mem, big_faces, s);
+        dev_free(ctx->mem, base, s);
         dev_free(ctx->mem, med, s);
         dev_free(ctx->mem, big, s);
         return st;
     };
-    // count + cursor (2 nb), then: big-face count, canon list counts (2)
-    AGAL_TRY(dev_alloc(ctx->mem, &count, (size_t)2 * nb + 4, s));
+    // zeroed: count + cursor (2 nb), big-face count, canon list counts (2), the scan's status words (64-bit)
+    const int64_t head = (2 * nb + 4) & ~int64_t(1), words = head + 2 * (scan_tiles(nb) + 1);
+    Slab arrays;
+    arrays.add(&count, (size_t)words);
+    arrays.add(&big_faces, (size_t)F);
+    AGAL_TRY(arrays.get(ctx->mem, &base, s));
     cursor = count + nb;
     uint32_t *nbig = count + 2 * nb, *lists = count + 2 * nb + 1;
-    fill_u32(count, 0u, 2 * nb + 4, s);
-    agal_status st = dev_alloc(ctx->mem, &big_faces, (size_t)std::max<int64_t>(F, 1), s);
-    if (st != AGAL_OK) return done(st);
+    fill_u32(count, 0u, words, s);
+    agal_status st = AGAL_OK;
     const unsigned big_grid = (unsigned)std::min<int64_t>(std::max<int64_t>(F, 1), 2048);
     {
         ProfScope prof(ctx, "bin_disc_count", s);
@@ -402,7 +405,7 @@ agal_status disc_pairs(agal_geom g, agal_bins bn, const DiscGrid &G, hipStream_t
     }
     AGAL_TRY_HIP(hipGetLastError());
     uint32_t P = 0, cls = 0;
-    st = scan_u32_total(ctx, count, bn->off, nb, nullptr, &P, s, true, &cls);
+    st = scan_u32_total(ctx, count, bn->off, nb, reinterpret_cast<uint64_t *>(count + head), &P, s, true, &cls);
     if (st != AGAL_OK) return done(st);
     bn->P = P;
     st = dev_alloc(ctx->mem, &bn->ids, (size_t)std::max<uint32_t>(P, 1u), s);
@@ -448,14 +451,18 @@ agal_status disc_fractions(agal_geom g, agal_bins bn, const DiscGrid &G, int64_t
                     (long long)bnum, (long long)F, (long long)(kMaxIndicatorBytes >> 30));
     int32_t *ind = nullptr;
     uint32_t *count = nullptr;
+    void *base = nullptr;
     auto done = [&](agal_status st) {
-        dev_free(ctx->mem, ind, s);
-        dev_free(ctx->mem, count, s);
+        dev_free(ctx->mem, base, s);
         return st;
     };
-    AGAL_TRY(dev_alloc(ctx->mem, &ind, (size_t)std::max<int64_t>(bnum * F, 1), s));
-    agal_status st = dev_alloc(ctx->mem, &count, (size_t)nb, s);
-    if (st != AGAL_OK) return done(st);
+    uint64_t *status = nullptr;
+    Slab arrays;
+    arrays.add(&ind, (size_t)(bnum * F));
+    arrays.add(&count, (size_t)nb);
+    arrays.add(&status, (size_t)scan_tiles(nb) + 1);
+    AGAL_TRY(arrays.get(ctx->mem, &base, s));
+    agal_status st = AGAL_OK;
     int64_t cap = std::min<int64_t>(10 * std::max<int64_t>(F, 1), (int64_t)UINT32_MAX);   // the paper's first guess
     for (int attempt = 0; attempt < 2; ++attempt) {
         dev_free(ctx->mem, bn->ids, s);
@@ -473,7 +480,8 @@ agal_status disc_fractions(agal_geom g, agal_bins bn, const DiscGrid &G, int64_t
                 hipLaunchKernelGGL(k_disc_rows, dim3((unsigned)std::min<int64_t>(n, 65536)), dim3(kRowThreads), 0, s,
                                    ind, F, n, count + c0);
             }
-            st = scan_u32(ctx, count, bn->off, c0 + n, s);
+            fill_u64(status, 0ull, scan_tiles(c0 + n) + 1, s);
+            st = scan_u32(ctx, count, bn->off, c0 + n, status, s);
             if (st != AGAL_OK) return done(st);
             {
                 ProfScope prof(ctx, "bin_disc_copy", s);

@@ -104,10 +104,15 @@ agal_status agal_import_faces(agal_context ctx, int dim, const float *d_vertices
     g->dim = dim;
     g->F = n_faces;
     g->Nv = n_vertices;
-    agal_status st = dev_alloc(ctx->mem, &g->coords, (size_t)dim * dim * n_faces, s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &g->aabb, (size_t)2 * dim * n_faces, s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &g->rec, (size_t)(dim == 3 ? 16 : 8) * n_faces, s);
-    if (st == AGAL_OK) st = dev_alloc(ctx->mem, &g->fidx, (size_t)dim * n_faces, s);
+    const unsigned grid = grid_for(std::max(n_vertices * dim, n_faces));
+    uint32_t *part = nullptr;   // four words per workgroup
+    Slab arrays;
+    arrays.add(&g->coords, (size_t)dim * dim * n_faces);
+    arrays.add(&g->aabb, (size_t)2 * dim * n_faces);
+    arrays.add(&g->rec, (size_t)(dim == 3 ? 16 : 8) * n_faces);
+    arrays.add(&g->fidx, (size_t)dim * n_faces);
+    arrays.add(&part, (size_t)4 * grid);
+    agal_status st = arrays.get(ctx->mem, &g->base, s);
     if (st != AGAL_OK) {
         agal_destroy_geom(g);
         return st;
@@ -118,13 +123,6 @@ agal_status agal_import_faces(agal_context ctx, int dim, const float *d_vertices
     ctx->h_counts[0] = 0u;
     ctx->h_counts[1] = 0u;
     const HostSignal sig = host_signal(ctx);
-    const unsigned grid = grid_for(std::max(n_vertices * dim, n_faces));
-    uint32_t *part = nullptr;   // four words per workgroup
-    st = dev_alloc(ctx->mem, &part, (size_t)4 * grid, s);
-    if (st != AGAL_OK) {
-        agal_destroy_geom(g);
-        return st;
-    }
     {
         ProfScope prof(ctx, "import", s);
         if (dim == 3)
@@ -135,7 +133,6 @@ agal_status agal_import_faces(agal_context ctx, int dim, const float *d_vertices
                                g->coords, g->aabb, g->rec, g->fidx, part);
         hipLaunchKernelGGL(k_import_signal, dim3(1), dim3(256), 0, s, part, (int)grid, err, dim, sig);
     }
-    dev_free(ctx->mem, part, s);
     hipError_t e = hipGetLastError();
     st = e != hipSuccess ? fail(AGAL_EHIP, "agal_import_faces: %s", hipGetErrorString(e))
                          : wait_signal(ctx, s, sig, "agal_import_faces");
@@ -169,10 +166,7 @@ agal_status agal_geom_view(agal_geom g, int *dim, int64_t *n_faces, int64_t *n_v
 
 void agal_destroy_geom(agal_geom g) {
     if (!g) return;
-    dev_free(g->ctx->mem, g->coords, g->stream);
-    dev_free(g->ctx->mem, g->aabb, g->stream);
-    dev_free(g->ctx->mem, g->rec, g->stream);
-    dev_free(g->ctx->mem, g->fidx, g->stream);
+    dev_free(g->ctx->mem, g->base, g->stream);
     delete g;
 }
 

@@ -138,11 +138,17 @@ struct CallScratch {
     agal_context ctx;
     hipStream_t s;
     std::vector<void *> ptrs;
+    agal_status get(Slab &arrays) {
+        void *base = nullptr;
+        AGAL_TRY(arrays.get(ctx->mem, &base, s));
+        ptrs.push_back(base);
+        return AGAL_OK;
+    }
     template <class T>
     agal_status get(T **p, size_t count) {
-        AGAL_TRY(dev_alloc(ctx->mem, p, count, s));
-        ptrs.push_back(*p);
-        return AGAL_OK;
+        Slab one;
+        one.add(p, count);
+        return get(one);
     }
     ~CallScratch() {
         for (void *p : ptrs) dev_free(ctx->mem, p, s);
@@ -151,12 +157,12 @@ struct CallScratch {
 
 template <int D, int Q>
 agal_status alloc_link_outputs(agal_links lk, uint32_t nn, hipStream_t s) {
-    agal_context ctx = lk->ctx;
     lk->n = nn;
-    AGAL_TRY(dev_alloc(ctx->mem, &lk->key, (size_t)std::max<uint32_t>(nn, 1u), s));
-    AGAL_TRY(dev_alloc(ctx->mem, &lk->q, (size_t)std::max<uint32_t>(nn, 1u) * Q, s));
-    AGAL_TRY(dev_alloc(ctx->mem, &lk->face, (size_t)std::max<uint32_t>(nn, 1u) * Q, s));
-    return AGAL_OK;
+    Slab arrays;
+    arrays.add(&lk->key, (size_t)nn);
+    arrays.add(&lk->q, (size_t)nn * Q);
+    arrays.add(&lk->face, (size_t)nn * Q);
+    return arrays.get(lk->ctx->mem, &lk->base, s);
 }
 
 // Walk mode: bins walked per block, nodes staged per block, then compacted.
@@ -172,12 +178,14 @@ agal_status links_forward_walk(agal_geom g, agal_bins bn, agal_forest fo, agal_l
     uint64_t *skey = nullptr, *status = nullptr;
     float *sq = nullptr;
     int32_t *sface = nullptr;
-    AGAL_TRY(st.get(&count, (size_t)LL.n));
-    AGAL_TRY(st.get(&off, (size_t)LL.n + 1));
-    AGAL_TRY(st.get(&status, (size_t)scan_tiles(LL.n) + 1));
-    AGAL_TRY(st.get(&skey, (size_t)cap));
-    AGAL_TRY(st.get(&sq, (size_t)cap * Q));
-    AGAL_TRY(st.get(&sface, (size_t)cap * Q));
+    Slab arrays;
+    arrays.add(&count, (size_t)LL.n);
+    arrays.add(&off, (size_t)LL.n + 1);
+    arrays.add(&status, (size_t)scan_tiles(LL.n) + 1);
+    arrays.add(&skey, (size_t)cap);
+    arrays.add(&sq, (size_t)cap * Q);
+    arrays.add(&sface, (size_t)cap * Q);
+    AGAL_TRY(st.get(arrays));
     LinkArgs<D, Q> A = link_args<D, Q>(g, bn, fo);
     A.node_key = skey;
     A.q = sq;
@@ -203,17 +211,20 @@ agal_status links_forward_walk(agal_geom g, agal_bins bn, agal_forest fo, agal_l
 
 // First half of the list build: the parent table, the zeroed node masks and
 // every block's candidate count (lwork[0 .. n); lwork[n .. 2n) zeroed for the
-// scatter cursors).
+// scatter cursors, and behind them the look-back status words of the two scans
+// of the call).  `arrays` holds the caller's own arrays on entry: all of them
+// share one block.
 template <int D>
 struct ListBuild {
     BlockFind B{};
     LinkFaceGrid G{};
     unsigned long long *nmask = nullptr;
-    uint32_t *lwork = nullptr;
+    uint32_t *lwork = nullptr, *loff = nullptr;
+    uint64_t *status[2] = {};
 };
 
 template <int D>
-agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t max_coords, CallScratch &st,
+agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t max_coords, CallScratch &st, Slab &arrays,
                        ListBuild<D> &LB, hipStream_t s) {
     const agal::Level &LL = fo->lev[fo->L];
     const int64_t n = LL.n;
@@ -226,16 +237,24 @@ agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t 
     unsigned long long *hash = nullptr;
     const unsigned fgrid = (unsigned)((g->F + kLinkFaceG - 1) / kLinkFaceG);
     const unsigned bgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
-    AGAL_TRY(st.get(&LB.nmask, (size_t)n));
+    const int64_t status_words = scan_tiles(n) + 1;   // 64-bit words
+    const int64_t work_words = (2 * n + 1) & ~int64_t(1);
+    arrays.add(&LB.lwork, (size_t)(work_words + 4 * status_words));   // counts, scatter cursors, status words
+    arrays.add(&LB.nmask, (size_t)n);
+    arrays.add(&LB.loff, (size_t)n + 1);
     if (L > 0) {
         // parents: n / 2^D (complete families); at most half the slots used
         int bits = 6;
         while (bits < 31 && (int64_t(1) << bits) < 2 * ((n + (1 << D) - 1) >> D)) ++bits;
         B.hmask = (uint32_t)((int64_t(1) << bits) - 1);
         B.hshift = 32 - bits;
-        AGAL_TRY(st.get(&hash, (size_t)B.hmask + 1));
-        fill_u64(reinterpret_cast<uint64_t *>(hash), ~0ull, (int64_t)B.hmask + 1, s);
+        arrays.add(&hash, (size_t)B.hmask + 1);
     }
+    AGAL_TRY(st.get(arrays));
+    LB.status[0] = reinterpret_cast<uint64_t *>(LB.lwork + work_words);
+    LB.status[1] = LB.status[0] + status_words;
+    fill2_u32(LB.lwork, 0u, work_words + 4 * status_words, reinterpret_cast<uint32_t *>(hash), ~0u,
+              hash ? 2 * ((int64_t)B.hmask + 1) : 0, s);
     hipLaunchKernelGGL((k_link_blocks<D>), dim3(bgrid), dim3(256), 0, s, LL.keys, n, hash, B.hmask, B.hshift,
                        LB.nmask);
     B.hash = hash;
@@ -246,8 +265,6 @@ agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t 
         G.m[a] = 2.0 * (double)eps[a];
         G.NB[a] = a < D ? (fo->roots[a] << L) : 1;
     }
-    AGAL_TRY(st.get(&LB.lwork, (size_t)2 * n));   // counts, then scatter cursors
-    fill_u32(LB.lwork, 0u, 2 * n, s);
     hipLaunchKernelGGL((k_link_faces<D, false>), dim3(fgrid), dim3(64), 0, s, g->aabb, g->F, G, B, max_coords,
                        LB.lwork, nullptr, nullptr, nullptr, nullptr, 0u);
     AGAL_TRY_HIP(hipGetLastError());
@@ -291,29 +308,36 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
     LinkArgs<D, Q> A = link_args<D, Q>(g, bn, fo);
     CallScratch st{ctx, s};
     ListBuild<D> LB;
-    uint32_t *loff = nullptr, *lblk = nullptr, *noff = nullptr, *nblk = nullptr;
+    uint32_t *lblk = nullptr, *noff = nullptr, *nblk = nullptr;
     int32_t *list = nullptr;
+    Slab arrays;
+    arrays.add(&noff, (size_t)n + 1);
+    if (list_cap <= kListNoWait) {
+        // the bound is small enough to allocate: no host wait
+        arrays.add(&list, (size_t)list_cap);
+        arrays.add(&lblk, (size_t)list_cap);
+    }
     const unsigned fgrid = (unsigned)((g->F + kLinkFaceG - 1) / kLinkFaceG);
     const unsigned bgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
     {
         ProfScope prof(ctx, "q_lists", s);
-        AGAL_TRY(list_count<D>(g, fo, A.eps, max_coords, st, LB, s));
-        AGAL_TRY(st.get(&loff, (size_t)n + 1));
-        if (list_cap <= kListNoWait) {
-            // the bound is small enough to allocate: no host wait
-            AGAL_TRY(scan_u32(ctx, LB.lwork, loff, n, s));
+        AGAL_TRY(list_count<D>(g, fo, A.eps, max_coords, st, arrays, LB, s));
+        if (list) {
+            AGAL_TRY(scan_u32(ctx, LB.lwork, LB.loff, n, LB.status[0], s));
         } else {
             uint32_t total = 0;
-            AGAL_TRY(scan_u32_total(ctx, LB.lwork, loff, n, nullptr, &total, s));
+            AGAL_TRY(scan_u32_total(ctx, LB.lwork, LB.loff, n, LB.status[0], &total, s));
             list_cap = total;
+            Slab lists;
+            lists.add(&list, (size_t)list_cap);
+            lists.add(&lblk, (size_t)list_cap);
+            AGAL_TRY(st.get(lists));
         }
-        AGAL_TRY(st.get(&list, (size_t)std::max<int64_t>(list_cap, 1)));
-        AGAL_TRY(st.get(&lblk, (size_t)std::max<int64_t>(list_cap, 1)));
         hipLaunchKernelGGL((k_link_faces<D, true>), dim3(fgrid), dim3(64), 0, s, g->aabb, g->F, LB.G, LB.B,
-                           max_coords, nullptr, loff, LB.lwork + n, list, lblk, (uint32_t)list_cap);
+                           max_coords, nullptr, LB.loff, LB.lwork + n, list, lblk, (uint32_t)list_cap);
     }
     AGAL_TRY_HIP(hipGetLastError());
-    A.loff = loff;
+    A.loff = LB.loff;
     A.list = list;
     A.list_cap = (uint32_t)list_cap;
     unsigned long long *nmask = LB.nmask;
@@ -325,9 +349,8 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         hipLaunchKernelGGL((k_links_nodes<D, Q>), dim3(grid), dim3(64), 0, s, A, lblk, nmask);
     }
     AGAL_TRY_HIP(hipGetLastError());
-    AGAL_TRY(st.get(&noff, (size_t)n + 1));
     uint32_t nn = 0;
-    AGAL_TRY(scan_popc64_total(ctx, nmask, noff, n, &nn, s));
+    AGAL_TRY(scan_popc64_total(ctx, nmask, noff, n, LB.status[1], &nn, s));
     AGAL_TRY((alloc_link_outputs<D, Q>(lk, nn, s)));
     if (nn > 0) {
         AGAL_TRY(st.get(&nblk, (size_t)nn));
@@ -361,11 +384,10 @@ agal_status list_entries_impl(agal_geom g, agal_forest fo, const LinkMode &m, in
     CallScratch st{g->ctx, s};
     ListBuild<D> LB;
     const int64_t n = fo->lev[fo->L].n;
-    uint32_t *loff = nullptr;
-    AGAL_TRY(list_count<D>(g, fo, m.eps, m.per_face, st, LB, s));
-    AGAL_TRY(st.get(&loff, (size_t)n + 1));
+    Slab arrays;
+    AGAL_TRY(list_count<D>(g, fo, m.eps, m.per_face, st, arrays, LB, s));
     uint32_t total = 0;
-    AGAL_TRY(scan_u32_total(g->ctx, LB.lwork, loff, n, nullptr, &total, s, false));
+    AGAL_TRY(scan_u32_total(g->ctx, LB.lwork, LB.loff, n, LB.status[0], &total, s, false));
     *entries = total;
     return AGAL_OK;
 }
@@ -599,9 +621,7 @@ agal_status agal_classify_nodes(agal_geom g, agal_links l, uint8_t *d_class, voi
 
 void agal_destroy_links(agal_links l) {
     if (!l) return;
-    dev_free(l->ctx->mem, l->key, l->stream);
-    dev_free(l->ctx->mem, l->q, l->stream);
-    dev_free(l->ctx->mem, l->face, l->stream);
+    dev_free(l->ctx->mem, l->base, l->stream);
     delete l;
 }
 

@@ -27,6 +27,7 @@ struct agal_forest_diff_t {
     int L = 0;
     int64_t n_new[agal::kMaxLevels + 1] = {};
     int64_t n_old[agal::kMaxLevels + 1] = {};
+    void *base = nullptr;   // owns the arrays below
     int32_t *old_index[agal::kMaxLevels + 1] = {};
     uint8_t *state[agal::kMaxLevels + 1] = {};
     uint8_t *removed[agal::kMaxLevels + 1] = {};
@@ -130,7 +131,14 @@ agal_status agal_forest_diff_create(agal_forest old_f, agal_forest new_f, void *
     d->L = new_f->L;
     unsigned long long *counts = nullptr;
     const int nl = d->L + 1;
-    agal_status st = dev_alloc(ctx->mem, &counts, (size_t)nl * 4, s);
+    Slab arrays;
+    arrays.add(&counts, (size_t)nl * 4);
+    for (int l = 0; l < nl; ++l) {
+        arrays.add(&d->old_index[l], (size_t)new_f->lev[l].n);
+        arrays.add(&d->state[l], (size_t)new_f->lev[l].n);
+        arrays.add(&d->removed[l], (size_t)old_f->lev[l].n);
+    }
+    agal_status st = arrays.get(ctx->mem, &d->base, s);
     if (st != AGAL_OK) {
         delete d;
         return st;
@@ -142,10 +150,6 @@ agal_status agal_forest_diff_create(agal_forest old_f, agal_forest new_f, void *
             const Level &A = old_f->lev[l], &B = new_f->lev[l];
             d->n_new[l] = B.n;
             d->n_old[l] = A.n;
-            st = dev_alloc(ctx->mem, &d->old_index[l], (size_t)std::max<int64_t>(B.n, 1), s);
-            if (st == AGAL_OK) st = dev_alloc(ctx->mem, &d->state[l], (size_t)std::max<int64_t>(B.n, 1), s);
-            if (st == AGAL_OK) st = dev_alloc(ctx->mem, &d->removed[l], (size_t)std::max<int64_t>(A.n, 1), s);
-            if (st != AGAL_OK) break;
             if (B.n > 0)
                 hipLaunchKernelGGL(k_diff_new, dim3((unsigned)std::min<int64_t>((B.n + kDiffThreads - 1) / kDiffThreads, 2048)),
                                    dim3(kDiffThreads), 0, s, B.keys, B.leaf, B.n, A.keys, A.leaf, A.n, d->old_index[l],
@@ -163,7 +167,6 @@ agal_status agal_forest_diff_create(agal_forest old_f, agal_forest new_f, void *
         const hipError_t e3 = e2 == hipSuccess ? hipStreamSynchronize(s) : e2;
         if (e3 != hipSuccess) st = fail(AGAL_EHIP, "agal_forest_diff_create: %s", hipGetErrorString(e3));
     }
-    dev_free(ctx->mem, counts, s);
     if (st != AGAL_OK) {
         agal_destroy_forest_diff(d);
         return st;
@@ -188,11 +191,7 @@ agal_status agal_forest_diff_view(agal_forest_diff d, int level, const int32_t *
 
 void agal_destroy_forest_diff(agal_forest_diff d) {
     if (!d) return;
-    for (int l = 0; l <= kMaxLevels; ++l) {
-        dev_free(d->ctx->mem, d->old_index[l], d->stream);
-        dev_free(d->ctx->mem, d->state[l], d->stream);
-        dev_free(d->ctx->mem, d->removed[l], d->stream);
-    }
+    dev_free(d->ctx->mem, d->base, d->stream);
     delete d;
 }
 

@@ -165,20 +165,23 @@ unsigned grid_for(int64_t n, int threads = 256, int64_t cap = 16384) {
     return (unsigned)b;
 }
 
+// One block of device memory, released at the end of its scope (stream ordered).
 struct Scratch {
     agal_context ctx;
     hipStream_t s;
-    std::vector<void *> ptrs;
-    template <class T>
-    agal_status get(T **p, size_t n) {
-        AGAL_TRY(dev_alloc(ctx->mem, p, n, s));
-        ptrs.push_back(*p);
-        return AGAL_OK;
-    }
-    ~Scratch() {
-        for (void *p : ptrs) ctx->mem.release(p, s);
-    }
+    void *base = nullptr;
+    agal_status get(Slab &arrays) { return arrays.get(ctx->mem, &base, s); }
+    ~Scratch() { dev_free(ctx->mem, base, s); }
 };
+
+// A level's arrays (n blocks; cells flags per block, 0: none) in one block.
+void add_level(Slab &arrays, agal::Level &v, int64_t n, int cells) {
+    v.n = n;
+    arrays.add(&v.keys, (size_t)n);
+    arrays.add(&v.leaf, (size_t)n);
+    arrays.add(&v.mark, (size_t)n);
+    if (cells) arrays.add(&v.cf, (size_t)n * cells);
+}
 
 // Which candidate walker the flag pass of n blocks takes at cell size dx and
 // distance h.  The deduplicating one (many list entries per memory latency,
@@ -231,38 +234,44 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
     agal_context ctx = g->ctx;
     const auto &mem = ctx->mem;
     uint32_t *err = nullptr;
-    Scratch keep{ctx, s, {}};
-    AGAL_TRY(keep.get(&err, 1));
 
     // level 0: every root, key = x-fastest linear index
     agal::Level &L0 = fo->lev[0];
-    L0.n = (int64_t)fo->roots[0] * fo->roots[1] * fo->roots[2];
-    AGAL_TRY(dev_alloc(mem, &L0.keys, (size_t)L0.n, s));
-    AGAL_TRY(dev_alloc(mem, &L0.leaf, (size_t)L0.n, s));
-    AGAL_TRY(dev_alloc(mem, &L0.mark, (size_t)L0.n, s));
-    // Zeroed scratch of pass l: the look-back status words of the pass's scan of
-    // the marks, then the pass marks of every level l' <= l.
+    {
+        Slab arrays;
+        add_level(arrays, L0, (int64_t)fo->roots[0] * fo->roots[1] * fo->roots[2], fo->L > 0 ? CELLS : 0);
+        arrays.add(&err, 1);
+        AGAL_TRY(arrays.get(mem, &L0.base, s));
+    }
+    // Scratch of pass l, in one block: a zeroed buffer (the look-back status
+    // words of the pass's scan of the marks, then the pass marks of every level
+    // l' <= l), the block table where there is one, and per level l' <= l the
+    // marks' prefix and the marked keys (at most all of the level's).
     struct PassBuf {
         uint8_t *buf = nullptr;
         int64_t words = 0, status_bytes = 0;
+        uint32_t *table = nullptr, *pos[kMaxLevels + 1] = {}, *mk[kMaxLevels + 1] = {};
     };
-    auto pass_buf = [&](Scratch &sc, int l, PassBuf &pb) -> agal_status {
+    auto pass_buf = [&](Scratch &sc, int l, int64_t table_entries, PassBuf &pb) -> agal_status {
         int64_t ns[kMaxLevels + 1], tot = 0;
+        Slab arrays;
         for (int m = 0; m <= l; ++m) {
             ns[m] = fo->lev[m].n;
             tot += ns[m];
+            arrays.add(&pb.pos[m], (size_t)ns[m] + 1);
+            arrays.add(&pb.mk[m], (size_t)ns[m]);
         }
         pb.status_bytes = 8 * (scan_flags_u8_multi_tiles(ns, l + 1) + 1);
         pb.words = (pb.status_bytes + tot + 3) / 4;
-        return sc.get(&pb.buf, (size_t)(4 * pb.words));
+        arrays.add(&pb.buf, (size_t)(4 * pb.words));
+        if (table_entries) arrays.add(&pb.table, (size_t)table_entries);
+        return sc.get(arrays);
     };
     // the level-0 cell flags (for the face-centric step) and the first pass's
-    // scratch are zeroed by the root-init launch
+    // zeroed scratch are cleared by the root-init launch
+    Scratch keep{ctx, s};
     PassBuf pb0;
-    if (fo->L > 0) {
-        AGAL_TRY(dev_alloc(mem, &L0.cf, (size_t)L0.n * CELLS, s));
-        AGAL_TRY(pass_buf(keep, 0, pb0));
-    }
+    if (fo->L > 0) AGAL_TRY(pass_buf(keep, 0, 0, pb0));
     hipLaunchKernelGGL(k_init_roots, dim3(grid_for(L0.n)), dim3(256), 0, s, L0.keys, L0.leaf, L0.mark, L0.n, err,
                        reinterpret_cast<uint4 *>(L0.cf), CELLS / 16, reinterpret_cast<uint32_t *>(pb0.buf),
                        pb0.words);
@@ -279,7 +288,7 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
     dev::Faces faces{g->coords, g->aabb, g->rec, g->F};
 
     for (int l = 0; l < fo->L; ++l) {
-        Scratch pass{ctx, s, {}};
+        Scratch pass{ctx, s};
         agal::Level &Ll = fo->lev[l];
         float eps_l[3];
         for (int a = 0; a < 3; ++a) eps_l[a] = dev::kEps * std::max(1.0f, std::max(std::fabs(fo->lo[a]), std::fabs(fo->hi[a])));
@@ -287,11 +296,10 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
                              face_flag_pairs(D, g->max_extent, fo->d[l], fo->dx[l], eps_l) <= kFaceFlagMaxPairs;
         // the block table of level l (face-centric step above level 0): never
         // cleared, its entries are checked against the level's keys
-        uint32_t *table = nullptr;
-        if (l > 0 && by_face && Ll.n > 0) AGAL_TRY(pass.get(&table, (size_t)block_grid_size<D>(fo, l)));
         PassBuf pb = pb0;
+        if (l > 0) AGAL_TRY(pass_buf(pass, l, by_face && Ll.n > 0 ? block_grid_size<D>(fo, l) : 0, pb));
+        uint32_t *table = pb.table;
         if (l > 0) {
-            AGAL_TRY(pass_buf(pass, l, pb));
             // zeroed by the table launch when there is one
             if (!table) fill_u32(reinterpret_cast<uint32_t *>(pb.buf), 0u, pb.words, s);
         }
@@ -305,7 +313,6 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             }
         }
         // (i) flag every cell of every level-l block
-        if (l > 0) AGAL_TRY(dev_alloc(mem, &Ll.cf, (size_t)Ll.n * CELLS, s));
         if (Ll.n > 0) {
             FlagArgs<D> A{};
             A.faces = faces;
@@ -385,18 +392,16 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
                                pm[m - 1], fo->roots[0], fo->roots[1], fo->roots[2], err);
         }
         // (iii) children: count marks per level, then merge level by level
-        uint32_t *pos[kMaxLevels + 1] = {};
         uint32_t nmark[kMaxLevels + 2] = {};
         {
             const uint8_t *ins[kMaxLevels + 1];
             int64_t ns[kMaxLevels + 1];
             for (int m = 0; m <= l; ++m) {
-                AGAL_TRY(pass.get(&pos[m], (size_t)fo->lev[m].n + 1));
                 ins[m] = pm[m];
                 ns[m] = fo->lev[m].n;
             }
             // marks per level and the balance error word, back through mapped host memory
-            AGAL_TRY(scan_flags_u8_multi(ctx, ins, pos, ns, l + 1, err, nmark, s, scan_status));
+            AGAL_TRY(scan_flags_u8_multi(ctx, ins, pb.pos, ns, l + 1, err, nmark, s, scan_status));
         }
         if (nmark[l + 1] != 0) return fail(AGAL_ESTATE, "agal_near_wall_refine: forest lost 2:1 balance");
         // every parent level with marks at once: the new child levels are fresh
@@ -414,10 +419,9 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             if (c == 0) {
                 if (m + 1 == l + 1 && C.keys == nullptr) {
                     // no child level yet: an empty one keeps views valid
-                    AGAL_TRY(dev_alloc(mem, &C.keys, 1, s));
-                    AGAL_TRY(dev_alloc(mem, &C.leaf, 1, s));
-                    AGAL_TRY(dev_alloc(mem, &C.mark, 1, s));
-                    C.n = 0;
+                    Slab arrays;
+                    add_level(arrays, C, 0, m + 1 < fo->L ? CELLS : 0);
+                    AGAL_TRY(arrays.get(mem, &C.base, s));
                 }
                 continue;
             }
@@ -425,15 +429,17 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             segm[ga.nseg] = m;
             agal::Level &N = Nl[ga.nseg];
             ++ga.nseg;
-            AGAL_TRY(pass.get(&gs.mk, (size_t)c));
-            N.n = C.n + (c << D);
-            AGAL_TRY(dev_alloc(mem, &N.keys, (size_t)N.n, s));
-            AGAL_TRY(dev_alloc(mem, &N.leaf, (size_t)N.n, s));
-            AGAL_TRY(dev_alloc(mem, &N.mark, (size_t)N.n, s));
-            if (C.cf) AGAL_TRY(dev_alloc(mem, &N.cf, (size_t)N.n * CELLS, s));
+            Slab arrays;
+            add_level(arrays, N, C.n + (c << D), m + 1 < fo->L ? CELLS : 0);
+            const agal_status got = arrays.get(mem, &N.base, s);
+            if (got != AGAL_OK) {
+                for (int k = 0; k < ga.nseg; ++k) dev_free(mem, Nl[k].base, s);
+                return got;
+            }
+            gs.mk = pb.mk[m];
             gs.pkeys = P.keys;
             gs.pm = pm[m];
-            gs.pos = pos[m];
+            gs.pos = pb.pos[m];
             gs.pleaf = P.leaf;
             gs.pmark = P.mark;
             gs.pn = P.n;
@@ -446,7 +452,8 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             gs.nkeys = N.keys;
             gs.nleaf = N.leaf;
             gs.nmark = N.mark;
-            gs.ncf = N.cf;
+            // level l + 1's cell flags are written by the next pass
+            gs.ncf = m < l ? N.cf : nullptr;
         }
         if (ga.nseg > 0) {
             for (int k = 0; k < ga.nseg; ++k) {
@@ -459,10 +466,7 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
         }
         for (int k = 0; k < ga.nseg; ++k) {
             agal::Level &C = fo->lev[segm[k] + 1];
-            dev_free(mem, C.keys, s);
-            dev_free(mem, C.leaf, s);
-            dev_free(mem, C.mark, s);
-            dev_free(mem, C.cf, s);
+            dev_free(mem, C.base, s);
             C = Nl[k];
         }
         AGAL_TRY_HIP(hipGetLastError());
@@ -558,12 +562,7 @@ agal_status agal_forest_info(agal_forest f, int *dim, int *n_levels) {
 
 void agal_destroy_forest(agal_forest f) {
     if (!f) return;
-    for (int l = 0; l <= kMaxLevels; ++l) {
-        dev_free(f->ctx->mem, f->lev[l].keys, f->stream);
-        dev_free(f->ctx->mem, f->lev[l].leaf, f->stream);
-        dev_free(f->ctx->mem, f->lev[l].mark, f->stream);
-        dev_free(f->ctx->mem, f->lev[l].cf, f->stream);
-    }
+    for (int l = 0; l <= kMaxLevels; ++l) dev_free(f->ctx->mem, f->lev[l].base, f->stream);
     delete f;
 }
 

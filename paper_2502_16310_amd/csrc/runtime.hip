@@ -157,6 +157,19 @@ void fill_u8(uint8_t *p, uint8_t v, int64_t n, hipStream_t s) { fill(p, v, n, s)
 void fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) { fill(p, v, n, s); }
 void fill_u64(uint64_t *p, uint64_t v, int64_t n, hipStream_t s) { fill(p, v, n, s); }
 
+__global__ void k_fill2(uint32_t *p0, uint32_t v0, int64_t n0, uint32_t *p1, uint32_t v1, int64_t n1) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t; i < n0; i += step) p0[i] = v0;
+    for (int64_t i = t; i < n1; i += step) p1[i] = v1;
+}
+
+void fill2_u32(uint32_t *p0, uint32_t v0, int64_t n0, uint32_t *p1, uint32_t v1, int64_t n1, hipStream_t s) {
+    const int64_t n = std::max(n0, n1);
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_fill2, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256), 0, s, p0, v0, n0, p1,
+                       v1, n1);
+}
+
 // ---------------------------------------------------------------------------
 // exclusive scan (decoupled look-back)
 // ---------------------------------------------------------------------------
@@ -296,24 +309,12 @@ __global__ __launch_bounds__(kBigScanThreads) void k_scan(In in, uint32_t *out, 
     }
 }
 
-agal_status lookback_alloc(agal_context ctx, int64_t tiles, uint64_t **status, uint32_t **ticket, hipStream_t s) {
-    // one buffer: status words then the ticket
-    uint64_t *buf = nullptr;
-    AGAL_TRY(dev_alloc(ctx->mem, &buf, (size_t)tiles + 1, s));
-    fill_u64(buf, 0ull, tiles + 1, s);
-    *status = buf;
-    *ticket = reinterpret_cast<uint32_t *>(buf + tiles);
-    return AGAL_OK;
-}
-
-// status: tiles + 1 zeroed words (look-back status, then the ticket), or null
-// to have one allocated and zeroed here.  total: when non-null, the sum is
-// written to mapped host memory by the kernel and returned after a stream
-// synchronisation (no separate read-back).
+// status: tiles + 1 zeroed words (look-back status, then the ticket).  total:
+// when non-null, the sum is written to mapped host memory by the kernel and
+// returned after a stream synchronisation (no separate read-back).
 template <class In>
-static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, hipStream_t s,
-                             uint64_t *status = nullptr, uint32_t *total = nullptr, bool timed = true,
-                             uint32_t *cls = nullptr) {
+static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, hipStream_t s, uint64_t *status,
+                             uint32_t *total = nullptr, bool timed = true, uint32_t *cls = nullptr) {
     if (n <= 0) {
         fill_u32(out, 0u, 1, s);
         if (total) *total = 0;
@@ -321,10 +322,7 @@ static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, 
         return AGAL_OK;
     }
     const int64_t tiles = scan_tiles(n);
-    const bool own = status == nullptr;
-    uint32_t *ticket = nullptr;
-    if (own) AGAL_TRY(lookback_alloc(ctx, tiles, &status, &ticket, s));
-    else ticket = reinterpret_cast<uint32_t *>(status + tiles);
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(status + tiles);
     const HostSignal sig = total ? host_signal(ctx) : HostSignal{nullptr, nullptr, 0u};
     {
         ProfScope prof(timed ? ctx : nullptr, "scan_exclusive", s);
@@ -336,7 +334,6 @@ static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, 
             hipLaunchKernelGGL((k_scan<In, false>), dim3((unsigned)tiles), dim3(kBigScanThreads), 0, s, in, out, n,
                                status, ticket, host, sig);
     }
-    if (own) dev_free(ctx->mem, status, s);
     AGAL_TRY_HIP(hipGetLastError());
     if (total) {
         AGAL_TRY(wait_signal(ctx, s, sig, "device scan"));
@@ -348,16 +345,16 @@ static agal_status scan_impl(agal_context ctx, In in, uint32_t *out, int64_t n, 
 
 int64_t scan_tiles(int64_t n) { return n <= 0 ? 0 : (n + kBigScanTile - 1) / kBigScanTile; }
 
-agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, hipStream_t s) {
-    return scan_impl(ctx, LoadU32{in}, out, n, s);
+agal_status scan_u32(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, uint64_t *status, hipStream_t s) {
+    return scan_impl(ctx, LoadU32{in}, out, n, s, status);
 }
 agal_status scan_u32_total(agal_context ctx, const uint32_t *in, uint32_t *out, int64_t n, uint64_t *status,
                            uint32_t *total, hipStream_t s, bool timed, uint32_t *cls) {
     return scan_impl(ctx, LoadU32{in}, out, n, s, status, total, timed, cls);
 }
 agal_status scan_popc64_total(agal_context ctx, const unsigned long long *masks, uint32_t *out, int64_t n,
-                              uint32_t *total, hipStream_t s) {
-    return scan_impl(ctx, LoadPopc64{masks}, out, n, s, nullptr, total);
+                              uint64_t *status, uint32_t *total, hipStream_t s) {
+    return scan_impl(ctx, LoadPopc64{masks}, out, n, s, status, total);
 }
 
 // Several flag scans in one launch: the tiles of all arrays share one ticket
@@ -434,7 +431,7 @@ int64_t scan_flags_u8_multi_tiles(const int64_t *n, int k) {
 }
 
 agal_status scan_flags_u8_multi(agal_context ctx, const uint8_t *const *in, uint32_t *const *out, const int64_t *n,
-                                int k, const uint32_t *extra, uint32_t *totals, hipStream_t s, uint64_t *status_zeroed) {
+                                int k, const uint32_t *extra, uint32_t *totals, hipStream_t s, uint64_t *status) {
     if (k <= 0) return AGAL_OK;
     if (k > kMultiScanMax) return fail(AGAL_EINVAL, "scan_flags_u8_multi: at most %d arrays", kMultiScanMax);
     MultiScanArgs a{};
@@ -450,15 +447,11 @@ agal_status scan_flags_u8_multi(agal_context ctx, const uint8_t *const *in, uint
         a.tile0[i] = tiles;
         tiles += (uint32_t)std::max<int64_t>(1, (n[i] + kScanTile - 1) / kScanTile);   // an empty array still writes out[0]
     }
-    uint64_t *status = status_zeroed;
-    uint32_t *ticket = nullptr;
-    if (status) ticket = reinterpret_cast<uint32_t *>(status + tiles);
-    else AGAL_TRY(lookback_alloc(ctx, tiles, &status, &ticket, s));
+    uint32_t *ticket = reinterpret_cast<uint32_t *>(status + tiles);
     {
         ProfScope prof(ctx, "scan_exclusive", s);
         hipLaunchKernelGGL(k_scan_flags_multi, dim3(tiles), dim3(kScanThreads), 0, s, a, status, ticket);
     }
-    if (!status_zeroed) dev_free(ctx->mem, status, s);
     AGAL_TRY_HIP(hipGetLastError());
     AGAL_TRY(wait_signal(ctx, s, a.sig, "mark scan"));
     for (int i = 0; i <= k; ++i) totals[i] = ctx->h_counts[i];

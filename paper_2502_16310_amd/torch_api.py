@@ -365,6 +365,8 @@ class LinkFractions(torch.autograd.Function):
         fctx.vshape = tuple(vertices.shape)
         key, q, face = links.tensors()
         fctx.mark_non_differentiable(key, face)
+        # keys and faces have no gradient: backward gets None for them instead of zeros of their size (n x Q words)
+        fctx.set_materialize_grads(False)
         return key, q, face
 
     @staticmethod
