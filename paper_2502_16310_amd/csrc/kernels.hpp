@@ -1280,6 +1280,66 @@ __device__ __forceinline__ void ripple_item(const uint32_t *keys_m, int64_t n_m,
     }
 }
 
+// Child generation of one pass (single body), for every parent level m with
+// marks at once.  With pos the exclusive prefix of the level's marks, an
+// existing block of level m + 1 moves up by the children of the marked parents
+// before its own, pos[its parent] 2^D, and the children of marked parent i go
+// where the level holds its smaller keys, plus pos[i] 2^D: no list of the
+// marked keys is needed, and the parents' own bytes (leaf 0, export mark) are
+// set in the same launch.
+struct GrowSeg {
+    const uint32_t *pkeys;   // parent level m
+    const uint8_t *pm;
+    const uint32_t *pos;
+    uint8_t *pleaf, *pmark;  // set in place; null when the level is rebuilt in this launch (as a child level)
+    int64_t pn;
+    const uint32_t *ckeys;   // child level m + 1 before the pass
+    const uint8_t *cleaf, *cmark, *ccf;
+    const uint8_t *cpm;      // its pass marks (null: it was not tested)
+    int64_t cn;
+    uint32_t *nkeys;         // child level m + 1 after the pass
+    uint8_t *nleaf, *nmark, *ncf;   // ncf null: no cell flags to carry or clear
+};
+
+template <int D>
+__device__ __forceinline__ void grow_old_item(const GrowSeg &g, int64_t j) {
+    constexpr int CELLS = D == 3 ? 64 : 16;
+    const uint32_t k = g.ckeys[j];
+    const uint8_t mk = g.cpm ? g.cpm[j] : 0;
+    const int64_t p = j + ((int64_t)g.pos[dev::lower_bound_u32(g.pkeys, g.pn, k >> D)] << D);
+    g.nkeys[p] = k;
+    g.nleaf[p] = mk ? 0 : g.cleaf[j];
+    g.nmark[p] = mk ? mk : g.cmark[j];
+    if (g.ncf)   // one 16- or 64-byte row: 16-byte moves
+#pragma unroll
+        for (int c = 0; c < CELLS / 16; ++c)
+            reinterpret_cast<uint4 *>(g.ncf + p * CELLS)[c] = reinterpret_cast<const uint4 *>(g.ccf + j * CELLS)[c];
+}
+
+// Child t & (2^D - 1) of parent t >> D: its place, or -1 (the parent is not
+// marked); key_out: its key.
+template <int D>
+__device__ __forceinline__ int64_t grow_child_item(const GrowSeg &g, int64_t t, uint32_t &key_out) {
+    constexpr int CELLS = D == 3 ? 64 : 16;
+    const int64_t i = t >> D;
+    const uint8_t mk = g.pm[i];
+    if (!mk) return -1;
+    const uint32_t ci = (uint32_t)(t & ((1 << D) - 1)), key = g.pkeys[i];
+    if (ci == 0 && g.pleaf) {
+        g.pleaf[i] = 0;
+        g.pmark[i] = mk;
+    }
+    const int64_t p = dev::lower_bound_u32(g.ckeys, g.cn, key << D) + ((int64_t)g.pos[i] << D) + ci;
+    key_out = (key << D) | ci;
+    g.nkeys[p] = key_out;
+    g.nleaf[p] = 1;
+    g.nmark[p] = 0;
+    if (g.ncf)
+#pragma unroll
+        for (int c = 0; c < CELLS / 16; ++c) reinterpret_cast<uint4 *>(g.ncf + p * CELLS)[c] = make_uint4(0u, 0u, 0u, 0u);
+    return p;
+}
+
 // Marked blocks of level m: become parents (leaf 0, export mark = pass mark)
 // and their keys are compacted in order into mk.
 __device__ __forceinline__ void mark_parents_item(const uint32_t *keys, const uint8_t *pm, const uint32_t *pos,

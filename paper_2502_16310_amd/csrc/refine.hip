@@ -63,23 +63,6 @@ void launch_flag_faces(const FaceFlagArgs<D> &A, hipStream_t s) {
                        0, s, A);
 }
 
-// table[block grid position] = block index for every block of a level, the
-// block's cell flags zeroed (4^D bytes, 16-byte stores), and the pass's zeroed
-// scratch (zero[0 .. nzero)) cleared, in one launch.
-template <int D>
-__global__ void k_block_table(const uint32_t *keys, int64_t n, int level, int R0, int R1, int NB0, int NB1,
-                              uint32_t *table, uint4 *cf, uint32_t *zero, int64_t nzero) {
-    constexpr int V = (D == 3 ? 64 : 16) / 16;
-    AGAL_GRID_STRIDE(i, n) {
-        int c[3];
-        dev::decode_key<D>(keys[i], level, R0, R1, c);
-        table[((int64_t)c[2] * NB1 + c[1]) * NB0 + c[0]] = (uint32_t)i;
-#pragma unroll
-        for (int j = 0; j < V; ++j) cf[i * V + j] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    AGAL_GRID_STRIDE(i, nzero) zero[i] = 0u;
-}
-
 template <int D>
 __global__ void k_ripple(const uint32_t *keys_m, int64_t n_m, const uint8_t *pm_m, int m, const uint32_t *keys_p,
                          int64_t n_p, const uint8_t *leaf_p, uint8_t *pm_p, int R0, int R1, int R2, uint32_t *err) {
@@ -104,58 +87,46 @@ __global__ void k_init_roots(uint32_t *keys, uint8_t *leaf, uint8_t *mark, int64
     if (blockIdx.x == 0 && threadIdx.x == 0) *err = 0u;
 }
 
-// Child generation of one pass for every parent level m with marks, in two
-// launches: first the parents (k_mark_parents_all), then the new child levels
-// (existing children moved and new children written, k_grow_all).  Segment i
-// is parent level seg[i].m; items of the launches are numbered across the
-// segments by the host-made prefixes.
-struct GrowSeg {
-    const uint32_t *pkeys;   // parent level m
-    const uint8_t *pm;
-    const uint32_t *pos;
-    uint8_t *pleaf, *pmark;
-    int64_t pn;
-    uint32_t *mk;            // marked parent keys (c of them)
-    int64_t c;
-    const uint32_t *ckeys;   // child level m + 1 before the pass
-    const uint8_t *cleaf, *cmark, *ccf;
-    int64_t cn;
-    uint32_t *nkeys;         // child level m + 1 after the pass
-    uint8_t *nleaf, *nmark, *ncf;
-};
+// Child generation of one pass, all parent levels in one launch (items are
+// numbered across the segments by the host-made prefix: a segment's existing
+// children, then its parents times 2^D), and what the next pass starts from: its
+// zeroed scratch and, for the face-centric step, the block table of the level
+// it tests (table[block grid position] = block index; ncf of that level's
+// segment clears the cell flags).  What bounds it is the searches' chains of
+// loads and, on small bodies, the launches: a thread per (parent, child), the
+// unmarked ones leaving at once, in place of a launch that listed the marked
+// keys, one that placed their children and one for the table (20,480 faces, 3
+// passes: 33 us in 8 launches, 20 us in 3; 327,680 faces, 4 passes: 69 -> 60).
 struct GrowArgs {
     GrowSeg seg[kMaxLevels + 1];
-    int64_t pre_p[kMaxLevels + 2];   // prefix of pn
-    int64_t pre_g[kMaxLevels + 2];   // prefix of cn + (c << D)
+    int64_t pre[kMaxLevels + 2];   // prefix of cn + (pn << D)
     int nseg;
-    int D;
+    uint32_t *table;               // of segment 0's child level (null: none)
+    int tlevel, R0, R1;
+    uint32_t *zero;
+    int64_t nzero;
 };
 
-__device__ __forceinline__ int seg_of(const int64_t *pre, int nseg, int64_t i) {
-    int k = 0;
-    while (k + 1 < nseg && pre[k + 1] <= i) ++k;
-    return k;
-}
-
-__global__ void k_mark_parents_all(GrowArgs a) {
-    AGAL_GRID_STRIDE(i, a.pre_p[a.nseg]) {
-        const int k = seg_of(a.pre_p, a.nseg, i);
+template <int D>
+__global__ void k_grow(GrowArgs a) {
+    AGAL_GRID_STRIDE(i, a.pre[a.nseg]) {
+        int k = 0;
+        while (k + 1 < a.nseg && a.pre[k + 1] <= i) ++k;
         const GrowSeg &g = a.seg[k];
-        mark_parents_item(g.pkeys, g.pm, g.pos, g.pleaf, g.pmark, g.mk, i - a.pre_p[k]);
+        const int64_t j = i - a.pre[k];
+        if (j < g.cn) {
+            grow_old_item<D>(g, j);
+            continue;
+        }
+        uint32_t key = 0;
+        const int64_t p = grow_child_item<D>(g, j - g.cn, key);
+        if (p >= 0 && k == 0 && a.table) {
+            int c[3];
+            dev::decode_key<D>(key, a.tlevel, a.R0, a.R1, c);
+            a.table[((int64_t)c[2] * (a.R1 << a.tlevel) + c[1]) * (a.R0 << a.tlevel) + c[0]] = (uint32_t)p;
+        }
     }
-}
-
-template <int CELLS>
-__global__ void k_grow_all(GrowArgs a) {
-    AGAL_GRID_STRIDE(i, a.pre_g[a.nseg]) {
-        const int k = seg_of(a.pre_g, a.nseg, i);
-        const GrowSeg &g = a.seg[k];
-        const int64_t j = i - a.pre_g[k];
-        if (j < g.cn)
-            merge_old_item<CELLS>(g.ckeys, g.cleaf, g.cmark, g.ccf, g.mk, g.c, a.D, g.nkeys, g.nleaf, g.nmark, g.ncf, j);
-        else
-            children_item<CELLS>(g.mk, g.ckeys, g.cn, a.D, g.nkeys, g.nleaf, g.nmark, g.ncf, j - g.cn);
-    }
+    AGAL_GRID_STRIDE(i, a.nzero) a.zero[i] = 0u;
 }
 
 unsigned grid_for(int64_t n, int threads = 256, int64_t cap = 16384) {
@@ -171,7 +142,8 @@ struct Scratch {
     hipStream_t s;
     void *base = nullptr;
     agal_status get(Slab &arrays) { return arrays.get(ctx->mem, &base, s); }
-    ~Scratch() { dev_free(ctx->mem, base, s); }
+    void release() { dev_free(ctx->mem, base, s); }
+    ~Scratch() { release(); }
 };
 
 // A level's arrays (n blocks; cells flags per block, 0: none) in one block.
@@ -245,36 +217,42 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
     }
     // Scratch of pass l, in one block: a zeroed buffer (the look-back status
     // words of the pass's scan of the marks, then the pass marks of every level
-    // l' <= l), the block table where there is one, and per level l' <= l the
-    // marks' prefix and the marked keys (at most all of the level's).
+    // l' <= l), the block table for the face-centric step above level 0 (never
+    // cleared: its entries are checked against the level's keys), and per level
+    // l' <= l the marks' prefix.
     struct PassBuf {
         uint8_t *buf = nullptr;
         int64_t words = 0, status_bytes = 0;
-        uint32_t *table = nullptr, *pos[kMaxLevels + 1] = {}, *mk[kMaxLevels + 1] = {};
+        bool by_face = false;
+        uint32_t *table = nullptr, *pos[kMaxLevels + 1] = {};
     };
-    auto pass_buf = [&](Scratch &sc, int l, int64_t table_entries, PassBuf &pb) -> agal_status {
+    auto pass_buf = [&](Scratch &sc, int l, PassBuf &pb) -> agal_status {
+        pb = PassBuf{};
+        float eps[3];
+        for (int a = 0; a < 3; ++a) eps[a] = dev::kEps * std::max(1.0f, std::max(std::fabs(fo->lo[a]), std::fabs(fo->hi[a])));
+        pb.by_face = !own_bin && block_grid_size<D>(fo, l) <= ctx->flag_table_max &&
+                     face_flag_pairs(D, g->max_extent, fo->d[l], fo->dx[l], eps) <= kFaceFlagMaxPairs;
         int64_t ns[kMaxLevels + 1], tot = 0;
         Slab arrays;
         for (int m = 0; m <= l; ++m) {
             ns[m] = fo->lev[m].n;
             tot += ns[m];
             arrays.add(&pb.pos[m], (size_t)ns[m] + 1);
-            arrays.add(&pb.mk[m], (size_t)ns[m]);
         }
         pb.status_bytes = 8 * (scan_flags_u8_multi_tiles(ns, l + 1) + 1);
         pb.words = (pb.status_bytes + tot + 3) / 4;
         arrays.add(&pb.buf, (size_t)(4 * pb.words));
-        if (table_entries) arrays.add(&pb.table, (size_t)table_entries);
+        if (l > 0 && pb.by_face && ns[l] > 0) arrays.add(&pb.table, (size_t)block_grid_size<D>(fo, l));
         return sc.get(arrays);
     };
     // the level-0 cell flags (for the face-centric step) and the first pass's
     // zeroed scratch are cleared by the root-init launch
-    Scratch keep{ctx, s};
-    PassBuf pb0;
-    if (fo->L > 0) AGAL_TRY(pass_buf(keep, 0, 0, pb0));
+    Scratch scratch[2] = {{ctx, s}, {ctx, s}};   // pass l's is scratch[l & 1]
+    PassBuf pb;
+    if (fo->L > 0) AGAL_TRY(pass_buf(scratch[0], 0, pb));
     hipLaunchKernelGGL(k_init_roots, dim3(grid_for(L0.n)), dim3(256), 0, s, L0.keys, L0.leaf, L0.mark, L0.n, err,
-                       reinterpret_cast<uint4 *>(L0.cf), CELLS / 16, reinterpret_cast<uint32_t *>(pb0.buf),
-                       pb0.words);
+                       reinterpret_cast<uint4 *>(L0.cf), CELLS / 16, reinterpret_cast<uint32_t *>(pb.buf),
+                       pb.words);
 
     dev::BinGrid bins{};
     bins.off = bn->off;
@@ -288,21 +266,9 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
     dev::Faces faces{g->coords, g->aabb, g->rec, g->F};
 
     for (int l = 0; l < fo->L; ++l) {
-        Scratch pass{ctx, s};
+        // the pass's zeroed scratch, block table and cell flags were prepared by
+        // the launch before it (the roots' or the previous pass's children)
         agal::Level &Ll = fo->lev[l];
-        float eps_l[3];
-        for (int a = 0; a < 3; ++a) eps_l[a] = dev::kEps * std::max(1.0f, std::max(std::fabs(fo->lo[a]), std::fabs(fo->hi[a])));
-        const bool by_face = !own_bin && block_grid_size<D>(fo, l) <= ctx->flag_table_max &&
-                             face_flag_pairs(D, g->max_extent, fo->d[l], fo->dx[l], eps_l) <= kFaceFlagMaxPairs;
-        // the block table of level l (face-centric step above level 0): never
-        // cleared, its entries are checked against the level's keys
-        PassBuf pb = pb0;
-        if (l > 0) AGAL_TRY(pass_buf(pass, l, by_face && Ll.n > 0 ? block_grid_size<D>(fo, l) : 0, pb));
-        uint32_t *table = pb.table;
-        if (l > 0) {
-            // zeroed by the table launch when there is one
-            if (!table) fill_u32(reinterpret_cast<uint32_t *>(pb.buf), 0u, pb.words, s);
-        }
         uint8_t *pm[kMaxLevels + 1] = {};
         uint64_t *scan_status = reinterpret_cast<uint64_t *>(pb.buf);
         {
@@ -335,7 +301,7 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             const bool dedup = flag_dedup<D>(bn, fo->dx[l], A.h, Ll.n, ctx->n_cu);
             if (own_bin) {
                 hipLaunchKernelGGL((k_flag_own_bin<D>), dim3((unsigned)waves), dim3(64), 0, s, A);
-            } else if (by_face) {
+            } else if (pb.by_face) {
                 FaceFlagArgs<D> B{};
                 B.rec = g->rec;
                 B.F = g->F;
@@ -345,7 +311,7 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
                     B.dx[a] = A.dx[a];
                     B.eps[a] = A.eps[a];
                 }
-                B.table = table;
+                B.table = pb.table;
                 B.keys = Ll.keys;
                 B.n = Ll.n;
                 B.level = l;
@@ -354,12 +320,6 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
                 B.h = A.h;
                 B.cf = Ll.cf;
                 B.pmark = pm[l];
-                // the cell flags start at zero: level 0's from k_init_roots, the others' here
-                if (table)
-                    hipLaunchKernelGGL(k_block_table<D>, dim3(grid_for(Ll.n)), dim3(256), 0, s, Ll.keys, Ll.n, l,
-                                       fo->roots[0], fo->roots[1], B.NB[0], B.NB[1], table,
-                                       reinterpret_cast<uint4 *>(Ll.cf), reinterpret_cast<uint32_t *>(pb.buf),
-                                       pb.words);
                 if (g->F > 0) {
                     const int G = face_flag_g(g->F, ctx->n_cu);
                     if (G == 16) launch_flag_faces<D, 16>(B, s);
@@ -384,12 +344,12 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
         }
         // (ii) balance ripple, level l down to 1
         for (int m = l; m >= 1; --m) {
-            if (fo->lev[m].n == 0) continue;
+            const agal::Level &M = fo->lev[m], &P = fo->lev[m - 1];
+            if (M.n == 0) continue;
             ProfScope prof(ctx, "balance_ripple", s);
-            hipLaunchKernelGGL(k_ripple<D>, dim3(grid_for(fo->lev[m].n * (D == 3 ? 26 : 8))), dim3(256), 0, s,
-                               fo->lev[m].keys,
-                               fo->lev[m].n, pm[m], m, fo->lev[m - 1].keys, fo->lev[m - 1].n, fo->lev[m - 1].leaf,
-                               pm[m - 1], fo->roots[0], fo->roots[1], fo->roots[2], err);
+            hipLaunchKernelGGL(k_ripple<D>, dim3(grid_for(M.n * (D == 3 ? 26 : 8))), dim3(256), 0, s,
+                               M.keys, M.n, pm[m], m, P.keys, P.n, P.leaf, pm[m - 1],
+                               fo->roots[0], fo->roots[1], fo->roots[2], err);
         }
         // (iii) children: count marks per level, then merge level by level
         uint32_t nmark[kMaxLevels + 2] = {};
@@ -406,12 +366,11 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
         if (nmark[l + 1] != 0) return fail(AGAL_ESTATE, "agal_near_wall_refine: forest lost 2:1 balance");
         // every parent level with marks at once: the new child levels are fresh
         // arrays, and a level that is both a parent (m) and a child (of m - 1)
-        // has its leaf and mark bytes set by the first launch before the second
-        // copies them
+        // takes its marks while it is copied.  The old arrays go back after the
+        // launch that reads them.
         GrowArgs ga{};
-        ga.D = D;
-        agal::Level Nl[kMaxLevels + 1];
-        int segm[kMaxLevels + 1];
+        void *gone[kMaxLevels + 1] = {};
+        const bool next_by_face = l + 1 < fo->L && !own_bin;   // (its cell flags are cleared; other steps write them all)
         for (int m = l; m >= 0; --m) {
             const int64_t c = nmark[m];
             agal::Level &P = fo->lev[m];
@@ -426,24 +385,22 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
                 continue;
             }
             GrowSeg &gs = ga.seg[ga.nseg];
-            segm[ga.nseg] = m;
-            agal::Level &N = Nl[ga.nseg];
-            ++ga.nseg;
+            agal::Level N;
             Slab arrays;
             add_level(arrays, N, C.n + (c << D), m + 1 < fo->L ? CELLS : 0);
             const agal_status got = arrays.get(mem, &N.base, s);
             if (got != AGAL_OK) {
-                for (int k = 0; k < ga.nseg; ++k) dev_free(mem, Nl[k].base, s);
+                for (int k = 0; k < ga.nseg; ++k) dev_free(mem, gone[k], s);
                 return got;
             }
-            gs.mk = pb.mk[m];
             gs.pkeys = P.keys;
             gs.pm = pm[m];
             gs.pos = pb.pos[m];
-            gs.pleaf = P.leaf;
-            gs.pmark = P.mark;
+            const bool rebuilt = m > 0 && nmark[m - 1] != 0;   // by the next segment
+            gs.pleaf = rebuilt ? nullptr : P.leaf;
+            gs.pmark = rebuilt ? nullptr : P.mark;
             gs.pn = P.n;
-            gs.c = c;
+            gs.cpm = m < l ? pm[m + 1] : nullptr;
             gs.ckeys = C.keys;
             gs.cleaf = C.leaf;
             gs.cmark = C.mark;
@@ -452,23 +409,31 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             gs.nkeys = N.keys;
             gs.nleaf = N.leaf;
             gs.nmark = N.mark;
-            // level l + 1's cell flags are written by the next pass
-            gs.ncf = m < l ? N.cf : nullptr;
+            gs.ncf = m < l || next_by_face ? N.cf : nullptr;
+            ga.pre[ga.nseg + 1] = ga.pre[ga.nseg] + gs.cn + (gs.pn << D);
+            gone[ga.nseg++] = C.base;
+            C = N;
         }
-        if (ga.nseg > 0) {
-            for (int k = 0; k < ga.nseg; ++k) {
-                ga.pre_p[k + 1] = ga.pre_p[k] + ga.seg[k].pn;
-                ga.pre_g[k + 1] = ga.pre_g[k] + ga.seg[k].cn + (ga.seg[k].c << D);
-            }
+        agal_status st = AGAL_OK;
+        PassBuf next;
+        if (l + 1 < fo->L) {
+            st = pass_buf(scratch[(l + 1) & 1], l + 1, next);
+            ga.zero = reinterpret_cast<uint32_t *>(next.buf);
+            ga.nzero = next.words;
+        }
+        // (marks at level l, the first segment, whenever there are any: balance marks come from flagged blocks)
+        ga.table = next.table;
+        ga.tlevel = l + 1;
+        ga.R0 = fo->roots[0];
+        ga.R1 = fo->roots[1];
+        if (st == AGAL_OK && (ga.nseg > 0 || ga.nzero > 0)) {
             ProfScope prof(ctx, "child_gen", s);
-            hipLaunchKernelGGL(k_mark_parents_all, dim3(grid_for(ga.pre_p[ga.nseg])), dim3(256), 0, s, ga);
-            hipLaunchKernelGGL(k_grow_all<CELLS>, dim3(grid_for(ga.pre_g[ga.nseg])), dim3(256), 0, s, ga);
+            hipLaunchKernelGGL(k_grow<D>, dim3(grid_for(std::max(ga.pre[ga.nseg], ga.nzero))), dim3(256), 0, s, ga);
         }
-        for (int k = 0; k < ga.nseg; ++k) {
-            agal::Level &C = fo->lev[segm[k] + 1];
-            dev_free(mem, C.base, s);
-            C = Nl[k];
-        }
+        for (int k = 0; k < ga.nseg; ++k) dev_free(mem, gone[k], s);
+        scratch[l & 1].release();
+        pb = next;
+        AGAL_TRY(st);
         AGAL_TRY_HIP(hipGetLastError());
     }
     return AGAL_OK;
