@@ -66,6 +66,7 @@ struct BodyDev {
     // offsets, the lists, and each node's block
     int lists;
     int64_t per_face;
+    uint32_t *ptable;   // dense parent table (null: the hash table, or level 0)
     unsigned long long *hash;
     uint32_t hmask;
     int hshift;
@@ -673,6 +674,7 @@ __global__ __launch_bounds__(64) void k_b_compact(const BodyDev *bodies, int nb,
 template <int D>
 __device__ __forceinline__ BlockFind body_find(const BodyDev &X, uint32_t n) {
     BlockFind B{};
+    B.table = X.ptable;
     B.hash = X.hash;
     B.hmask = X.hmask;
     B.hshift = X.hshift;
@@ -715,7 +717,8 @@ __global__ void k_b_link_blocks(const BodyDev *bodies, int nb, const uint32_t *c
     AGAL_THREAD_ITEMS(it, total) {
         const int b = find_seg(s_pre, nb, it);
         const BodyDev &X = bodies[b];
-        link_block_item<D>(X.keys[X.L][final_buf(X.L, X.L)], it - s_pre[b], X.hash, X.hmask, X.hshift, X.nmask);
+        link_block_item<D>(X.keys[X.L][final_buf(X.L, X.L)], it - s_pre[b], X.ptable, X.L, X.R, X.hash, X.hmask,
+                           X.hshift, X.nmask);
     }
 }
 
@@ -841,6 +844,7 @@ struct BodyHost {
     float max_extent[3] = {};   // largest face box extent per axis (from the sizing run)
     bool lists = false;         // the single-body link step takes list mode
     int64_t list_entries = 0;   // candidate-list entries of the sizing run
+    int64_t parents = 0;        // list mode: positions of the dense parent table (0: none)
 };
 
 }  // namespace batch
@@ -1278,7 +1282,11 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
             X.hash = nullptr;
             X.hmask = 0;
             X.hshift = 0;
-            if (X.L > 0) {
+            int64_t parents = X.L > 0 ? 1 : 0;   // positions of the parents' grid
+            for (int a = 0; a < D; ++a) parents *= X.L > 0 ? (int64_t)X.R[a] << (X.L - 1) : 0;
+            X.ptable = nullptr;
+            h.parents = parents <= kParentTable ? parents : 0;   // its dense table: with the flag step's, below
+            if (X.L > 0 && !h.parents) {
                 int bits = 6;
                 while (bits < 31 && (int64_t(1) << bits) < 2 * ((nL + (1 << D) - 1) >> D)) ++bits;
                 X.hmask = (uint32_t)((int64_t(1) << bits) - 1);
@@ -1412,6 +1420,13 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
             for (int a = 0; a < D; ++a) e *= (int64_t)X.R[a] << p;
             AGAL_TRY(own(bt, &X.ftable[p], (size_t)e));
         }
+    }
+    // the link step's parent table: the last pass's block table is free by then and has its size
+    for (int b = 0; b < bt->nb; ++b) {
+        BodyDev &X = bt->bodies[b];
+        if (!bt->host[b].parents) continue;
+        X.ptable = X.ftable[X.L - 1];
+        if (!X.ptable) AGAL_TRY(own(bt, &X.ptable, (size_t)bt->host[b].parents));
     }
     AGAL_TRY(own(bt, &bt->d_wg_pre, wg_pre.size()));
     AGAL_TRY_HIP(hipMemcpyAsync(bt->d_wg_pre, wg_pre.data(), wg_pre.size() * sizeof(uint32_t), hipMemcpyHostToDevice,

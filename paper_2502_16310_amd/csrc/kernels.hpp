@@ -2857,10 +2857,19 @@ __device__ __forceinline__ void compact_block(int c, int64_t src, int64_t dst, c
 
 // ---- link fractions, list mode: candidate blocks per face ------------------
 // Finest-level block of integer block coordinates c: at level 0 the root's
-// linear index; above, the parent's first child (hash table of parent keys,
-// linear probing; slot = parent key << 32 | index of its first child, ~0
-// empty) plus the child index.  -1: no such block.
+// linear index; above, the parent's first child plus the child index.  The
+// parent is found in a dense table over the parents' grid (index of its first
+// child; never cleared, the block found is checked against its key) or, where
+// that grid is too large, in a hash table of parent keys (linear probing; slot =
+// parent key << 32 | index of its first child, ~0 empty).  -1: no such block.
+// The dense table needs no clearing launch and one load per probe: blocks, count
+// and scatter 27 -> 20 us for 64^3 parents (20,480 faces), 130 -> 119 for 256^3
+// (327,680 faces, 64 MiB of which the body touches a few); the limit is the flag
+// step's own for its tables.
+constexpr int64_t kParentTable = int64_t(1) << 24;   // positions
+
 struct BlockFind {
+    const uint32_t *table;    // null: the hash table
     const unsigned long long *hash;
     uint32_t hmask;   // slots - 1
     int hshift;       // 32 - log2(slots)
@@ -2872,6 +2881,11 @@ struct BlockFind {
 
 __device__ __forceinline__ uint32_t hash_slot(uint32_t key, int shift) { return (key * 2654435761u) >> shift; }
 
+// Place of the block at coordinates p in the dense table over level m.
+__device__ __forceinline__ int64_t parent_slot(const int p[3], int m, const int R[3]) {
+    return ((int64_t)p[2] * (R[1] << m) + p[1]) * (R[0] << m) + p[0];
+}
+
 template <int D>
 __device__ __forceinline__ int64_t find_block(const BlockFind &B, const int c[3]) {
     if (B.level == 0) {
@@ -2882,6 +2896,10 @@ __device__ __forceinline__ int64_t find_block(const BlockFind &B, const int c[3]
     const uint32_t pk = dev::encode_key<D>(p, B.level - 1, B.R[0], B.R[1]);
     uint32_t ci = (uint32_t)(c[0] & 1) | ((uint32_t)(c[1] & 1) << 1);
     if (D == 3) ci |= (uint32_t)(c[2] & 1) << 2;
+    if (B.table) {
+        const int64_t i = (int64_t)B.table[parent_slot(p, B.level - 1, B.R)] + ci;
+        return i < B.n && B.keys[i] == ((pk << D) | ci) ? i : -1;
+    }
     uint32_t s = hash_slot(pk, B.hshift);
     for (uint32_t probe = 0; probe <= B.hmask; ++probe) {
         const unsigned long long v = B.hash[s];
@@ -2895,16 +2913,23 @@ __device__ __forceinline__ int64_t find_block(const BlockFind &B, const int c[3]
     return -1;
 }
 
-// Block i of the level: its node mask zeroed and, above level 0, the parent
-// of every first child (child index 0) inserted into the table.
+// Block i of the level: its node mask zeroed and, above level 0, the parent of
+// every first child (child index 0) entered into the dense or the hash table.
 template <int D>
-__device__ __forceinline__ void link_block_item(const uint32_t *keys, int64_t i, unsigned long long *hash,
-                                                uint32_t hmask, int hshift, unsigned long long *mask) {
+__device__ __forceinline__ void link_block_item(const uint32_t *keys, int64_t i, uint32_t *table, int level,
+                                                const int R[3], unsigned long long *hash, uint32_t hmask, int hshift,
+                                                unsigned long long *mask) {
     mask[i] = 0ull;
-    if (!hash) return;
+    if (!table && !hash) return;
     const uint32_t key = keys[i];
     if (key & ((1u << D) - 1u)) return;
     const uint32_t pk = key >> D;
+    if (table) {
+        int p[3];
+        dev::decode_key<D>(pk, level - 1, R[0], R[1], p);
+        table[parent_slot(p, level - 1, R)] = (uint32_t)i;
+        return;
+    }
     const unsigned long long v = ((unsigned long long)pk << 32) | (uint32_t)i;
     uint32_t s = hash_slot(pk, hshift);
     for (uint32_t probe = 0; probe <= hmask; ++probe) {

@@ -72,11 +72,15 @@ __global__ __launch_bounds__(64) void k_compact_nodes(const uint32_t *count, con
 }
 
 // ---- list mode ------------------------------------------------------------
+// (zero[0 .. nzero): the list build's zeroed words, where no hash table had to
+// be cleared by a launch before)
 template <int D>
-__global__ void k_link_blocks(const uint32_t *keys, int64_t n, unsigned long long *hash, uint32_t hmask, int hshift,
-                              unsigned long long *mask) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        link_block_item<D>(keys, i, hash, hmask, hshift, mask);
+__global__ void k_link_blocks(const uint32_t *keys, int64_t n, BlockFind B, uint32_t *table, unsigned long long *hash,
+                              unsigned long long *mask, uint32_t *zero, int64_t nzero) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t; i < n; i += step)
+        link_block_item<D>(keys, i, table, B.level, B.R, hash, B.hmask, B.hshift, mask);
+    for (int64_t i = t; i < nzero; i += step) zero[i] = 0u;
 }
 
 template <int D, bool kScatter>
@@ -242,7 +246,13 @@ agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t 
     arrays.add(&LB.lwork, (size_t)(work_words + 4 * status_words));   // counts, scatter cursors, status words
     arrays.add(&LB.nmask, (size_t)n);
     arrays.add(&LB.loff, (size_t)n + 1);
-    if (L > 0) {
+    // parents' positions; dense table up to kParentTable of them
+    int64_t grid = 1;
+    for (int a = 0; a < D; ++a) grid *= L > 0 ? (int64_t)fo->roots[a] << (L - 1) : 0;
+    uint32_t *table = nullptr;
+    if (L > 0 && grid <= kParentTable) {
+        arrays.add(&table, (size_t)grid);
+    } else if (L > 0) {
         // parents: n / 2^D (complete families); at most half the slots used
         int bits = 6;
         while (bits < 31 && (int64_t(1) << bits) < 2 * ((n + (1 << D) - 1) >> D)) ++bits;
@@ -253,11 +263,13 @@ agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t 
     AGAL_TRY(st.get(arrays));
     LB.status[0] = reinterpret_cast<uint64_t *>(LB.lwork + work_words);
     LB.status[1] = LB.status[0] + status_words;
-    fill2_u32(LB.lwork, 0u, work_words + 4 * status_words, reinterpret_cast<uint32_t *>(hash), ~0u,
-              hash ? 2 * ((int64_t)B.hmask + 1) : 0, s);
-    hipLaunchKernelGGL((k_link_blocks<D>), dim3(bgrid), dim3(256), 0, s, LL.keys, n, hash, B.hmask, B.hshift,
-                       LB.nmask);
+    const int64_t zero_words = work_words + 4 * status_words;
+    if (hash)
+        fill2_u32(LB.lwork, 0u, zero_words, reinterpret_cast<uint32_t *>(hash), ~0u, 2 * ((int64_t)B.hmask + 1), s);
+    hipLaunchKernelGGL((k_link_blocks<D>), dim3(bgrid), dim3(256), 0, s, LL.keys, n, B, table, hash, LB.nmask,
+                       LB.lwork, hash ? 0 : zero_words);
     B.hash = hash;
+    B.table = table;
     LinkFaceGrid &G = LB.G;
     for (int a = 0; a < 3; ++a) {
         G.lo[a] = fo->lo[a];
