@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstdint>
+#include <type_traits>
 
 #include "device.hpp"
 
@@ -1431,24 +1432,38 @@ struct LinkArgs {
 };
 
 // Candidate faces staged in LDS by one link wave: vertices (3D: and the FP32
-// normal n = (b - a) x (c - a), |E1|_1, |E2|_1 and S = sum |n_a dx_a|), the
-// face id and the face's near code (one bit per (axis, cell position) of the
-// block it was staged for).
-// With kNorms (3D) the face's L1 norms |E1|_1, |E2|_1 and sum_a |n_a dx_a|
-// are staged too (f[12..14]); without them the filter forms them again from
-// the staged corners and normal, with the same expressions, so the results are
-// the same and the staging area is a fifth smaller.
+// normal n = (b - a) x (c - a), and the two numbers of the reach test below),
+// the face id and the face's near code (one bit per (axis, cell position) of
+// the block it was staged for).
+// With kNorms (3D) the face's L1 norms |E1|_1 and |E2|_1 are staged too (f[14],
+// f[15]); without them the filter forms them again from the staged corners, with
+// the same expressions, so the results are the same and the staging area is
+// smaller (as is the code, whose 12 bits are those of one block).
 template <int D, int CAP = kLinkCap, bool kNorms = true>
 struct LinkStaged {
-    static constexpr int NF = D == 3 ? (kNorms ? 15 : 12) : 4;
+    static constexpr int NF = D == 3 ? (kNorms ? 16 : 14) : 4;
+    using Code = typename std::conditional<kNorms, uint32_t, uint16_t>::type;
     float f[NF][CAP];
     int32_t id[CAP];
-    uint32_t code[CAP];
+    Code code[CAP];
 };
 
+// c0: centre of cell (0, 0, 0) of the block the face is staged for.
+//
+// The reach test (link_reach) asks whether any direction's segment from a cell
+// of that block can meet the face's plane: |T . n| <= S = sum_a |n_a dx_a| within
+// rounding, T = o - v0.  T . n is taken as base + sum_a i_a (n_a dx_a) from cell
+// (0, 0, 0)'s value, i_a the cell's position: ten operations for a pair instead of
+// ~45.  It has to pass every pair that link_filter can pass, so the bound adds to
+// S and to the filter's own margins MD and MT (|T|_1 at most nT over the block)
+// what the two sums may differ by: the cells' centres are rounded each on its
+// own (by less than eps / 2 per axis), and the two sums carry at most 2^-20 nT
+// |E1|_1 |E2|_1 of rounding together (|n_a| <= |E1|_1 |E2|_1), and a few of the
+// smallest denormal numbers.  A refined star of 14 M links, 1 M nodes: the pass
+// that finds nodes 395 -> 390 us; with the row pass's two lanes per node, rows 966 -> 920.
 template <int D, int CAP, bool kN>
 __device__ __forceinline__ void link_stage(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r, const float dx[3],
-                                           uint32_t code) {
+                                           const float eps[3], const float c0[3], uint32_t code) {
     S.id[pos] = f;
     if constexpr (D == 3) {
         const float *v = r;
@@ -1462,16 +1477,25 @@ __device__ __forceinline__ void link_stage(LinkStaged<D, CAP, kN> &S, int pos, i
         S.f[9][pos] = n0;
         S.f[10][pos] = n1;
         S.f[11][pos] = n2;
+        const float n1n = fabsf(e10) + fabsf(e11) + fabsf(e12), n2n = fabsf(e20) + fabsf(e21) + fabsf(e22);
+        const float T0 = c0[0] - v[0], T1 = c0[1] - v[1], T2 = c0[2] - v[2];
+        const float nT = ((fabsf(T0) + fabsf(T1)) + fabsf(T2)) + 3.0f * ((dx[0] + dx[1]) + dx[2]);
+        const float Sn = (fabsf(n0 * dx[0]) + fabsf(n1 * dx[1])) + fabsf(n2 * dx[2]);
+        const float Se = (fabsf(n0 * eps[0]) + fabsf(n1 * eps[1])) + fabsf(n2 * eps[2]);
+        const float mx = fmaxf(fmaxf(dx[0], dx[1]), dx[2]);
+        // MD + MT and the two sums' rounding: 2^-20 (max dx + 2 nT) |E1| |E2|, a quarter more for their own roundings
+        const float slack = 1.1920928955078125e-06f * (mx + 2.0f * nT) * (n1n * n2n);
+        S.f[12][pos] = (T0 * n0 + T1 * n1) + T2 * n2;
+        S.f[13][pos] = ((Sn * 1.00001f + Se) + slack) + 1e-43f;
         if constexpr (kN) {
-            S.f[12][pos] = fabsf(e10) + fabsf(e11) + fabsf(e12);
-            S.f[13][pos] = fabsf(e20) + fabsf(e21) + fabsf(e22);
-            S.f[14][pos] = fabsf(n0 * dx[0]) + fabsf(n1 * dx[1]) + fabsf(n2 * dx[2]);
+            S.f[14][pos] = n1n;
+            S.f[15][pos] = n2n;
         }
     } else {
 #pragma unroll
         for (int k = 0; k < 4; ++k) S.f[k][pos] = r[k];
     }
-    S.code[pos] = code;
+    S.code[pos] = (typename LinkStaged<D, CAP, kN>::Code)code;
 }
 
 // FP32 filter of staged face j for a link origin o over all direction pairs.
@@ -1505,8 +1529,8 @@ __device__ __forceinline__ uint32_t link_filter(const LinkStaged<D, CAP, kN> &S,
         const float n0 = S.f[9][j], n1 = S.f[10][j], n2 = S.f[11][j];
         float n1n, n2n;
         if constexpr (kN) {
-            n1n = S.f[12][j];
-            n2n = S.f[13][j];
+            n1n = S.f[14][j];
+            n2n = S.f[15][j];
         } else {
             n1n = fabsf(e10) + fabsf(e11) + fabsf(e12);
             n2n = fabsf(e20) + fabsf(e21) + fabsf(e22);
@@ -1590,29 +1614,14 @@ __device__ __forceinline__ uint32_t link_filter(const LinkStaged<D, CAP, kN> &S,
     return cm;
 }
 
-// Whether any direction pair can pass the filter for staged face j and origin
-// o: the filter's |t| test with the largest |D . n| of any direction,
-// S = sum |n_a dx_a| (3D; always in 2D).
+// Whether any direction pair can pass the filter for staged face j and the cell
+// at position i of the block it was staged for (3D; always in 2D).
 template <int D, int CAP, bool kN>
-__device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, kN> &S, int j, const float o[3], const float dx[3]) {
+__device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, kN> &S, int j, const float i[3], const float dx[3]) {
     if constexpr (D == 3) {
-        const float T0 = o[0] - S.f[0][j], T1 = o[1] - S.f[1][j], T2 = o[2] - S.f[2][j];
-        const float n0 = S.f[9][j], n1 = S.f[10][j], n2 = S.f[11][j];
-        float n1n, n2n, Sn;
-        if constexpr (kN) {
-            n1n = S.f[12][j];
-            n2n = S.f[13][j];
-            Sn = S.f[14][j];
-        } else {
-            n1n = (fabsf(S.f[3][j] - S.f[0][j]) + fabsf(S.f[4][j] - S.f[1][j])) + fabsf(S.f[5][j] - S.f[2][j]);
-            n2n = (fabsf(S.f[6][j] - S.f[0][j]) + fabsf(S.f[7][j] - S.f[1][j])) + fabsf(S.f[8][j] - S.f[2][j]);
-            Sn = (fabsf(n0 * dx[0]) + fabsf(n1 * dx[1])) + fabsf(n2 * dx[2]);
-        }
-        const float nT = fabsf(T0) + fabsf(T1) + fabsf(T2);
-        const float mx_ = fmaxf(fmaxf(dx[0], dx[1]), dx[2]) * 9.5367431640625e-07f;
-        const float MD = mx_ * n1n * n2n;
-        const float MT = 9.5367431640625e-07f * nT * n1n * n2n;
-        return fabsf((T0 * n0 + T1 * n1) + T2 * n2) <= Sn + MD + MT;
+        const float s = ((S.f[12][j] + i[0] * (S.f[9][j] * dx[0])) + i[1] * (S.f[10][j] * dx[1])) +
+                        i[2] * (S.f[11][j] * dx[2]);
+        return !(fabsf(s) > S.f[13][j]);   // a NaN stays for the filter
     } else {
         return true;
     }
@@ -1664,6 +1673,7 @@ __device__ __forceinline__ double link_decide(const LinkStaged<D, CAP, kN> &S, i
 template <int D>
 struct LinkBox {
     float mlo[D][4], mhi[D][4];
+    float c0[3];   // centre of cell (0, 0, 0)
     float qlo[3], qhi[3];
     int ilo[3], ihi[3];
 };
@@ -1674,6 +1684,7 @@ __device__ __forceinline__ void link_box(const LinkArgs<D, Q> &A, const int sc[3
     for (int a = 0; a < 3; ++a) {
         bx.qlo[a] = bx.qhi[a] = 0.0f;
         bx.ilo[a] = bx.ihi[a] = 0;
+        bx.c0[a] = a < D ? dev::uniform(dev::cell_centre(A.lo[a], 4 * sc[a], A.dx[a])) : 0.0f;
     }
 #pragma unroll
     for (int a = 0; a < D; ++a)
@@ -1739,7 +1750,7 @@ __device__ __forceinline__ int link_gather(const LinkArgs<D, Q> &A, int64_t blk,
             rest &= ~part;
             const int pos = count + dev::lanes_below(part);
             count += __popcll(part);
-            if (now) link_stage<D>(S, pos, f, r, A.dx, face_code(bb));
+            if (now) link_stage<D>(S, pos, f, r, A.dx, A.eps, bx.c0, face_code(bb));
         }
     };
     if (A.list) {
@@ -1793,6 +1804,7 @@ __device__ __forceinline__ void links_wave(const LinkArgs<D, Q> &A, int64_t firs
     // bits.  (2D: block t of the wave uses bits 8t..8t+7; a face near a cell of
     // block t lies in block t's link box, so it is staged, and coded, for t.)
     const int pos3[3] = {cell & 3, (cell >> 2) & 3, cell >> 4};
+    const float fpos[3] = {(float)pos3[0], (float)pos3[1], (float)pos3[2]};
     uint32_t lbits = 0;
 #pragma unroll
     for (int a = 0; a < D; ++a) lbits |= 1u << (sub * 4 * D + 4 * a + pos3[a]);
@@ -1887,7 +1899,7 @@ __device__ __forceinline__ void links_wave(const LinkArgs<D, Q> &A, int64_t firs
                 if (nm) {
                     j = j0 + __builtin_ctzll(nm);
                     nm &= nm - 1ull;
-                    pass = link_reach<D>(S, j, o, A.dx);
+                    pass = link_reach<D>(S, j, fpos, A.dx);
                 }
                 const uint64_t m = __ballot(pass);
                 if (pass) s_qa[na + dev::lanes_below(m)] = ((uint32_t)lane << 7) | (uint32_t)j;
@@ -2032,10 +2044,13 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                 dev::load_rec<D>(A.faces.rec, f, r);
                 dev::decode_key<D>(A.keys[b], A.level, A.R[0], A.R[1], bc);
                 bits = link_code_at<D, Q>(A, bc, r + D * D);
+                float c0[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int a = 0; a < D; ++a) c0[a] = dev::cell_centre(A.lo[a], 4 * bc[a], A.dx[a]);
                 cnt = 1;
 #pragma unroll
                 for (int a = 0; a < D; ++a) cnt *= (uint32_t)__popc((bits >> (4 * a)) & 15u);
-                link_stage<D>(S, lane, f, r, A.dx, bits);
+                link_stage<D>(S, lane, f, r, A.dx, A.eps, c0, bits);
             }
         }
         const uint32_t incl = dev::wave_inclusive_sum(cnt);
@@ -2122,11 +2137,8 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                     const int iz = D == 3 ? (int)((en >> (16 + 2 * uz)) & 3u) : 0;
                     const int cell = ix | (iy << 2) | (iz << 4);
                     if (!((s_m[s_head[k]] >> cell) & 1ull)) {
-                        float o[3] = {0.0f, 0.0f, 0.0f};
-                        o[0] = dev::cell_centre(A.lo[0], 4 * s_bc[k][0] + ix, A.dx[0]);
-                        o[1] = dev::cell_centre(A.lo[1], 4 * s_bc[k][1] + iy, A.dx[1]);
-                        if constexpr (D == 3) o[2] = dev::cell_centre(A.lo[2], 4 * s_bc[k][2] + iz, A.dx[2]);
-                        want = link_reach<D>(S, k, o, A.dx);
+                        const float i3[3] = {(float)ix, (float)iy, (float)iz};
+                        want = link_reach<D>(S, k, i3, A.dx);
                         item = ((uint32_t)k << 8) | (uint32_t)cell;
                     }
                 }
@@ -2147,7 +2159,7 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 }
 
 // Row pass of list mode: one wave per kRowNodes consecutive nodes (node k:
-// block nblk[k], node key written beforehand), one lane per node.  28 nodes
+// block nblk[k], node key written beforehand), two lanes per node.  28 nodes
 // per wave keep the best-key table at 5.8 KB and the wave's LDS at 8.75 KB, so
 // that 18 waves fit a CU (64 nodes: 9 waves and 14 % slower; 16, 20, 24, 32
 // and 48 measured too: fewer nodes per wave stage the same entries more often,
@@ -2159,7 +2171,7 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // links_wave, in a node-major table from which the wave writes its rows of q
 // and face ids as flat coalesced runs.
 constexpr int kRowNodes = 28;   // nodes per wave of the row pass
-static_assert(kRowNodes % 4 == 0 && kRowNodes <= 64, "16-byte row stores, one lane per node");
+static_assert(kRowNodes % 4 == 0 && kRowNodes <= 32, "16-byte row stores, two lanes per node");
 
 template <int D, int Q>
 __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint32_t *nblk,
@@ -2176,9 +2188,12 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         for (int a = 0; a < 3; ++a) s_dir[lane][a] = (float)dir_c<D>(1 + 2 * lane, a) * A.dx[a];
     const int64_t k0 = chunk * kRowNodes;
     const int nnodes = (int)min<int64_t>(kRowNodes, (int64_t)nn - k0);
-    const bool valid = lane < nnodes;
-    const uint32_t myb = valid ? nblk[k0 + lane] : 0xFFFFFFFFu;
-    const uint64_t nkey = valid ? node_key[k0 + lane] : 0ull;
+    // two lanes per node while the staged faces are looked through: lane l and l + 32 have node l, and each
+    // half of its faces
+    const int node = lane & 31, half = lane >> 5;
+    const bool valid = node < nnodes;
+    const uint32_t myb = valid ? nblk[k0 + node] : 0xFFFFFFFFu;
+    const uint64_t nkey = valid ? node_key[k0 + node] : 0ull;
     const int cell = (int)(nkey % CELLS);
     int bc[3] = {0, 0, 0};
     if (valid) dev::decode_key<D>((uint32_t)(nkey / CELLS), A.level, A.R[0], A.R[1], bc);
@@ -2186,21 +2201,19 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     o[0] = dev::cell_centre(A.lo[0], 4 * bc[0] + (cell & 3), A.dx[0]);
     o[1] = dev::cell_centre(A.lo[1], 4 * bc[1] + ((cell >> 2) & 3), A.dx[1]);
     o[2] = D == 3 ? dev::cell_centre(A.lo[2], 4 * bc[2] + (cell >> 4), A.dx[2]) : 0.0f;
+    const int pos3[3] = {cell & 3, (cell >> 2) & 3, cell >> 4};
+    const float fpos[3] = {(float)pos3[0], (float)pos3[1], (float)pos3[2]};
     uint32_t lbits = 0;
-    {
-        const int pos3[3] = {cell & 3, (cell >> 2) & 3, cell >> 4};
 #pragma unroll
-        for (int a = 0; a < D; ++a) lbits |= 1u << (4 * a + pos3[a]);
-    }
+    for (int a = 0; a < D; ++a) lbits |= 1u << (4 * a + pos3[a]);
     // node-major best keys: a row of Q - 1 keys per node, read back in row order
     __shared__ unsigned long long s_best[kRowNodes][Q - 1];
     __shared__ float s_o[kRowNodes][3];
     constexpr int TCAP = 128;
     __shared__ uint16_t s_qa[TCAP];   // (node, staged entry) pairs to filter: l << 5 | j
     __shared__ uint16_t s_qb[TCAP];   // direction pairs to decide: l << 10 | j << 5 | p
+    for (int i = lane; i < kRowNodes * (Q - 1); i += dev::kWave) (&s_best[0][0])[i] = ~0ull;
     if (lane < kRowNodes) {
-#pragma unroll
-        for (int i = 0; i < Q - 1; ++i) s_best[lane][i] = ~0ull;
 #pragma unroll
         for (int a = 0; a < 3; ++a) s_o[lane][a] = o[a];
     }
@@ -2275,7 +2288,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
                 if (s_sblk[mid] <= myb) lo = mid + 1;
                 else hi = mid;
             }
-            for (int j = jlo; j < lo; ++j) nm |= ((S.code[j] & lbits) == lbits) ? (1u << j) : 0u;
+            for (int j = jlo + half; j < lo; j += 2) nm |= ((S.code[j] & lbits) == lbits) ? (1u << j) : 0u;
         }
         while (__ballot(nm != 0)) {
             bool pass = false;
@@ -2283,10 +2296,10 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
             if (nm) {
                 j = __builtin_ctz(nm);
                 nm &= nm - 1u;
-                pass = link_reach<D>(S, j, o, A.dx);
+                pass = link_reach<D>(S, j, fpos, A.dx);
             }
             const uint64_t m = __ballot(pass);
-            if (pass) s_qa[na + dev::lanes_below(m)] = (uint16_t)((lane << 5) | j);
+            if (pass) s_qa[na + dev::lanes_below(m)] = (uint16_t)((node << 5) | j);
             na += __popcll(m);
             if (na >= 64) take_a(64);
         }
@@ -2305,7 +2318,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         bool keep = false;
         int32_t f = -1;
         uint32_t b = 0, code = 0;
-        float r[RF];
+        float r[RF], ec0[3] = {0.0f, 0.0f, 0.0f};
         if (e < e1) {
             f = A.list[e];
             b = lblk[e];
@@ -2314,6 +2327,8 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
                 int ebc[3] = {0, 0, 0};
                 dev::decode_key<D>(A.keys[b], A.level, A.R[0], A.R[1], ebc);
                 code = link_code_at<D, Q>(A, ebc, r + D * D);
+#pragma unroll
+                for (int a = 0; a < D; ++a) ec0[a] = dev::cell_centre(A.lo[a], 4 * ebc[a], A.dx[a]);
                 keep = true;
 #pragma unroll
                 for (int a = 0; a < D; ++a) keep = keep && ((code >> (4 * a)) & 15u) != 0u;
@@ -2331,7 +2346,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
             const int pos = count + dev::lanes_below(part);
             count += __popcll(part);
             if (now) {
-                link_stage<D>(S, pos, f, r, A.dx, code);
+                link_stage<D>(S, pos, f, r, A.dx, A.eps, ec0, code);
                 s_sblk[pos] = b;
             }
         }
