@@ -785,7 +785,7 @@ __global__ void k_b_node_map(const BodyDev *bodies, int nb, const uint32_t *cnt,
 }
 
 template <int D, int Q>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_b_links_rows(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_b_links_rows(
     const BodyDev *bodies, int nb, const uint32_t *cnt, const uint32_t *nodes, const uint32_t *wg_pre) {
     const uint32_t it = blockIdx.x;
     const int b = body_of_wg(wg_pre, nb, it);

@@ -1459,7 +1459,7 @@ struct LinkStaged {
 // what the two sums may differ by: the cells' centres are rounded each on its
 // own (by less than eps / 2 per axis), and the two sums carry at most 2^-20 nT
 // |E1|_1 |E2|_1 of rounding together (|n_a| <= |E1|_1 |E2|_1), and a few of the
-// smallest denormal numbers.  A refined star of 14 M links, 1 M nodes: the pass
+// smallest denormal numbers.  A refined star of 7.3 M nodes: the pass
 // that finds nodes 395 -> 390 us; with the row pass's two lanes per node, rows 966 -> 920.
 template <int D, int CAP, bool kN>
 __device__ __forceinline__ void link_stage(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r, const float dx[3],
@@ -2160,7 +2160,7 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 
 // Row pass of list mode: one wave per kRowNodes consecutive nodes (node k:
 // block nblk[k], node key written beforehand), two lanes per node.  28 nodes
-// per wave keep the best-key table at 5.8 KB and the wave's LDS at 8.75 KB, so
+// per wave keep the best-key table at 6 KB and the wave's LDS at 8.6 KB, so
 // that 18 waves fit a CU (64 nodes: 9 waves and 14 % slower; 16, 20, 24, 32
 // and 48 measured too: fewer nodes per wave stage the same entries more often,
 // which costs more than the extra waves gain).
@@ -2170,6 +2170,11 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // own block near its cell; the best hit per direction is kept as in
 // links_wave, in a node-major table from which the wave writes its rows of q
 // and face ids as flat coalesced runs.
+// Bound by vector instructions (2,300 per wave with the rows' words put together
+// element by element from a table without the rest direction, whose key for no
+// hit needed a select; ~2,000 with the table laid out and keyed as the rows are
+// written): a refined star's 7.3 M nodes 920 -> 860 us, 1.7 M nodes of D3Q19
+// 182 -> 172; six bodies in one launch 720 -> 677 (there with five waves a SIMD).
 constexpr int kRowNodes = 28;   // nodes per wave of the row pass
 static_assert(kRowNodes % 4 == 0 && kRowNodes <= 32, "16-byte row stores, two lanes per node");
 
@@ -2206,24 +2211,23 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     uint32_t lbits = 0;
 #pragma unroll
     for (int a = 0; a < D; ++a) lbits |= 1u << (4 * a + pos3[a]);
-    // node-major best keys: a row of Q - 1 keys per node, read back in row order
-    __shared__ unsigned long long s_best[kRowNodes][Q - 1];
-    __shared__ float s_o[kRowNodes][3];
+    // node-major best keys (t's bits, face), a row of Q per node: the wave's rows of q and face ids as they are
+    // written.  A key without a hit is (-1.0f, -1), above every hit's as unsigned numbers.
+    constexpr unsigned long long kNoHit = 0xBF800000FFFFFFFFull;
+    __shared__ alignas(16) unsigned long long s_best[kRowNodes * Q];
     constexpr int TCAP = 128;
     __shared__ uint16_t s_qa[TCAP];   // (node, staged entry) pairs to filter: l << 5 | j
     __shared__ uint16_t s_qb[TCAP];   // direction pairs to decide: l << 10 | j << 5 | p
-    for (int i = lane; i < kRowNodes * (Q - 1); i += dev::kWave) (&s_best[0][0])[i] = ~0ull;
-    if (lane < kRowNodes) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) s_o[lane][a] = o[a];
-    }
+    static_assert(kRowNodes * Q % 4 == 0, "rows written four elements at a time");
+    for (int i = 2 * lane; i < kRowNodes * Q; i += 2 * dev::kWave)
+        *reinterpret_cast<ulonglong2 *>(s_best + i) = make_ulonglong2(kNoHit, kNoHit);
     int na = 0, nb = 0;
 
     auto consider = [&](int i, int l, double t64, int32_t f) {
         if (!(t64 >= 0.0 && t64 <= 1.0)) return;
         const float t = (float)t64 + 0.0f;
         const unsigned long long key = ((unsigned long long)__float_as_uint(t) << 32) | (uint32_t)f;
-        atomicMin(&s_best[l][i], key);
+        atomicMin(&s_best[l * Q + i], key);
     };
     auto take_b = [&](int take) {
         dev::wave_sync();
@@ -2231,14 +2235,14 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         dev::wave_sync();
         if (lane < nb - take) s_qb[lane] = s_qb[take + lane];
         nb -= take;
+        const int l = (int)(item >> 10);   // lane l has node l's centre
+        const double ol[3] = {__shfl(o[0], l, dev::kWave), __shfl(o[1], l, dev::kWave), __shfl(o[2], l, dev::kWave)};
         if (lane < take) {
-            const int l = (int)(item >> 10);
             const int j = (int)((item >> 5) & 31u);
             const int p = (int)(item & 31u);
-            const double ol[3] = {s_o[l][0], s_o[l][1], s_o[l][2]};
             const double t = link_decide<D>(S, j, ol, s_dir[p]);
-            consider(2 * p, l, t, S.id[j]);
-            consider(2 * p + 1, l, -t, S.id[j]);
+            consider(1 + 2 * p, l, t, S.id[j]);
+            consider(2 + 2 * p, l, -t, S.id[j]);
         }
     };
     auto take_a = [&](int take) {
@@ -2248,11 +2252,9 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         if (lane < na - take) s_qa[lane] = s_qa[take + lane];
         na -= take;
         const int l = (int)(item >> 5), j = (int)(item & 31u);
+        const float ol[3] = {__shfl(o[0], l, dev::kWave), __shfl(o[1], l, dev::kWave), __shfl(o[2], l, dev::kWave)};
         uint32_t cm = 0;
-        if (lane < take) {
-            const float ol[3] = {s_o[l][0], s_o[l][1], s_o[l][2]};
-            cm = link_filter<D, NP, false, kLinkCap>(S, j, ol, A.dx, nullptr);
-        }
+        if (lane < take) cm = link_filter<D, NP, false, kLinkCap>(S, j, ol, A.dx, nullptr);
         while (__ballot(cm != 0)) {
             const bool has = cm != 0;
             int p = 0;
@@ -2361,41 +2363,17 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     float *qd = A.q + k0 * Q;
     int32_t *fd = A.face + k0 * Q;
     const int total = nnodes * Q, total4 = total & ~3;
-    int l = (4 * lane) / Q, i = (4 * lane) % Q;   // node and direction of element 4 lane, advanced 256 a step
     for (int e = 4 * lane; e < total4; e += 256) {
-        float qv[4];
-        int32_t fv[4];
-        int ll = l, ii = i;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const unsigned long long key = ii == 0 ? ~0ull : s_best[ll][ii - 1];
-            const bool hit = key != ~0ull;
-            qv[k] = hit ? __uint_as_float((uint32_t)(key >> 32)) : -1.0f;
-            fv[k] = hit ? (int32_t)(uint32_t)key : -1;
-            if (++ii == Q) {
-                ii = 0;
-                ++ll;
-            }
-        }
+        const uint4 k01 = *reinterpret_cast<const uint4 *>(s_best + e), k23 = *reinterpret_cast<const uint4 *>(s_best + e + 2);
         // rows are not read again by this pass: stored past the caches' keep policy
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        typedef int i4 __attribute__((ext_vector_type(4)));
-        __builtin_nontemporal_store(f4{qv[0], qv[1], qv[2], qv[3]}, reinterpret_cast<f4 *>(qd + e));
-        __builtin_nontemporal_store(i4{fv[0], fv[1], fv[2], fv[3]}, reinterpret_cast<i4 *>(fd + e));
-        i += 256 % Q;
-        l += 256 / Q;
-        if (i >= Q) {
-            i -= Q;
-            ++l;
-        }
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        __builtin_nontemporal_store(u4{k01.y, k01.w, k23.y, k23.w}, reinterpret_cast<u4 *>(qd + e));
+        __builtin_nontemporal_store(u4{k01.x, k01.z, k23.x, k23.z}, reinterpret_cast<u4 *>(fd + e));
     }
     if (lane < total - total4) {
         const int e = total4 + lane;
-        const int le = e / Q, ie = e % Q;
-        const unsigned long long key = ie == 0 ? ~0ull : s_best[le][ie - 1];
-        const bool hit = key != ~0ull;
-        qd[e] = hit ? __uint_as_float((uint32_t)(key >> 32)) : -1.0f;
-        fd[e] = hit ? (int32_t)(uint32_t)key : -1;
+        qd[e] = __uint_as_float((uint32_t)(s_best[e] >> 32));
+        fd[e] = (int32_t)(uint32_t)s_best[e];
     }
 }
 
