@@ -1627,12 +1627,27 @@ __device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, kN> &S, int 
     }
 }
 
+// x, negated when by is negative.
+__device__ __forceinline__ double flip_sign(double x, double by) {
+    return __longlong_as_double(__double_as_longlong(x) ^ (__double_as_longlong(by) & LLONG_MIN));
+}
+
 // FP64 decision for staged face j, direction Dv (the first direction of a
 // pair) and origin o: the segment-triangle test (Moller-Trumbore, two-sided,
 // closed) in the same expression order as the definition; returns t of Dv,
 // or NaN when the line misses the face or det = 0.  The opposite direction
 // hits at -t (negating D negates P, det and t exactly), so the pair has a
 // link in direction Dv when t is in [0, 1] and in -Dv when -t is.
+//
+// The definition asks for u = un / det >= 0, u <= 1, v >= 0 and u + v <= 1, each
+// rounded.  Only t is divided here; the answers are the same.  No quotient
+// underflows (un and det are sums of products of FP32 numbers), so u and v have
+// the signs of un and vn once det's is taken out; un / |det| rounds to more than
+// 1 exactly when un > |det|; and fl(u + v) is off by at most 2^-52 near 1, so
+// beyond 2^-50 |det| from un + vn = |det| the sum decides, and within it the two
+// quotients are formed as the definition has them.  A division is ~14 of the
+// ~130 instructions of a decision: the row pass of a refined star's 7.3 M nodes
+// 838 -> 811 us, of 1.7 M nodes of D3Q19 168 -> 162.
 template <int D, int CAP, bool kN>
 __device__ __forceinline__ double link_decide(const LinkStaged<D, CAP, kN> &S, int j, const double o[3], const float dir[3]) {
     const double nan = __builtin_nan("");
@@ -1646,11 +1661,14 @@ __device__ __forceinline__ double link_decide(const LinkStaged<D, CAP, kN> &S, i
                              Dv[0] * E2[1] - Dv[1] * E2[0]};
         const double det = E1[0] * P[0] + E1[1] * P[1] + E1[2] * P[2];
         if (det == 0.0) return nan;
-        const double u = (T[0] * P[0] + T[1] * P[1] + T[2] * P[2]) / det;
-        if (u < 0.0 || u > 1.0) return nan;
+        const double ad = fabs(det);
+        const double un = flip_sign(T[0] * P[0] + T[1] * P[1] + T[2] * P[2], det);
+        if (un < 0.0 || un > ad) return nan;
         const double Qv[3] = {T[1] * E1[2] - T[2] * E1[1], T[2] * E1[0] - T[0] * E1[2], T[0] * E1[1] - T[1] * E1[0]};
-        const double v = (Dv[0] * Qv[0] + Dv[1] * Qv[1] + Dv[2] * Qv[2]) / det;
-        if (v < 0.0 || u + v > 1.0) return nan;
+        const double vn = flip_sign(Dv[0] * Qv[0] + Dv[1] * Qv[1] + Dv[2] * Qv[2], det);
+        const double over = (un + vn) - ad, m = ad * 0x1p-50;
+        if (vn < 0.0 || over > m) return nan;
+        if (over >= -m && un / ad + vn / ad > 1.0) return nan;
         return (E2[0] * Qv[0] + E2[1] * Qv[1] + E2[2] * Qv[2]) / det;
     } else {
         const double a0 = S.f[0][j], a1 = S.f[1][j];
@@ -1659,10 +1677,9 @@ __device__ __forceinline__ double link_decide(const LinkStaged<D, CAP, kN> &S, i
         const double den = D0 * e1 - D1 * e0;
         if (den == 0.0) return nan;
         const double w0 = a0 - o[0], w1 = a1 - o[1];
-        const double t = (w0 * e1 - w1 * e0) / den;
-        const double sp = (w0 * D1 - w1 * D0) / den;
-        if (!(sp >= 0.0 && sp <= 1.0)) return nan;
-        return t;
+        const double sn = flip_sign(w0 * D1 - w1 * D0, den);
+        if (!(sn >= 0.0 && sn <= fabs(den))) return nan;
+        return (w0 * e1 - w1 * e0) / den;
     }
 }
 

@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void k_node_map(const unsigned long long *mask
 }
 
 template <int D, int Q>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_links_rows(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_rows(
     LinkArgs<D, Q> A, const uint32_t *lblk, const uint32_t *nblk, uint32_t nn) {
     links_rows_nodes<D, Q>(A, lblk, nblk, A.node_key, nn, (int64_t)blockIdx.x);
 }
