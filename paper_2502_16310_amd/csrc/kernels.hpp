@@ -2028,9 +2028,10 @@ __device__ __forceinline__ uint32_t div_1to4(uint32_t u, uint32_t n) {
 // the new bits go out with one device atomic per block at the window's end
 // (device-scope atomics are performed past the per-XCD L2, so one per hit
 // costs memory-side traffic).
-// mask: one 64-bit word per block, zeroed; lblk: the block of each entry.
+// mask: one 64-bit word per block, zeroed; lblk: the block of each entry;
+// lcode (written): its near code, 0 for an entry without a face or block.
 template <int D, int Q>
-__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, const uint32_t *lblk,
+__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, const uint32_t *lblk, uint16_t *lcode,
                                                     unsigned long long *mask, int64_t wg, int64_t nwg) {
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
@@ -2069,6 +2070,7 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                 for (int a = 0; a < D; ++a) cnt *= (uint32_t)__popc((bits >> (4 * a)) & 15u);
                 link_stage<D>(S, lane, f, r, A.dx, A.eps, c0, bits);
             }
+            lcode[e] = (uint16_t)bits;
         }
         const uint32_t incl = dev::wave_inclusive_sum(cnt);
         const uint32_t npairs = (uint32_t)__builtin_amdgcn_readlane((int)incl, dev::kWave - 1);
@@ -2192,12 +2194,15 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // hit needed a select; ~2,000 with the table laid out and keyed as the rows are
 // written): a refined star's 7.3 M nodes 920 -> 860 us, 1.7 M nodes of D3Q19
 // 182 -> 172; six bodies in one launch 720 -> 677 (there with five waves a SIMD).
+// The entries' near codes come from the node pass, 2 B an entry: formed here they
+// took ~190 instructions of a wave that has ~20 entries on its 64 lanes (star 823 ->
+// 788, the node pass 375 -> 381).
 constexpr int kRowNodes = 28;   // nodes per wave of the row pass
 static_assert(kRowNodes % 4 == 0 && kRowNodes <= 32, "16-byte row stores, two lanes per node");
 
 template <int D, int Q>
-__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint32_t *nblk,
-                                                 const uint64_t *node_key, uint32_t nn, int64_t chunk) {
+__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint16_t *lcode,
+                                                 const uint32_t *nblk, const uint64_t *node_key, uint32_t nn, int64_t chunk) {
     constexpr int CELLS = D == 3 ? 64 : 16;
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
@@ -2341,16 +2346,16 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         if (e < e1) {
             f = A.list[e];
             b = lblk[e];
-            if (f >= 0 && f < A.faces.F && (int64_t)b < A.n) {
+            code = lcode[e];   // 0: not a face and block
+            keep = true;
+#pragma unroll
+            for (int a = 0; a < D; ++a) keep = keep && ((code >> (4 * a)) & 15u) != 0u;
+            if (keep) {
                 dev::load_rec<D>(A.faces.rec, f, r);
                 int ebc[3] = {0, 0, 0};
                 dev::decode_key<D>(A.keys[b], A.level, A.R[0], A.R[1], ebc);
-                code = link_code_at<D, Q>(A, ebc, r + D * D);
 #pragma unroll
                 for (int a = 0; a < D; ++a) ec0[a] = dev::cell_centre(A.lo[a], 4 * ebc[a], A.dx[a]);
-                keep = true;
-#pragma unroll
-                for (int a = 0; a < D; ++a) keep = keep && ((code >> (4 * a)) & 15u) != 0u;
             }
         }
         uint64_t rest = __ballot(keep);
