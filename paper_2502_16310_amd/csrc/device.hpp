@@ -134,6 +134,15 @@ __device__ __forceinline__ float cell_centre(float lo, int g, float dx) {
     return lo + (float)(2 * g + 1) * (0.5f * dx);
 }
 
+// Workgroup b of n to tile: consecutive workgroups go to the eight XCDs in turn,
+// each with an L2 of its own; here G consecutive tiles go to one XCD (the last,
+// partial group of 8 G as they come).
+template <int G>
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n) {
+    const uint32_t r = b % (8u * G), b0 = b - r;
+    return b0 + 8u * G <= n ? b0 + (r & 7u) * G + (r >> 3) : b;
+}
+
 // Lower bound of `key` in sorted keys[0..n).
 __device__ __forceinline__ int64_t lower_bound_u32(const uint32_t *keys, int64_t n, uint32_t key) {
     int64_t lo = 0, hi = n;

@@ -2192,13 +2192,16 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
     }
 }
 
-// Row pass of list mode: one wave per kRowNodes consecutive nodes (node k:
+// Row pass of list mode: one wave per row_nodes(Q) consecutive nodes (node k:
 // block nblk[k], node key written beforehand), two lanes per node.  28 nodes
 // per wave keep the best-key table at 6 KB and the wave's LDS at 8.6 KB, so
 // that 18 waves fit a CU (64 nodes: 9 waves and 14 % slower; 16, 20, 24, 32
 // and 48 measured too: fewer nodes per wave stage the same entries more often,
 // which costs more than the extra waves gain).
-// kRowNodes * Q words stay a multiple of four for the 16-byte row stores.  The wave stages
+// D3Q19 and D2Q9 rows leave room for the 32 nodes that two lanes each allow: 1.7 M nodes of D3Q19 150.5 -> 146.5 us.
+// Runs of 32 consecutive waves go to one XCD, as neighbours share faces and list entries:
+// -> 142.8 us, a refined star 750 -> 741 (runs of 128 and 512 the same).
+// row_nodes(Q) * Q words stay a multiple of four for the 16-byte row stores.  The wave stages
 // the candidate entries of its blocks -- one contiguous range of the lists,
 // blocks being in node order -- and every lane tests the staged faces of its
 // own block near its cell; the best hit per direction is kept as in
@@ -2212,12 +2215,13 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // The entries' near codes come from the node pass, 2 B an entry: formed here they
 // took ~190 instructions of a wave that has ~20 entries on its 64 lanes (star 823 ->
 // 788, the node pass 375 -> 381).
-constexpr int kRowNodes = 28;   // nodes per wave of the row pass
-static_assert(kRowNodes % 4 == 0 && kRowNodes <= 32, "16-byte row stores, two lanes per node");
+constexpr int row_nodes(int q) { return q > 19 ? 28 : 32; }   // nodes per wave of the row pass
+constexpr int kRowTiles = 32;   // consecutive waves of the row pass on one XCD
 
 template <int D, int Q>
 __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint16_t *lcode,
                                                  const uint32_t *nblk, const uint64_t *node_key, uint32_t nn, int64_t chunk) {
+    constexpr int kRowNodes = row_nodes(Q);
     constexpr int CELLS = D == 3 ? 64 : 16;
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
@@ -2255,7 +2259,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     constexpr int TCAP = 128;
     __shared__ uint16_t s_qa[TCAP];   // (node, staged entry) pairs to filter: l << 5 | j
     __shared__ uint16_t s_qb[TCAP];   // direction pairs to decide: l << 10 | j << 5 | p
-    static_assert(kRowNodes * Q % 4 == 0, "rows written four elements at a time");
+    static_assert(kRowNodes % 4 == 0 && kRowNodes <= 32, "16-byte row stores, two lanes per node");
     for (int i = 2 * lane; i < kRowNodes * Q; i += 2 * dev::kWave)
         *reinterpret_cast<ulonglong2 *>(s_best + i) = make_ulonglong2(kNoHit, kNoHit);
     int na = 0, nb = 0;

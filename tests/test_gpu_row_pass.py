@@ -30,3 +30,20 @@ def test_last_wave_of_rows(dim, lattice):
         rests.add(len(gl["key"]) % 4)
     log(f"  D{dim}Q{lattice}: nodes {counts}")
     assert len(rests) >= 2
+
+
+@pytest.mark.parametrize("dim,lattice,roots,levels", [(2, 9, (64, 64, 1), 4), (3, 19, (6, 6, 6), 3), (3, 27, (6, 6, 6), 3)])
+def test_waves_in_runs_per_xcd(dim, lattice, roots, levels):
+    """More than the 256 waves of one full group of runs, and a partial group behind it."""
+    import paper_2502_16310_amd as agal
+    walk, lists = agal.Context(), agal.Context()
+    walk.set_link_list_limit(0)
+    lists.set_link_list_limit(1 << 30)
+    v, f = geomgen.circle(200, 0.4, (0.5, 0.5)) if dim == 2 else geomgen.star(4)
+    wl = geomgen.Workload("rows", dim, v, f, roots, levels, 32, lattice)
+    d_spec = [float(max(wl.cell_size(l, a) for a in range(dim))) for l in range(levels)]
+    gw, gl = gpu_run(wl, ctx=walk, d_spec=d_spec), gpu_run(wl, ctx=lists, d_spec=d_spec)
+    log(f"  D{dim}Q{lattice}: {len(gl['key'])} nodes")
+    assert len(gl["key"]) > 256 * 32 + 1
+    assert np.array_equal(gw["key"], gl["key"]) and np.array_equal(gw["face"], gl["face"])
+    assert np.array_equal(gw["q"].view(np.int32), gl["q"].view(np.int32))
