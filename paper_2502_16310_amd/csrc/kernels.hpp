@@ -1032,10 +1032,15 @@ __device__ __forceinline__ void prop_spread_item(const uint32_t *keys, int64_t n
 // exists and the index is the linear one.  Cell flags and block marks must
 // start at zero; only ones are stored, so faces that meet the same cell race
 // harmlessly.
+// The pass is bound by vector instructions: ~300 of the full test for 64 pairs,
+// ~110 to find the pairs, their blocks and flags, and ~60 to queue those that
+// need the test.  With the short form of the test (below) before the block is
+// looked up, no queue: 327,680 faces over four levels 298 -> 195 us, 81,920
+// faces over three 101 -> 70, 20,480 faces 44 -> 34.
 // Faces per wave G (4, 8 or 16) is picked per launch: small face counts take
 // small G so that the pass still has several waves per SIMD to hide the table
-// and flag reads (measured on MI355X: 20,480 faces 68 -> 54 us with G = 4;
-// 327,680 faces 295 us with G = 16, 438 us with G = 4).
+// and flag reads (measured before the short form: 20,480 faces 68 -> 54 us with
+// G = 4; 327,680 faces 295 us with G = 16, 438 us with G = 4).
 constexpr int kFaceFlagWaves = 4;   // waves per workgroup
 constexpr int kFaceFlagInts = 10;   // per-face words of the wave's face table
 inline int face_flag_g(int64_t faces, int n_cu) {
@@ -1060,6 +1065,88 @@ struct FaceFlagArgs {
     uint8_t *cf;              // n x 4^D, zeroed
     uint8_t *pmark;           // n, zeroed
 };
+
+// Inclusive sum over the wave on DPP (every lane active): row shifts by 1, 2,
+// 4 and 8, then lane 15 of the previous row into rows 1 and 3 and lane 31
+// into rows 2 and 3; lanes without a source add 0.
+__device__ __forceinline__ uint32_t dpp_inclusive_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
+// Short form of sat_triangle for one face and many cells of half-width h: the
+// 13 axes are set up once per face (sat_axes: axes of edge `part`, or with part
+// 3 the plane and the box), and a cell costs ~50 operations instead of ~300.
+// With m the cell's centre and every axis a, its separation is |a . (m - v0) -
+// c| - w, w = half the triangle's extent along a plus the cell's; sat_gap
+// returns the largest of the 13.  Where R bounds the distance of a corner to the
+// centre on each axis and u = 2^-24, sat_triangle's rounded comparison of an
+// edge axis is off by at most 22 u R^2, its plane's (here over R) by 136 u R^2,
+// and the ones here by at most 36 and 75; so a gap beyond 2^-15 R^2 = 512 u R^2
+// (delta) decides: above, sat_triangle finds a separating axis, below -delta it
+// finds none.  In between, and where R is so small or large that R^3 leaves
+// FP32's range (beyond 1e-12 .. 1e12: delta = inf), the test itself is run.  An
+// axis that is zero (edge along a coordinate axis) separates nothing there either.
+constexpr int kSatWords = 13;   // float4 per face: 9 edge axes (a, c, w), normal, v0, box
+
+__device__ __forceinline__ void sat_axes(const float *r, float h, const float eps[3], int part, float4 *out) {
+    const float b[3] = {r[3] - r[0], r[4] - r[1], r[5] - r[2]}, c[3] = {r[6] - r[0], r[7] - r[1], r[8] - r[2]};
+    float R = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) R = fmaxf(R, (r[12 + a] - r[9 + a]) + (fabsf(h) + eps[a]));
+    R *= 1.0001f;
+    const float R2 = R * R;
+    if (part < 3) {
+        float e[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) e[a] = part == 0 ? b[a] : (part == 1 ? r[6 + a] - r[3 + a] : -c[a]);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {   // on components (y, z), (x, z), (x, y)
+            const int i = x == 0 ? 1 : 0, j = x == 2 ? 1 : 2;
+            const float au = x == 1 ? e[j] : -e[j], av = x == 1 ? -e[i] : e[i];
+            const float p1 = au * b[i] + av * b[j], p2 = au * c[i] + av * c[j];
+            const float mn = fminf(fminf(p1, p2), 0.0f), mx = fmaxf(fmaxf(p1, p2), 0.0f);
+            const bool none = au == 0.0f && av == 0.0f;
+            out[3 * part + x] = make_float4(au, av, -0.5f * (mn + mx),
+                                            none ? R2 : 0.5f * (mx - mn) + h * (fabsf(au) + fabsf(av)));
+        }
+    } else {
+        const float inv = 1.0f / R;
+        const float n[3] = {(b[1] * c[2] - b[2] * c[1]) * inv, (b[2] * c[0] - b[0] * c[2]) * inv,
+                            (b[0] * c[1] - b[1] * c[0]) * inv};
+        out[9] = make_float4(n[0], n[1], n[2], h * ((fabsf(n[0]) + fabsf(n[1])) + fabsf(n[2])));
+        out[10] = make_float4(r[0], r[1], r[2], R);
+        float bc[3], bw[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            bc[a] = 0.5f * ((r[9 + a] - r[a]) + (r[12 + a] - r[a]));
+            bw[a] = 0.5f * (r[12 + a] - r[9 + a]) + h;
+        }
+        const bool fits = R2 >= 1e-24f && R2 <= 1e24f;
+        out[11] = make_float4(bc[0], bc[1], bc[2], fits ? 3.0517578125e-05f * R2 : INFINITY);
+        out[12] = make_float4(bw[0], bw[1], bw[2], 0.0f);
+    }
+}
+
+__device__ __forceinline__ float sat_gap(const float4 *ax, const float m[3], float &delta) {
+    const float4 v = ax[10], n = ax[9], bc = ax[11], bw = ax[12];
+    const float p[3] = {m[0] - v.x, m[1] - v.y, m[2] - v.z};
+    const float box = fmaxf(fmaxf(fabsf(p[0] - bc.x) - bw.x, fabsf(p[1] - bc.y) - bw.y), fabsf(p[2] - bc.z) - bw.z);
+    float gap = fmaxf(box * v.w, fabsf(fmaf(n.x, p[0], fmaf(n.y, p[1], n.z * p[2]))) - n.w);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        const float4 a = ax[k];
+        const int i = k % 3 == 0 ? 1 : 0, j = k % 3 == 2 ? 1 : 2;
+        gap = fmaxf(gap, fabsf(fmaf(a.x, p[i], fmaf(a.y, p[j], a.z))) - a.w);
+    }
+    delta = bc.w;
+    return gap;
+}
 
 // One wave: faces face0 .. face0 + G - 1.  The (face, cell) pairs of
 // its faces are listed in face order and taken 64 at a time, one per lane.  A
@@ -1091,9 +1178,9 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
             for (int a = 0; a < D; ++a) {
                 // cells i with centre lo + (i + 1/2) dx in [min - h - eps, max + h + eps]
                 const int nc = 4 * A.NB[a];
-                const double lo = A.lo[a], dx = A.dx[a], reach = (double)A.h + (double)A.eps[a];
-                const double xl = fmin(fmax(((double)r[D * D + a] - reach - lo) / dx - 0.5, -1.0), (double)nc);
-                const double xh = fmax(fmin(((double)r[D * D + D + a] + reach - lo) / dx - 0.5, (double)nc), -1.0);
+                const double lo = A.lo[a], inv = 1.0 / (double)A.dx[a], reach = (double)A.h + (double)A.eps[a];
+                const double xl = fmin(fmax(((double)r[D * D + a] - reach - lo) * inv - 0.5, -1.0), (double)nc);
+                const double xh = fmax(fmin(((double)r[D * D + D + a] + reach - lo) * inv - 0.5, (double)nc), -1.0);
                 const int i0 = max(0, (int)ceil(xl));
                 const int i1 = min(nc - 1, (int)floor(xh));
                 ilo[a] = i0;
@@ -1113,12 +1200,16 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
     // pair indices below 2^16 (every face of the wave): quotients by the
     // per-axis cell counts as multiply-high by ceil(2^32 / n), exact there
     const bool small = __ballot(cnt > 65536u) == 0ull;
-    // 64-bit inclusive wave prefix of the pair counts
+    // inclusive wave prefix of the pair counts: 32 bits hold 64 counts of 2^16
     uint64_t incl = cnt;
+    if (small) {
+        incl = dpp_inclusive_sum((uint32_t)cnt);
+    } else {
 #pragma unroll
-    for (int d = 1; d < dev::kWave; d <<= 1) {
-        const uint64_t y = __shfl_up(incl, d, dev::kWave);
-        if (lane >= d) incl += y;
+        for (int d = 1; d < dev::kWave; d <<= 1) {
+            const uint64_t y = __shfl_up(incl, d, dev::kWave);
+            if (lane >= d) incl += y;
+        }
     }
     const uint64_t total = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(incl >> 32), dev::kWave - 1) << 32) |
                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)incl, dev::kWave - 1);
@@ -1128,51 +1219,15 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
         s_i[lane][7] = (int)(uint32_t)(pre >> 32);
     }
     dev::wave_sync();
-    // A pair that needs the separating-axis test (its block exists at the
-    // level, its cell is not flagged yet) is queued with its cell centre,
-    // block and face; the queue is tested 64 pairs at a time, one per lane, so
-    // that the lanes of a step whose pairs were dropped do not idle through the
-    // test.  The test and what it writes are those of the pair itself.
-    constexpr int QCAP = 128;   // below 64 between steps, at most 64 added per step
-    __shared__ float s_qm[kFaceFlagWaves][3][QCAP];
-    __shared__ uint32_t s_qb[kFaceFlagWaves][QCAP];
-    __shared__ uint32_t s_qk[kFaceFlagWaves][QCAP];
-    const int wq = (int)(threadIdx.x / dev::kWave);
-    int nq = 0;   // wave-uniform
-    auto test = [&](int take) {
+    constexpr int NAX = D == 3 ? kSatWords : 1;
+    __shared__ float4 s_ax[kFaceFlagWaves][G][NAX];
+    float4(*ax)[NAX] = s_ax[threadIdx.x / dev::kWave];
+    if constexpr (D == 3) {
+        for (int i = lane; i < 4 * G; i += dev::kWave) sat_axes(s_rec[i >> 2], A.h, A.eps, i & 3, ax[i >> 2]);
         dev::wave_sync();
-        float m[3] = {0.0f, 0.0f, 0.0f};
-        uint32_t blk = 0, kc = 0;
-        if (lane < take) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) m[a] = s_qm[wq][a][lane];
-            blk = s_qb[wq][lane];
-            kc = s_qk[wq][lane];
-        }
-        dev::wave_sync();
-        if (lane < nq - take) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) s_qm[wq][a][lane] = s_qm[wq][a][take + lane];
-            s_qb[wq][lane] = s_qb[wq][take + lane];
-            s_qk[wq][lane] = s_qk[wq][take + lane];
-        }
-        nq -= take;
-        if (lane < take) {
-            const int k = (int)(kc >> 8), cell = (int)(kc & 255u);
-            float vv[D * D];
-#pragma unroll
-            for (int j = 0; j < D * D; ++j) vv[j] = s_rec[k][j];
-            bool hit;
-            if constexpr (D == 3) hit = dev::sat_triangle(vv, m, A.h);
-            else hit = dev::sat_segment(vv, m, A.h);
-            if (hit) {
-                A.cf[(int64_t)blk * CELLS + cell] = 1;
-                A.pmark[blk] = 1;
-            }
-        }
-    };
-    // pair v: its cell, then whether it is queued
-    auto pair = [&](auto v, float (&m)[3], uint32_t &qblk, uint32_t &qkc) -> bool {
+    }
+    // pair v: its cell is tested, and flagged if its block exists at the level
+    auto pair = [&](auto v) {
         using T = decltype(v);
         auto pre_of = [&](int k) -> T {
             return (T)(((uint64_t)(uint32_t)s_i[k][7] << 32) | (uint32_t)s_i[k][6]);
@@ -1199,8 +1254,12 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
         } else {
             g[1] = s_i[k][1] + (int)q0;
         }
+        float m[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int a = 0; a < D; ++a) m[a] = dev::cell_centre(A.lo[a], g[a], A.dx[a]);
+        float acc = 0.0f, delta = 1.0f;   // 2D: undecided
+        if constexpr (D == 3) acc = sat_gap(ax[k], m, delta);
+        if (acc > delta) return;   // certainly separated
         int64_t blk = (int64_t)(g[1] >> 2) * A.NB[0] + (g[0] >> 2);
         int cell = (g[0] & 3) | ((g[1] & 3) << 2);
         if constexpr (D == 3) {
@@ -1211,36 +1270,32 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
             const uint32_t t = A.table[blk];
             const int bc[3] = {g[0] >> 2, g[1] >> 2, D == 3 ? g[2] >> 2 : 0};
             if ((int64_t)t >= A.n || A.keys[t] != dev::encode_key<D>(bc, A.level, A.R[0], A.R[1]))
-                return false;   // no such block at this level
+                return;   // no such block at this level
             blk = t;
         }
-        if (A.cf[blk * CELLS + cell]) return false;   // flagged already
-        qblk = (uint32_t)blk;   // a block index of the level (below 2^32)
-        qkc = ((uint32_t)k << 8) | (uint32_t)cell;
-        return true;
-    };
-    auto step = [&](bool valid, auto v) {
-        float m[3] = {0.0f, 0.0f, 0.0f};
-        uint32_t qblk = 0, qkc = 0;
-        const bool want = valid && pair(v, m, qblk, qkc);
-        const uint64_t bm = __ballot(want);
-        if (want) {
-            const int at = nq + dev::lanes_below(bm);
+        uint8_t *cf = A.cf + (blk * CELLS + cell);
+        if (*cf) return;   // flagged already
+        if (!(acc < -delta)) {
+            float vv[D * D];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) s_qm[wq][a][at] = m[a];
-            s_qb[wq][at] = qblk;
-            s_qk[wq][at] = qkc;
+            for (int j = 0; j < D * D; ++j) vv[j] = s_rec[k][j];
+            if constexpr (D == 3) {
+                if (!dev::sat_triangle(vv, m, A.h)) return;
+            } else {
+                if (!dev::sat_segment(vv, m, A.h)) return;
+            }
         }
-        nq += __popcll(bm);
-        if (nq >= dev::kWave) test(dev::kWave);
+        *cf = 1;
+        A.pmark[blk] = 1;
     };
     if (total <= 0xFFFFFFFFull) {
         const uint32_t tot = (uint32_t)total;
-        for (uint32_t c0 = 0; c0 < tot; c0 += dev::kWave) step(c0 + lane < tot, (uint32_t)(c0 + lane));
+        for (uint32_t c0 = 0; c0 < tot; c0 += dev::kWave)
+            if (c0 + lane < tot) pair((uint32_t)(c0 + lane));
     } else {
-        for (uint64_t c0 = 0; c0 < total; c0 += dev::kWave) step(c0 + lane < total, (uint64_t)(c0 + lane));
+        for (uint64_t c0 = 0; c0 < total; c0 += dev::kWave)
+            if (c0 + lane < total) pair((uint64_t)(c0 + lane));
     }
-    if (nq > 0) test(nq);
 }
 
 // 2:1 balance: a block of level m marked in this pass needs every neighbour
@@ -2578,19 +2633,6 @@ __device__ __forceinline__ void dpp_add(float (&s)[N], bool use) {
     if (use)
 #pragma unroll
         for (int k = 0; k < N; ++k) s[k] += up[k];
-}
-
-// Inclusive sum over the wave on DPP (every lane active): row shifts by 1, 2,
-// 4 and 8, then lane 15 of the previous row into rows 1 and 3 and lane 31
-// into rows 2 and 3; lanes without a source add 0.
-__device__ __forceinline__ uint32_t dpp_inclusive_sum(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
-    return v;
 }
 
 // The links of a tile of kAdjThreads nodes: the tile's face and weight rows
