@@ -51,57 +51,63 @@ __device__ __forceinline__ int64_t find_key(const uint32_t *keys, int64_t n, uin
     return -1;
 }
 
-// New blocks of one level: old index, state, and the created / refined /
-// coarsened counts.
-__global__ __launch_bounds__(kDiffThreads) void k_diff_new(const uint32_t *nkeys, const uint8_t *nleaf, int64_t nn,
-                                                           const uint32_t *okeys, const uint8_t *oleaf, int64_t no,
-                                                           int32_t *old_index, uint8_t *state,
-                                                           unsigned long long *counts) {
+// One level's new blocks (old index, state; created / refined / coarsened
+// counts) and old blocks (removed flag and count).
+struct DiffLevel {
+    const uint32_t *nkeys, *okeys;
+    const uint8_t *nleaf, *oleaf;
+    int64_t nn, no;
+    int32_t *old_index;
+    uint8_t *state, *removed;
+};
+struct DiffArgs {
+    DiffLevel lev[kMaxLevels + 1];
+    uint32_t wg0[2 * (kMaxLevels + 1) + 1];   // first workgroup: level l's new blocks at 2 l, its old ones at 2 l + 1
+    unsigned long long *counts;   // four per level, zeroed
+};
+
+// Every level in one launch: a level is one chain of dependent loads per thread
+// (a binary search), 5 to 9 us whatever its size, and eight launches ran one
+// after the other.  Four levels of a moving body, both ways: 58 us, together 19.
+__global__ __launch_bounds__(kDiffThreads) void k_diff(DiffArgs A) {
     __shared__ uint32_t s_acc[3];
+    int seg = 0;
+    while (blockIdx.x >= A.wg0[seg + 1]) ++seg;
+    const DiffLevel &V = A.lev[seg >> 1];
+    const int64_t first = (int64_t)(blockIdx.x - A.wg0[seg]) * kDiffThreads + threadIdx.x;
+    const int64_t stride = (int64_t)(A.wg0[seg + 1] - A.wg0[seg]) * kDiffThreads;
     uint32_t c[3] = {0u, 0u, 0u};
-    for (int64_t i = (int64_t)blockIdx.x * kDiffThreads + threadIdx.x; i < nn;
-         i += (int64_t)gridDim.x * kDiffThreads) {
-        const int64_t j = find_key(okeys, no, nkeys[i]);
-        uint8_t st = 0;
-        if (j < 0) st = 1;
-        else if (oleaf[j] && !nleaf[i]) st = 2;
-        else if (!oleaf[j] && nleaf[i]) st = 3;
-        old_index[i] = (int32_t)j;
-        state[i] = st;
-        if (st) ++c[st - 1];
+    if (seg & 1) {
+        for (int64_t j = first; j < V.no; j += stride) {
+            const bool gone = find_key(V.nkeys, V.nn, V.okeys[j]) < 0;
+            V.removed[j] = gone ? 1 : 0;
+            c[0] += gone ? 1u : 0u;
+        }
+    } else {
+        for (int64_t i = first; i < V.nn; i += stride) {
+            const int64_t j = find_key(V.okeys, V.no, V.nkeys[i]);
+            uint8_t st = 0;
+            if (j < 0) st = 1;
+            else if (V.oleaf[j] && !V.nleaf[i]) st = 2;
+            else if (!V.oleaf[j] && V.nleaf[i]) st = 3;
+            V.old_index[i] = (int32_t)j;
+            V.state[i] = st;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) c[k] += st == k + 1 ? 1u : 0u;
+        }
     }
     if (threadIdx.x < 3) s_acc[threadIdx.x] = 0u;
     __syncthreads();
-    const int lane = dev::lane_id();
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         // wave sums by shuffles, one LDS atomic per wave
         uint32_t v = c[k];
         for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, dev::kWave);
-        if (lane == 0 && v) atomicAdd(&s_acc[k], v);
+        if (dev::lane_id() == 0 && v) atomicAdd(&s_acc[k], v);
     }
     __syncthreads();
-    if (threadIdx.x < 3 && s_acc[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)s_acc[threadIdx.x]);
-}
-
-// Old blocks of one level: removed flag and count.
-__global__ __launch_bounds__(kDiffThreads) void k_diff_old(const uint32_t *okeys, int64_t no, const uint32_t *nkeys,
-                                                           int64_t nn, uint8_t *removed, unsigned long long *count) {
-    __shared__ uint32_t s_acc;
-    uint32_t c = 0u;
-    for (int64_t j = (int64_t)blockIdx.x * kDiffThreads + threadIdx.x; j < no;
-         j += (int64_t)gridDim.x * kDiffThreads) {
-        const bool gone = find_key(nkeys, nn, okeys[j]) < 0;
-        removed[j] = gone ? 1 : 0;
-        c += gone ? 1u : 0u;
-    }
-    if (threadIdx.x == 0) s_acc = 0u;
-    __syncthreads();
-    uint32_t v = c;
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, dev::kWave);
-    if (dev::lane_id() == 0 && v) atomicAdd(&s_acc, v);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_acc) atomicAdd(count, (unsigned long long)s_acc);
+    if (threadIdx.x < 3 && s_acc[threadIdx.x])
+        atomicAdd(&A.counts[4 * (seg >> 1) + ((seg & 1) ? 3 : threadIdx.x)], (unsigned long long)s_acc[threadIdx.x]);
 }
 
 bool same_grid(agal_forest a, agal_forest b) {
@@ -146,18 +152,19 @@ agal_status agal_forest_diff_create(agal_forest old_f, agal_forest new_f, void *
     fill_u64(reinterpret_cast<uint64_t *>(counts), 0ull, (int64_t)nl * 4, s);
     {
         ProfScope prof(ctx, "forest_diff", s);
-        for (int l = 0; l < nl && st == AGAL_OK; ++l) {
+        DiffArgs D{};
+        D.counts = counts;
+        for (int l = 0; l < nl; ++l) {
             const Level &A = old_f->lev[l], &B = new_f->lev[l];
             d->n_new[l] = B.n;
             d->n_old[l] = A.n;
-            if (B.n > 0)
-                hipLaunchKernelGGL(k_diff_new, dim3((unsigned)std::min<int64_t>((B.n + kDiffThreads - 1) / kDiffThreads, 2048)),
-                                   dim3(kDiffThreads), 0, s, B.keys, B.leaf, B.n, A.keys, A.leaf, A.n, d->old_index[l],
-                                   d->state[l], counts + 4 * l);
-            if (A.n > 0)
-                hipLaunchKernelGGL(k_diff_old, dim3((unsigned)std::min<int64_t>((A.n + kDiffThreads - 1) / kDiffThreads, 2048)),
-                                   dim3(kDiffThreads), 0, s, A.keys, A.n, B.keys, B.n, d->removed[l], counts + 4 * l + 3);
+            D.lev[l] = {B.keys, A.keys, B.leaf, A.leaf, B.n, A.n, d->old_index[l], d->state[l], d->removed[l]};
+            auto wgs = [](int64_t n) { return (uint32_t)std::min<int64_t>((n + kDiffThreads - 1) / kDiffThreads, 2048); };
+            D.wg0[2 * l + 1] = D.wg0[2 * l] + wgs(B.n);
+            D.wg0[2 * l + 2] = D.wg0[2 * l + 1] + wgs(A.n);
         }
+        if (D.wg0[2 * nl])
+            hipLaunchKernelGGL(k_diff, dim3(D.wg0[2 * nl]), dim3(kDiffThreads), 0, s, D);
     }
     if (st == AGAL_OK) {
         const hipError_t e1 = hipGetLastError();

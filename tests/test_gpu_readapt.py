@@ -84,3 +84,14 @@ def test_forests_over_different_grids_are_refused():
     with pytest.raises(agal.AgalError) as e:
         b["handles"][2].diff(a["handles"][2])
     assert e.value.status == agal.AGAL_EINVAL
+
+
+@pytest.mark.parametrize("levels,far", [(0, False), (1, True), (6, True), (6, False)])
+def test_empty_and_many_levels(orc, levels, far):
+    """Roots only; levels that are empty in one forest (the body outside the domain) or in neither."""
+    v, f = geomgen.circle(40, 0.2, (0.5, 0.5))
+    wl = geomgen.Workload("levels", 2, v, f, (3, 5, 1), levels, 8, 9)
+    near, away = gpu_run(wl, with_links=False), gpu_run(_moved(wl, (40.0, 0.0) if far else (0.07, 0.01)), with_links=False)
+    for a, b in ((near, away), (away, near), (away, away)):
+        counts = _check_diff(orc, a, b, levels)
+    log(f"  {levels} levels, far {far}: {counts}")
