@@ -2064,32 +2064,51 @@ __device__ __forceinline__ uint32_t link_code_at(const LinkArgs<D, Q> &A, const 
     return c;
 }
 
-// The set bits of a 4-bit mask in ascending order, two bits each (entry k
-// of the list is (list >> 2k) & 3).
-__device__ __forceinline__ uint32_t bit_list4(uint32_t m) {
-    uint32_t list = 0, n = 0;
-#pragma unroll
-    for (uint32_t b = 0; b < 4; ++b)
-        if ((m >> b) & 1u) {
-            list |= b << (2 * n);
-            ++n;
-        }
-    return list;
+// Cells (bit x + 4 y + 16 z) of a block that a face's near code covers.
+template <int D>
+__device__ __forceinline__ uint64_t code_cells(uint32_t c) {
+    const uint32_t y = (c >> 4) & 15u, z = (c >> 8) & 15u;
+    const uint32_t rows = ((y & 1u) | ((y & 2u) << 3) | ((y & 4u) << 6) | ((y & 8u) << 9)) * (c & 15u);   // 16 bits
+    if constexpr (D == 2) return rows;
+    const uint32_t lo = ((z & 1u) | ((z & 2u) << 15)) * rows, hi = (((z >> 2) & 1u) | ((z >> 2) & 2u) << 15) * rows;
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// u / n for n in 1 .. 4 and u < 4096 as (u * 2^16 / n) >> 16 (exact there:
-// the multiplier for 3 is 2^16 / 3 rounded up, off by less than 2^-16 of u).
-__device__ __forceinline__ uint32_t div_1to4(uint32_t u, uint32_t n) {
-    return (u * (n == 3u ? 21846u : 65536u >> (n >> 1))) >> 16;
+// Cells of its block that staged face j passes link_reach for (3D; all in 2D):
+// the same sums, each formed once for the cells that share it.
+template <int D, int CAP, bool kN>
+__device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, kN> &S, int j, const float dx[3]) {
+    if constexpr (D == 2) {
+        return ~0ull;
+    } else {
+        const float a = S.f[9][j] * dx[0], b = S.f[10][j] * dx[1], c = S.f[11][j] * dx[2], bound = S.f[13][j];
+        uint32_t m[2] = {0u, 0u};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const float sx = S.f[12][j] + (float)x * a;
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const float sy = sx + (float)y * b;
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    m[z / 2] |= fabsf(sy + (float)z * c) > bound ? 0u : 1u << (x + 4 * y + 16 * (z & 1));
+            }
+        }
+        return ((uint64_t)m[1] << 32) | m[0];
+    }
 }
 
 // Node pass of list mode: which finest-level cells have at least one link.
 // Work is taken from the candidate lists 64 (face, block) entries at a time
-// (persistent loop over the entries): every (entry, cell) pair whose cell
-// link box meets the face box -- exactly the pairs the row pass tests -- is
-// one lane's work.  A pair is dropped when its cell is known to have a link
-// already or when no direction can reach the face's plane; the others go
-// through a queue, 64 at a time, to the FP32 filter narrowed and widened by
+// (persistent loop over the entries), one per lane: a lane finds the cells of
+// its block whose link box meets its face's box and from which a direction can
+// reach its plane -- exactly the pairs the row pass filters -- as a 64-bit mask,
+// and the lanes give up a cell each in turn, without those known to have a link
+// already, to a queue.  (Listing every near pair, 64 at a time and one per lane,
+// took ~80 instructions for 64 pairs, of which most reach no plane; the masks take
+// ~280 for a window's 64 entries: a refined star 295 -> 254 us, six bodies 306 ->
+// 238, a moving sphere 76 -> 67.)
+// 64 pairs at a time go from the queue to the FP32 filter narrowed and widened by
 // its margins: a certain hit sets the cell's bit in its block's mask, a
 // possible one is decided in FP64 exactly as the row pass decides it.  So a
 // block's mask is the set of its cells for which the row pass finds a hit.
@@ -2107,8 +2126,6 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
     constexpr int RF = dev::kRecFloats<D>;
     __shared__ LinkStaged<D, 64> S;
     __shared__ float s_dir[NP][3];
-    __shared__ uint32_t s_pre[64];     // exclusive prefix of the entries' pair counts
-    __shared__ uint32_t s_enum[64];    // each entry's cells per axis: bit lists x, y, z and counts
     __shared__ int s_bc[64][3];        // its block coordinates
     __shared__ uint32_t s_head[64];    // first entry of the window with the same block
     __shared__ unsigned long long s_m[64];   // at a block's first entry: its mask as known to the wave
@@ -2122,7 +2139,8 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 
     for (int64_t w = wg; w * 64 < (int64_t)total; w += nwg) {
         const uint32_t e = (uint32_t)(w * 64) + (uint32_t)lane;
-        uint32_t bits = 0, cnt = 0, b = 0;
+        uint32_t bits = 0, b = 0;
+        unsigned long long cells = 0ull;   // of this lane's entry, not given up yet
         int bc[3] = {0, 0, 0};
         if (e < total) {
             const int32_t f = A.list[e];
@@ -2135,23 +2153,10 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                 float c0[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int a = 0; a < D; ++a) c0[a] = dev::cell_centre(A.lo[a], 4 * bc[a], A.dx[a]);
-                cnt = 1;
-#pragma unroll
-                for (int a = 0; a < D; ++a) cnt *= (uint32_t)__popc((bits >> (4 * a)) & 15u);
                 link_stage<D>(S, lane, f, r, A.dx, A.eps, c0, bits);
+                cells = code_cells<D>(bits) & reach_cells<D>(S, lane, A.dx);
             }
             lcode[e] = (uint16_t)bits;
-        }
-        const uint32_t incl = dev::wave_inclusive_sum(cnt);
-        const uint32_t npairs = (uint32_t)__builtin_amdgcn_readlane((int)incl, dev::kWave - 1);
-        s_pre[lane] = incl - cnt;
-        {
-            const uint32_t mx = bits & 15u, my = (bits >> 4) & 15u, mz = (bits >> 8) & 15u;
-            const uint32_t nx = (uint32_t)__popc(mx), ny = (uint32_t)__popc(my);
-            // bit lists (8 bits each) and the x and y counts less one (2 bits each)
-            s_enum[lane] = cnt ? (bit_list4(mx) | (bit_list4(my) << 8) | (bit_list4(mz) << 16) | ((nx - 1u) << 24) |
-                                  ((D == 3 ? ny - 1u : 0u) << 26))
-                               : 0u;
         }
         s_bc[lane][0] = bc[0];
         s_bc[lane][1] = bc[1];
@@ -2162,16 +2167,17 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
         const uint64_t heads = __ballot(head);
         const uint64_t upto = lane == dev::kWave - 1 ? ~0ull : ((2ull << lane) - 1ull);
         const uint64_t hb = heads & upto;
-        s_head[lane] = hb ? (uint32_t)(63 - __clzll((long long)hb)) : (uint32_t)lane;
+        const int my_head = hb ? 63 - __clzll((long long)hb) : lane;
+        s_head[lane] = (uint32_t)my_head;
         const unsigned long long m0 = head ? mask[b] : 0ull;
         s_m[lane] = m0;
         dev::wave_sync();
-        // one work loop: enumerate 64 pairs, queueing those still open, and
+        // one work loop: queue a cell of every lane that has one still open, and
         // decide 64 queued pairs whenever the queue holds that many (or the
-        // pairs are exhausted); each step has one place in the code
-        uint32_t c0 = 0;
+        // cells are exhausted); each step has one place in the code
         while (true) {
-            if (nq >= 64 || (nq > 0 && c0 >= npairs)) {
+            const bool more = __ballot(cells != 0ull) != 0ull;
+            if (nq >= 64 || (nq > 0 && !more)) {
                 const int ntake = min(nq, 64);
                 dev::wave_sync();
                 const uint32_t item = lane < ntake ? s_q[lane] : 0u;
@@ -2200,40 +2206,14 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                     }
                     if (hit) atomicOr(&s_m[s_head[j]], 1ull << cell);
                 }
-            } else if (c0 < npairs) {
-                const uint32_t v = c0 + (uint32_t)lane;
-                c0 += dev::kWave;
-                bool want = false;
-                uint32_t item = 0;
-                if (v < npairs) {
-                    int k = 0;   // the last entry whose pairs start at or before v
-#pragma unroll
-                    for (int step = 32; step >= 1; step >>= 1)
-                        if (s_pre[k + step] <= v) k += step;
-                    // pair u of entry k: x fastest, then y, then z over the entry's cells
-                    const uint32_t u = v - s_pre[k];
-                    const uint32_t en = s_enum[k];
-                    const uint32_t nx = ((en >> 24) & 3u) + 1u, ny = ((en >> 26) & 3u) + 1u;
-                    const uint32_t q1 = div_1to4(u, nx);
-                    const uint32_t ux = u - q1 * nx;
-                    uint32_t uy = q1, uz = 0;
-                    if constexpr (D == 3) {
-                        uz = div_1to4(q1, ny);
-                        uy = q1 - uz * ny;
-                    }
-                    const int ix = (int)((en >> (2 * ux)) & 3u);
-                    const int iy = (int)((en >> (8 + 2 * uy)) & 3u);
-                    const int iz = D == 3 ? (int)((en >> (16 + 2 * uz)) & 3u) : 0;
-                    const int cell = ix | (iy << 2) | (iz << 4);
-                    if (!((s_m[s_head[k]] >> cell) & 1ull)) {
-                        const float i3[3] = {(float)ix, (float)iy, (float)iz};
-                        want = link_reach<D>(S, k, i3, A.dx);
-                        item = ((uint32_t)k << 8) | (uint32_t)cell;
-                    }
-                }
-                const uint64_t m = __ballot(want);
-                if (want) s_q[nq + dev::lanes_below(m)] = item;
-                nq += __popcll(m);
+            } else if (more) {
+                cells &= ~s_m[my_head];
+                const bool want = cells != 0ull;
+                const uint32_t item = ((uint32_t)lane << 8) | (uint32_t)(want ? __builtin_ctzll(cells) : 0);
+                cells &= cells - 1ull;
+                const uint64_t wm = __ballot(want);
+                if (want) s_q[nq + dev::lanes_below(wm)] = item;
+                nq += __popcll(wm);
             } else {
                 break;
             }
