@@ -72,7 +72,7 @@ struct BodyDev {
     int hshift;
     unsigned long long *nmask;
     uint32_t *lwork, *loff, *lblk, *nblk;
-    uint16_t *lcode;
+    uint64_t *lcells;
     int32_t *list;
     uint32_t list_cap;
     uint32_t *blk_start, *blk_count, *blk_off;
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const BodyDev &X = bodies[b];
     if (X.Q != Q || !X.lists) return;
     const LinkArgs<D, Q> A = body_link_args<D, Q>(X, cnt[b * kLv + X.L]);
-    links_nodes_entries<D, Q>(A, X.lblk, X.lcode, X.nmask, it - wg_pre[b], wg_pre[b + 1] - wg_pre[b]);
+    links_nodes_entries<D, Q>(A, X.lblk, X.lcells, X.nmask, it - wg_pre[b], wg_pre[b + 1] - wg_pre[b]);
 }
 
 // Node counts per block (the links scan lays out the rows), and the list
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const uint32_t local = it - wg_pre[b];
     if (X.Q != Q || !X.lists || (int64_t)local * row_nodes(Q) >= (int64_t)nodes[b]) return;
     const LinkArgs<D, Q> A = body_link_args<D, Q>(X, cnt[b * kLv + X.L]);
-    links_rows_nodes<D, Q>(A, X.lblk, X.lcode, X.nblk, X.key, nodes[b], local);
+    links_rows_nodes<D, Q>(A, X.lblk, X.lcells, X.nblk, X.key, nodes[b], local);
 }
 
 template <int D, int Q>
@@ -1299,7 +1299,7 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
             AGAL_TRY(own(bt, &X.loff, (size_t)nL + 1));
             AGAL_TRY(own(bt, &X.list, (size_t)list_cap));
             AGAL_TRY(own(bt, &X.lblk, (size_t)list_cap));
-            AGAL_TRY(own(bt, &X.lcode, (size_t)list_cap));
+            AGAL_TRY(own(bt, &X.lcells, (size_t)list_cap));
             AGAL_TRY(own(bt, &X.nblk, (size_t)X.cap_nodes));
             bt->any_lists = true;
         } else {

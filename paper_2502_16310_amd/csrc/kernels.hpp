@@ -12,7 +12,6 @@
 #include <algorithm>
 #include <climits>
 #include <cstdint>
-#include <type_traits>
 
 #include "device.hpp"
 
@@ -1493,15 +1492,30 @@ struct LinkArgs {
 // With kNorms (3D) the face's L1 norms |E1|_1 and |E2|_1 are staged too (f[14],
 // f[15]); without them the filter forms them again from the staged corners, with
 // the same expressions, so the results are the same and the staging area is
-// smaller (as is the code, whose 12 bits are those of one block).
+// smaller.  That form, the row pass's, has the node pass's mask of the block's
+// cells that reach the face in place of the near code and the reach test.
 template <int D, int CAP = kLinkCap, bool kNorms = true>
 struct LinkStaged {
-    static constexpr int NF = D == 3 ? (kNorms ? 16 : 14) : 4;
-    using Code = typename std::conditional<kNorms, uint32_t, uint16_t>::type;
+    static constexpr int NF = D == 3 ? (kNorms ? 16 : 12) : 4;
     float f[NF][CAP];
     int32_t id[CAP];
-    Code code[CAP];
+    uint32_t code[kNorms ? CAP : 2 * CAP];   // (cells 0 .. 31, then 32 .. 63)
 };
+
+// Corners (3D: and normal) of record r at place pos.
+template <int D, int CAP, bool kN>
+__device__ __forceinline__ void link_stage_face(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r) {
+    S.id[pos] = f;
+#pragma unroll
+    for (int k = 0; k < D * D; ++k) S.f[k][pos] = r[k];
+    if constexpr (D == 3) {
+        const float e10 = r[3] - r[0], e11 = r[4] - r[1], e12 = r[5] - r[2];
+        const float e20 = r[6] - r[0], e21 = r[7] - r[1], e22 = r[8] - r[2];
+        S.f[9][pos] = e11 * e22 - e12 * e21;
+        S.f[10][pos] = e12 * e20 - e10 * e22;
+        S.f[11][pos] = e10 * e21 - e11 * e20;
+    }
+}
 
 // c0: centre of cell (0, 0, 0) of the block the face is staged for.
 //
@@ -1516,24 +1530,18 @@ struct LinkStaged {
 // |E1|_1 |E2|_1 of rounding together (|n_a| <= |E1|_1 |E2|_1), and a few of the
 // smallest denormal numbers.  A refined star of 7.3 M nodes: the pass
 // that finds nodes 395 -> 390 us; with the row pass's two lanes per node, rows 966 -> 920.
-template <int D, int CAP, bool kN>
-__device__ __forceinline__ void link_stage(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r, const float dx[3],
-                                           const float eps[3], const float c0[3], uint32_t code) {
-    S.id[pos] = f;
+template <int D, int CAP>
+__device__ __forceinline__ void link_stage(LinkStaged<D, CAP, true> &S, int pos, int32_t f, const float *r,
+                                           const float dx[3], const float eps[3], const float c0[3], uint32_t code) {
+    link_stage_face<D>(S, pos, f, r);
     if constexpr (D == 3) {
-        const float *v = r;
-        const float e10 = v[3] - v[0], e11 = v[4] - v[1], e12 = v[5] - v[2];
-        const float e20 = v[6] - v[0], e21 = v[7] - v[1], e22 = v[8] - v[2];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) S.f[k][pos] = v[k];
+        const float e10 = r[3] - r[0], e11 = r[4] - r[1], e12 = r[5] - r[2];
+        const float e20 = r[6] - r[0], e21 = r[7] - r[1], e22 = r[8] - r[2];
         const float n0 = e11 * e22 - e12 * e21;
         const float n1 = e12 * e20 - e10 * e22;
         const float n2 = e10 * e21 - e11 * e20;
-        S.f[9][pos] = n0;
-        S.f[10][pos] = n1;
-        S.f[11][pos] = n2;
         const float n1n = fabsf(e10) + fabsf(e11) + fabsf(e12), n2n = fabsf(e20) + fabsf(e21) + fabsf(e22);
-        const float T0 = c0[0] - v[0], T1 = c0[1] - v[1], T2 = c0[2] - v[2];
+        const float T0 = c0[0] - r[0], T1 = c0[1] - r[1], T2 = c0[2] - r[2];
         const float nT = ((fabsf(T0) + fabsf(T1)) + fabsf(T2)) + 3.0f * ((dx[0] + dx[1]) + dx[2]);
         const float Sn = (fabsf(n0 * dx[0]) + fabsf(n1 * dx[1])) + fabsf(n2 * dx[2]);
         const float Se = (fabsf(n0 * eps[0]) + fabsf(n1 * eps[1])) + fabsf(n2 * eps[2]);
@@ -1542,15 +1550,10 @@ __device__ __forceinline__ void link_stage(LinkStaged<D, CAP, kN> &S, int pos, i
         const float slack = 1.1920928955078125e-06f * (mx + 2.0f * nT) * (n1n * n2n);
         S.f[12][pos] = (T0 * n0 + T1 * n1) + T2 * n2;
         S.f[13][pos] = ((Sn * 1.00001f + Se) + slack) + 1e-43f;
-        if constexpr (kN) {
-            S.f[14][pos] = n1n;
-            S.f[15][pos] = n2n;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) S.f[k][pos] = r[k];
+        S.f[14][pos] = n1n;
+        S.f[15][pos] = n2n;
     }
-    S.code[pos] = (typename LinkStaged<D, CAP, kN>::Code)code;
+    S.code[pos] = code;
 }
 
 // x, negated when by is negative.
@@ -1691,8 +1694,8 @@ __device__ __forceinline__ uint32_t link_filter(const LinkStaged<D, CAP, kN> &S,
 
 // Whether any direction pair can pass the filter for staged face j and the cell
 // at position i of the block it was staged for (3D; always in 2D).
-template <int D, int CAP, bool kN>
-__device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, kN> &S, int j, const float i[3], const float dx[3]) {
+template <int D, int CAP>
+__device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, true> &S, int j, const float i[3], const float dx[3]) {
     if constexpr (D == 3) {
         const float s = ((S.f[12][j] + i[0] * (S.f[9][j] * dx[0])) + i[1] * (S.f[10][j] * dx[1])) +
                         i[2] * (S.f[11][j] * dx[2]);
@@ -2076,8 +2079,8 @@ __device__ __forceinline__ uint64_t code_cells(uint32_t c) {
 
 // Cells of its block that staged face j passes link_reach for (3D; all in 2D):
 // the same sums, each formed once for the cells that share it.
-template <int D, int CAP, bool kN>
-__device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, kN> &S, int j, const float dx[3]) {
+template <int D, int CAP>
+__device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, true> &S, int j, const float dx[3]) {
     if constexpr (D == 2) {
         return ~0ull;
     } else {
@@ -2118,9 +2121,9 @@ __device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, kN> &S,
 // (device-scope atomics are performed past the per-XCD L2, so one per hit
 // costs memory-side traffic).
 // mask: one 64-bit word per block, zeroed; lblk: the block of each entry;
-// lcode (written): its near code, 0 for an entry without a face or block.
+// lcells (written): its mask of cells, 0 for an entry without a face or block.
 template <int D, int Q>
-__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, const uint32_t *lblk, uint16_t *lcode,
+__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, const uint32_t *lblk, uint64_t *lcells,
                                                     unsigned long long *mask, int64_t wg, int64_t nwg) {
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
@@ -2156,7 +2159,7 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                 link_stage<D>(S, lane, f, r, A.dx, A.eps, c0, bits);
                 cells = code_cells<D>(bits) & reach_cells<D>(S, lane, A.dx);
             }
-            lcode[e] = (uint16_t)bits;
+            lcells[e] = cells;
         }
         s_bc[lane][0] = bc[0];
         s_bc[lane][1] = bc[1];
@@ -2238,8 +2241,8 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // -> 142.8 us, a refined star 750 -> 741 (runs of 128 and 512 the same).
 // row_nodes(Q) * Q words stay a multiple of four for the 16-byte row stores.  The wave stages
 // the candidate entries of its blocks -- one contiguous range of the lists,
-// blocks being in node order -- and every lane tests the staged faces of its
-// own block near its cell; the best hit per direction is kept as in
+// blocks being in node order -- and every lane queues the staged faces of its
+// own block that its cell reaches; the best hit per direction is kept as in
 // links_wave, in a node-major table from which the wave writes its rows of q
 // and face ids as flat coalesced runs.
 // Bound by vector instructions (2,300 per wave with the rows' words put together
@@ -2247,14 +2250,16 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // hit needed a select; ~2,000 with the table laid out and keyed as the rows are
 // written): a refined star's 7.3 M nodes 920 -> 860 us, 1.7 M nodes of D3Q19
 // 182 -> 172; six bodies in one launch 720 -> 677 (there with five waves a SIMD).
-// The entries' near codes come from the node pass, 2 B an entry: formed here they
-// took ~190 instructions of a wave that has ~20 entries on its 64 lanes (star 823 ->
-// 788, the node pass 375 -> 381).
+// Which cells of its block an entry's face reaches comes from the node pass, a
+// 64-bit mask an entry.  The near code formed here took ~190 instructions of a wave
+// that has ~20 entries on its 64 lanes (star 823 -> 788 us, with 2 B an entry); the
+// reach test and what is staged for it ~140 more, run for twice the pairs (star
+// 732 -> 675, moving sphere 142.5 -> 130, batch 594 -> 559; the node pass 250 -> 258).
 constexpr int row_nodes(int q) { return q > 19 ? 28 : 32; }   // nodes per wave of the row pass
 constexpr int kRowTiles = 32;   // consecutive waves of the row pass on one XCD
 
 template <int D, int Q>
-__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint16_t *lcode,
+__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint64_t *lcells,
                                                  const uint32_t *nblk, const uint64_t *node_key, uint32_t nn, int64_t chunk) {
     constexpr int kRowNodes = row_nodes(Q);
     constexpr int CELLS = D == 3 ? 64 : 16;
@@ -2282,11 +2287,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     o[0] = dev::cell_centre(A.lo[0], 4 * bc[0] + (cell & 3), A.dx[0]);
     o[1] = dev::cell_centre(A.lo[1], 4 * bc[1] + ((cell >> 2) & 3), A.dx[1]);
     o[2] = D == 3 ? dev::cell_centre(A.lo[2], 4 * bc[2] + (cell >> 4), A.dx[2]) : 0.0f;
-    const int pos3[3] = {cell & 3, (cell >> 2) & 3, cell >> 4};
-    const float fpos[3] = {(float)pos3[0], (float)pos3[1], (float)pos3[2]};
-    uint32_t lbits = 0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) lbits |= 1u << (4 * a + pos3[a]);
+    const uint32_t *node_cells = S.code + (cell >> 5) * kLinkCap;   // the staged faces' words with this cell's bit
     // node-major best keys (t's bits, face), a row of Q per node: the wave's rows of q and face ids as they are
     // written.  A key without a hit is (-1.0f, -1), above every hit's as unsigned numbers.
     constexpr unsigned long long kNoHit = 0xBF800000FFFFFFFFull;
@@ -2344,9 +2345,8 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
             if (nb >= 64) take_b(64);
         }
     };
-    // staged entries near the lane's cell (same block, all its code bits),
-    // queued while its links can reach them; both queues emptied before the
-    // staging area is refilled
+    // staged entries that the lane's cell reaches (same block, its bit of their
+    // masks), queued; both queues emptied before the staging area is refilled
     auto test_staged = [&](int n) {
         dev::wave_sync();
         uint32_t nm = 0;
@@ -2366,18 +2366,14 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
                 if (s_sblk[mid] <= myb) lo = mid + 1;
                 else hi = mid;
             }
-            for (int j = jlo + half; j < lo; j += 2) nm |= ((S.code[j] & lbits) == lbits) ? (1u << j) : 0u;
+            for (int j = jlo + half; j < lo; j += 2) nm |= ((node_cells[j] >> (cell & 31)) & 1u) << j;
         }
         while (__ballot(nm != 0)) {
-            bool pass = false;
-            int j = 0;
-            if (nm) {
-                j = __builtin_ctz(nm);
-                nm &= nm - 1u;
-                pass = link_reach<D>(S, j, fpos, A.dx);
-            }
-            const uint64_t m = __ballot(pass);
-            if (pass) s_qa[na + dev::lanes_below(m)] = (uint16_t)((node << 5) | j);
+            const bool has = nm != 0;
+            const int j = has ? __builtin_ctz(nm) : 0;
+            nm &= nm - 1u;
+            const uint64_t m = __ballot(has);
+            if (has) s_qa[na + dev::lanes_below(m)] = (uint16_t)((node << 5) | j);
             na += __popcll(m);
             if (na >= 64) take_a(64);
         }
@@ -2395,22 +2391,15 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
         const uint32_t e = c0 + (uint32_t)lane;
         bool keep = false;
         int32_t f = -1;
-        uint32_t b = 0, code = 0;
-        float r[RF], ec0[3] = {0.0f, 0.0f, 0.0f};
+        uint32_t b = 0;
+        uint64_t cells = 0;
+        float r[RF];
         if (e < e1) {
             f = A.list[e];
             b = lblk[e];
-            code = lcode[e];   // 0: not a face and block
-            keep = true;
-#pragma unroll
-            for (int a = 0; a < D; ++a) keep = keep && ((code >> (4 * a)) & 15u) != 0u;
-            if (keep) {
-                dev::load_rec<D>(A.faces.rec, f, r);
-                int ebc[3] = {0, 0, 0};
-                dev::decode_key<D>(A.keys[b], A.level, A.R[0], A.R[1], ebc);
-#pragma unroll
-                for (int a = 0; a < D; ++a) ec0[a] = dev::cell_centre(A.lo[a], 4 * ebc[a], A.dx[a]);
-            }
+            cells = lcells[e];   // 0: not a face and block
+            keep = cells != 0;
+            if (keep) dev::load_rec<D>(A.faces.rec, f, r);
         }
         uint64_t rest = __ballot(keep);
         while (rest) {
@@ -2424,7 +2413,9 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
             const int pos = count + dev::lanes_below(part);
             count += __popcll(part);
             if (now) {
-                link_stage<D>(S, pos, f, r, A.dx, A.eps, ec0, code);
+                link_stage_face<D>(S, pos, f, r);
+                S.code[pos] = (uint32_t)cells;
+                S.code[kLinkCap + pos] = (uint32_t)(cells >> 32);
                 s_sblk[pos] = b;
             }
         }

@@ -92,9 +92,9 @@ __global__ __launch_bounds__(64) void k_link_faces(const float *aabb, int64_t F,
 }
 
 template <int D, int Q>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_nodes(LinkArgs<D, Q> A, const uint32_t *lblk, uint16_t *lcode,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_nodes(LinkArgs<D, Q> A, const uint32_t *lblk, uint64_t *lcells,
                                                     unsigned long long *mask) {
-    links_nodes_entries<D, Q>(A, lblk, lcode, mask, blockIdx.x, gridDim.x);
+    links_nodes_entries<D, Q>(A, lblk, lcells, mask, blockIdx.x, gridDim.x);
 }
 
 template <int D>
@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) void k_node_map(const unsigned long long *mask
 
 template <int D, int Q>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_rows(
-    LinkArgs<D, Q> A, const uint32_t *lblk, const uint16_t *lcode, const uint32_t *nblk, uint32_t nn) {
-    links_rows_nodes<D, Q>(A, lblk, lcode, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
+    LinkArgs<D, Q> A, const uint32_t *lblk, const uint64_t *lcells, const uint32_t *nblk, uint32_t nn) {
+    links_rows_nodes<D, Q>(A, lblk, lcells, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
 }
 
 template <int D, int Q>
@@ -322,14 +322,14 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
     ListBuild<D> LB;
     uint32_t *lblk = nullptr, *noff = nullptr, *nblk = nullptr;
     int32_t *list = nullptr;
-    uint16_t *lcode = nullptr;
+    uint64_t *lcells = nullptr;
     Slab arrays;
     arrays.add(&noff, (size_t)n + 1);
     if (list_cap <= kListNoWait) {
         // the bound is small enough to allocate: no host wait
         arrays.add(&list, (size_t)list_cap);
         arrays.add(&lblk, (size_t)list_cap);
-        arrays.add(&lcode, (size_t)list_cap);
+        arrays.add(&lcells, (size_t)list_cap);
     }
     const unsigned fgrid = (unsigned)((g->F + kLinkFaceG - 1) / kLinkFaceG);
     const unsigned bgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
@@ -345,7 +345,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
             Slab lists;
             lists.add(&list, (size_t)list_cap);
             lists.add(&lblk, (size_t)list_cap);
-            lists.add(&lcode, (size_t)list_cap);
+            lists.add(&lcells, (size_t)list_cap);
             AGAL_TRY(st.get(lists));
         }
         hipLaunchKernelGGL((k_link_faces<D, true>), dim3(fgrid), dim3(64), 0, s, g->aabb, g->F, LB.G, LB.B,
@@ -361,7 +361,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         const int64_t want = (list_cap + 63) / 64;
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)ctx->n_cu * 4 * 8));
         ProfScope prof(ctx, "q_nodes", s);
-        hipLaunchKernelGGL((k_links_nodes<D, Q>), dim3(grid), dim3(64), 0, s, A, lblk, lcode, nmask);
+        hipLaunchKernelGGL((k_links_nodes<D, Q>), dim3(grid), dim3(64), 0, s, A, lblk, lcells, nmask);
     }
     AGAL_TRY_HIP(hipGetLastError());
     uint32_t nn = 0;
@@ -376,7 +376,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         const unsigned mgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
         hipLaunchKernelGGL((k_node_map<D>), dim3(mgrid), dim3(256), 0, s, nmask, noff, LL.keys, n, nblk, lk->key);
         hipLaunchKernelGGL((k_links_rows<D, Q>), dim3((unsigned)(((int64_t)nn + row_nodes(Q) - 1) / row_nodes(Q))), dim3(64), 0, s, A, lblk,
-                           lcode, nblk, nn);
+                           lcells, nblk, nn);
     }
     AGAL_TRY_HIP(hipGetLastError());
     return AGAL_OK;
