@@ -794,7 +794,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const uint32_t local = it - wg_pre[b];
     if (X.Q != Q || !X.lists || (int64_t)local * row_nodes(Q) >= (int64_t)nodes[b]) return;
     const LinkArgs<D, Q> A = body_link_args<D, Q>(X, cnt[b * kLv + X.L]);
-    links_rows_nodes<D, Q>(A, X.lblk, X.lcells, X.nblk, X.key, nodes[b], local);
+    links_rows_nodes<D, Q>(A, X.lcells, X.nblk, X.key, nodes[b], local);
 }
 
 template <int D, int Q>

@@ -2255,18 +2255,20 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
 // that has ~20 entries on its 64 lanes (star 823 -> 788 us, with 2 B an entry); the
 // reach test and what is staged for it ~140 more, run for twice the pairs (star
 // 732 -> 675, moving sphere 142.5 -> 130, batch 594 -> 559; the node pass 250 -> 258).
+// The entries are staged at their places in the lists, so a node's are found from
+// its block's offsets instead of by two binary searches in LDS (star 676 -> 644,
+// moving sphere 130 -> 122, batch 543 -> 526).
 constexpr int row_nodes(int q) { return q > 19 ? 28 : 32; }   // nodes per wave of the row pass
 constexpr int kRowTiles = 32;   // consecutive waves of the row pass on one XCD
 
 template <int D, int Q>
-__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint32_t *lblk, const uint64_t *lcells,
-                                                 const uint32_t *nblk, const uint64_t *node_key, uint32_t nn, int64_t chunk) {
+__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint64_t *lcells, const uint32_t *nblk,
+                                                 const uint64_t *node_key, uint32_t nn, int64_t chunk) {
     constexpr int kRowNodes = row_nodes(Q);
     constexpr int CELLS = D == 3 ? 64 : 16;
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
     __shared__ LinkStaged<D, kLinkCap, false> S;
-    __shared__ uint32_t s_sblk[kLinkCap];   // block of each staged entry
     __shared__ float s_dir[NP][3];
     static_assert(kLinkCap <= 32 && kRowNodes <= 32 && NP <= 32, "near masks are 32-bit; queue items 16-bit");
     const int lane = dev::lane_id();
@@ -2278,7 +2280,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     // half of its faces
     const int node = lane & 31, half = lane >> 5;
     const bool valid = node < nnodes;
-    const uint32_t myb = valid ? nblk[k0 + node] : 0xFFFFFFFFu;
+    const uint32_t myb = valid ? nblk[k0 + node] : 0u;
     const uint64_t nkey = valid ? node_key[k0 + node] : 0ull;
     const int cell = (int)(nkey % CELLS);
     int bc[3] = {0, 0, 0};
@@ -2288,6 +2290,8 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     o[1] = dev::cell_centre(A.lo[1], 4 * bc[1] + ((cell >> 2) & 3), A.dx[1]);
     o[2] = D == 3 ? dev::cell_centre(A.lo[2], 4 * bc[2] + (cell >> 4), A.dx[2]) : 0.0f;
     const uint32_t *node_cells = S.code + (cell >> 5) * kLinkCap;   // the staged faces' words with this cell's bit
+    // the list entries of the node's block
+    const uint32_t own0 = valid ? A.loff[myb] : 0u, own1 = valid ? min(A.loff[myb + 1], A.list_cap) : 0u;
     // node-major best keys (t's bits, face), a row of Q per node: the wave's rows of q and face ids as they are
     // written.  A key without a hit is (-1.0f, -1), above every hit's as unsigned numbers.
     constexpr unsigned long long kNoHit = 0xBF800000FFFFFFFFull;
@@ -2347,27 +2351,12 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     };
     // staged entries that the lane's cell reaches (same block, its bit of their
     // masks), queued; both queues emptied before the staging area is refilled
-    auto test_staged = [&](int n) {
+    auto test_staged = [&](uint32_t c0, int n) {
         dev::wave_sync();
         uint32_t nm = 0;
-        if (valid) {
-            // staged entries keep the lists' block order: the lane's own block is one range, found by two
-            // binary searches, and only that range is tested
-            int lo = 0, hi = n;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s_sblk[mid] < myb) lo = mid + 1;
-                else hi = mid;
-            }
-            const int jlo = lo;
-            hi = n;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (s_sblk[mid] <= myb) lo = mid + 1;
-                else hi = mid;
-            }
-            for (int j = jlo + half; j < lo; j += 2) nm |= ((node_cells[j] >> (cell & 31)) & 1u) << j;
-        }
+        // the staged entries are the lists' entries c0 .. c0 + n - 1: those of the lane's block are one range of them
+        const int lo = (int)max<int64_t>((int64_t)own0 - c0, 0), hi = (int)min<int64_t>((int64_t)own1 - c0, n);
+        for (int j = lo + half; j < hi; j += 2) nm |= ((node_cells[j] >> (cell & 31)) & 1u) << j;
         while (__ballot(nm != 0)) {
             const bool has = nm != 0;
             const int j = has ? __builtin_ctz(nm) : 0;
@@ -2386,41 +2375,21 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     const uint32_t b_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)nblk[k0]);
     const uint32_t b_last = (uint32_t)__builtin_amdgcn_readfirstlane((int)nblk[k0 + nnodes - 1]);
     const uint32_t e0 = A.loff[b_first], e1 = min(A.loff[b_last + 1], A.list_cap);
-    int count = 0;
-    for (uint32_t c0 = e0; c0 < e1; c0 += dev::kWave) {
-        const uint32_t e = c0 + (uint32_t)lane;
-        bool keep = false;
-        int32_t f = -1;
-        uint32_t b = 0;
-        uint64_t cells = 0;
-        float r[RF];
-        if (e < e1) {
-            f = A.list[e];
-            b = lblk[e];
-            cells = lcells[e];   // 0: not a face and block
-            keep = cells != 0;
-            if (keep) dev::load_rec<D>(A.faces.rec, f, r);
-        }
-        uint64_t rest = __ballot(keep);
-        while (rest) {
-            if (count > 0 && count + __popcll(rest) > kLinkCap) {
-                test_staged(count);
-                count = 0;
-            }
-            const bool now = ((rest >> lane) & 1ull) && dev::lanes_below(rest) < kLinkCap - count;
-            const uint64_t part = __ballot(now);
-            rest &= ~part;
-            const int pos = count + dev::lanes_below(part);
-            count += __popcll(part);
-            if (now) {
-                link_stage_face<D>(S, pos, f, r);
-                S.code[pos] = (uint32_t)cells;
-                S.code[kLinkCap + pos] = (uint32_t)(cells >> 32);
-                s_sblk[pos] = b;
+    for (uint64_t c0 = e0; c0 < e1; c0 += kLinkCap) {
+        const int n = (int)min<uint64_t>(kLinkCap, e1 - c0);
+        if (lane < n) {
+            const uint64_t cells = lcells[c0 + lane];   // 0: not a face and block, or none of the cells reaches the face
+            S.code[lane] = (uint32_t)cells;
+            S.code[kLinkCap + lane] = (uint32_t)(cells >> 32);
+            if (cells) {
+                const int32_t f = A.list[c0 + lane];
+                float r[RF];
+                dev::load_rec<D>(A.faces.rec, f, r);
+                link_stage_face<D>(S, lane, f, r);
             }
         }
+        test_staged((uint32_t)c0, n);
     }
-    if (count > 0) test_staged(count);
     dev::wave_sync();
 
     // rows k0 .. k0 + nnodes - 1 of q and face ids: element e of the span is

@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) void k_node_map(const unsigned long long *mask
 
 template <int D, int Q>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_rows(
-    LinkArgs<D, Q> A, const uint32_t *lblk, const uint64_t *lcells, const uint32_t *nblk, uint32_t nn) {
-    links_rows_nodes<D, Q>(A, lblk, lcells, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
+    LinkArgs<D, Q> A, const uint64_t *lcells, const uint32_t *nblk, uint32_t nn) {
+    links_rows_nodes<D, Q>(A, lcells, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
 }
 
 template <int D, int Q>
@@ -375,7 +375,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         ProfScope prof(ctx, "q_links", s);
         const unsigned mgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
         hipLaunchKernelGGL((k_node_map<D>), dim3(mgrid), dim3(256), 0, s, nmask, noff, LL.keys, n, nblk, lk->key);
-        hipLaunchKernelGGL((k_links_rows<D, Q>), dim3((unsigned)(((int64_t)nn + row_nodes(Q) - 1) / row_nodes(Q))), dim3(64), 0, s, A, lblk,
+        hipLaunchKernelGGL((k_links_rows<D, Q>), dim3((unsigned)(((int64_t)nn + row_nodes(Q) - 1) / row_nodes(Q))), dim3(64), 0, s, A,
                            lcells, nblk, nn);
     }
     AGAL_TRY_HIP(hipGetLastError());
