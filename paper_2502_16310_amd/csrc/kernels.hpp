@@ -1035,7 +1035,10 @@ __device__ __forceinline__ void prop_spread_item(const uint32_t *keys, int64_t n
 // ~110 to find the pairs, their blocks and flags, and ~60 to queue those that
 // need the test.  With the short form of the test (below) before the block is
 // looked up, no queue: 327,680 faces over four levels 298 -> 195 us, 81,920
-// faces over three 101 -> 70, 20,480 faces 44 -> 34.
+// faces over three 101 -> 70, 20,480 faces 44 -> 34.  A face's set-up by four
+// lanes (a quarter of its record, an axis of its FP64 cell range, an edge's axes
+// each) instead of one: ~350 of a wave's 1,370 instructions less, 199 -> 177, 71 ->
+// 63, 35 -> 30.
 // Faces per wave G (4, 8 or 16) is picked per launch: small face counts take
 // small G so that the pass still has several waves per SIMD to hide the table
 // and flag reads (measured before the short form: 20,480 faces 68 -> 54 us with
@@ -1158,43 +1161,40 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
                                                 float (*s_rec)[dev::kRecFloats<D>], int (*s_i)[kFaceFlagInts]) {
     constexpr int RF = dev::kRecFloats<D>;
     constexpr int CELLS = D == 3 ? 64 : 16;
-    static_assert(G >= 2 && G <= 64 && (G & (G - 1)) == 0, "face search takes log2(G) steps");
+    static_assert(G >= 2 && 4 * G <= 64 && (G & (G - 1)) == 0, "face search takes log2(G) steps; four lanes per face");
     const int lane = dev::lane_id();
-    uint64_t cnt = 0;
-    if (lane < G) {
-        const int64_t f = face0 + lane;
-        int ilo[3] = {0, 0, 0}, n[3] = {0, 1, 1};
-        if (f < A.F) {
-            float r[RF];
-            dev::load_rec<D>(A.rec, f, r);
-#pragma unroll
-            for (int k = 0; k < RF; ++k) s_rec[lane][k] = r[k];
-            bool finite = true;
-#pragma unroll
-            for (int k = 0; k < D * D + 2 * D; ++k) finite = finite && isfinite(r[k]);
-            cnt = finite ? 1u : 0u;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                // cells i with centre lo + (i + 1/2) dx in [min - h - eps, max + h + eps]
-                const int nc = 4 * A.NB[a];
-                const double lo = A.lo[a], inv = 1.0 / (double)A.dx[a], reach = (double)A.h + (double)A.eps[a];
-                const double xl = fmin(fmax(((double)r[D * D + a] - reach - lo) * inv - 0.5, -1.0), (double)nc);
-                const double xh = fmax(fmin(((double)r[D * D + D + a] + reach - lo) * inv - 0.5, (double)nc), -1.0);
-                const int i0 = max(0, (int)ceil(xl));
-                const int i1 = min(nc - 1, (int)floor(xh));
-                ilo[a] = i0;
-                n[a] = finite ? max(0, i1 - i0 + 1) : 0;
-                cnt *= (uint64_t)n[a];
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            s_i[lane][a] = ilo[a];
-            s_i[lane][3 + a] = n[a];
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-            s_i[lane][8 + a] = n[a] > 1 ? (int)(uint32_t)((0x100000000ull + (uint64_t)n[a] - 1u) / (uint64_t)n[a]) : 0;
+    // four lanes per face: a quarter of its record each, then an axis of its cell range each
+    const int k4 = lane >> 2, q4 = lane & 3;
+    const bool own = k4 < G, live = own && face0 + k4 < A.F;
+    constexpr int RQ = RF / 4;
+    float4 part = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (live && q4 < RQ) part = reinterpret_cast<const float4 *>(A.rec)[(face0 + k4) * RQ + q4];
+    if (own && q4 < RQ) *reinterpret_cast<float4 *>(&s_rec[k4][4 * q4]) = part;
+    // (3D: the last word of a record is none of the face's)
+    const bool fine = isfinite(part.x) && isfinite(part.y) && isfinite(part.z) && ((D == 3 && q4 == 3) || isfinite(part.w));
+    const bool finite = ((__ballot(fine) >> (lane & ~3)) & 15ull) == 15ull;
+    dev::wave_sync();
+    int i0 = 0, n = 1;
+    if (own && q4 < D) {
+        // cells i with centre lo + (i + 1/2) dx in [min - h - eps, max + h + eps]
+        auto axis = [&](auto x, auto y, auto z) { return q4 == 0 ? x : (q4 == 1 ? y : z); };
+        const int nc = 4 * axis(A.NB[0], A.NB[1], A.NB[2]);
+        const double lo = axis(A.lo[0], A.lo[1], A.lo[2]), inv = 1.0 / (double)axis(A.dx[0], A.dx[1], A.dx[2]);
+        const double reach = (double)A.h + (double)axis(A.eps[0], A.eps[1], A.eps[2]);
+        const double mn = s_rec[k4][D * D + q4], mx = s_rec[k4][D * D + D + q4];
+        const double xl = fmin(fmax((mn - reach - lo) * inv - 0.5, -1.0), (double)nc);
+        const double xh = fmax(fmin((mx + reach - lo) * inv - 0.5, (double)nc), -1.0);
+        i0 = max(0, (int)ceil(xl));
+        const int i1 = min(nc - 1, (int)floor(xh));
+        n = live && finite ? max(0, i1 - i0 + 1) : 0;
+    }
+    uint64_t cnt = (uint64_t)(uint32_t)n * (uint32_t)__shfl_xor(n, 1, dev::kWave);
+    cnt *= __shfl_xor(cnt, 2, dev::kWave);
+    if (!own || q4 != 0) cnt = 0;   // a face's pairs count at its first lane
+    if (own && q4 < 3) {
+        s_i[k4][q4] = i0;
+        s_i[k4][3 + q4] = n;
+        if (q4 < 2) s_i[k4][8 + q4] = n > 1 ? (int)(0xFFFFFFFFu / (uint32_t)n + 1u) : 0;   // ceil(2^32 / n)
     }
     // pair indices below 2^16 (every face of the wave): quotients by the
     // per-axis cell counts as multiply-high by ceil(2^32 / n), exact there
@@ -1212,19 +1212,17 @@ __device__ __forceinline__ void flag_faces_wave(const FaceFlagArgs<D> &A, int64_
     }
     const uint64_t total = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(incl >> 32), dev::kWave - 1) << 32) |
                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)incl, dev::kWave - 1);
-    if (lane < G) {
+    if (own && q4 == 0) {
         const uint64_t pre = incl - cnt;
-        s_i[lane][6] = (int)(uint32_t)pre;
-        s_i[lane][7] = (int)(uint32_t)(pre >> 32);
+        s_i[k4][6] = (int)(uint32_t)pre;
+        s_i[k4][7] = (int)(uint32_t)(pre >> 32);
     }
-    dev::wave_sync();
     constexpr int NAX = D == 3 ? kSatWords : 1;
     __shared__ float4 s_ax[kFaceFlagWaves][G][NAX];
     float4(*ax)[NAX] = s_ax[threadIdx.x / dev::kWave];
-    if constexpr (D == 3) {
-        for (int i = lane; i < 4 * G; i += dev::kWave) sat_axes(s_rec[i >> 2], A.h, A.eps, i & 3, ax[i >> 2]);
-        dev::wave_sync();
-    }
+    if constexpr (D == 3)
+        if (own) sat_axes(s_rec[k4], A.h, A.eps, q4, ax[k4]);
+    dev::wave_sync();
     // pair v: its cell is tested, and flagged if its block exists at the level
     auto pair = [&](auto v) {
         using T = decltype(v);
