@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kPairThreads) void k_b_bin_pairs(const BodyDev *bod
     for (uint32_t it = blockIdx.x; it < total; it += gridDim.x) {
         const int b = find_seg(s_pre, nb, it);
         const BodyDev &B = bodies[b];
-        bin_pairs<D, kScatter>(B.aabb, B.F, B.bins, (int64_t)(it - s_pre[b]) * nf, nf, count_global + B.bin_base,
+        bin_pairs<D, kScatter, true>(B.aabb, B.F, B.bins, (int64_t)(it - s_pre[b]) * nf, nf, count_global + B.bin_base,
                                kScatter ? off_global + B.bin_base : nullptr, ids, S);
     }
 }

@@ -26,7 +26,7 @@ __global__ __launch_bounds__(kPairThreads) void k_bin_pairs(const float *aabb, i
                                                             uint32_t *count, const uint32_t *off, int32_t *ids) {
     __shared__ PairLds S;
     for (int64_t f0 = (int64_t)blockIdx.x * nf; f0 < F; f0 += (int64_t)gridDim.x * nf)
-        bin_pairs<D, kScatter>(aabb, F, g, f0, nf, count, off, ids, S);
+        bin_pairs<D, kScatter, false>(aabb, F, g, f0, nf, count, off, ids, S);
 }
 
 __global__ __launch_bounds__(kCanonThreads) void k_bin_canon_small(int32_t *ids, const uint32_t *off, int64_t nb,

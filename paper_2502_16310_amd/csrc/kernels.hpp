@@ -145,39 +145,13 @@ struct PairLds {
     uint32_t wsum[kPairThreads / dev::kWave];
 };
 
-// kScatter false: count[bin] += the faces' pairs.  true: count holds the totals
-// of the count pass and is used up (down to zero) as the cursor; the pairs go
-// to ids at off[bin] + the place taken.
-template <int D, bool kScatter>
-__device__ __forceinline__ void bin_pairs(const float *aabb, int64_t F, const dev::BinGrid &g, int64_t f0, int nf,
-                                          uint32_t *count, const uint32_t *off, int32_t *ids, PairLds &S) {
-    const int tid = threadIdx.x, lane = dev::lane_id(), w = tid / dev::kWave;
+// The total pairs of the nf faces of the workgroup's table (kOne: of its face k0 alone), a chunk of kPairThreads x
+// kPairRounds at a time.
+template <bool kScatter, bool kOne>
+__device__ __forceinline__ void bin_pair_chunks(const dev::BinGrid &g, int64_t f0, int nf, int k0, uint32_t total,
+                                                uint32_t *count, const uint32_t *off, int32_t *ids, PairLds &S) {
+    const int tid = threadIdx.x;
     uint32_t *key = reinterpret_cast<uint32_t *>(S.key4), *val = reinterpret_cast<uint32_t *>(S.val4);
-    uint32_t n = 0;
-    if (tid < nf && f0 + tid < F) {
-        int lo[3], hi[3];
-        face_bin_range<D>(aabb, F, f0 + tid, g, lo, hi);
-        uint32_t m[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) m[a] = (uint32_t)max(0, hi[a] - lo[a] + 1);
-        n = m[0] * m[1] * m[2];   // at most B^D <= 2^31
-        // (nf > 1: the faces' sum has to fit 32 bits; bin_pair_faces gives nf > 1 to faces of at most 512 bins, and
-        // a batch whose faces have outgrown its plan by so much is over its capacity all the same)
-        if (nf > 1) n = min(n, 1u << 24);
-        S.bin0[tid] = ((uint32_t)lo[2] * (uint32_t)g.B + (uint32_t)lo[1]) * (uint32_t)g.B + (uint32_t)lo[0];
-        S.nx[tid] = m[0];
-        S.ny[tid] = m[1];
-    }
-    const uint32_t incl = dev::wave_inclusive_sum(n);
-    if (lane == dev::kWave - 1) S.wsum[w] = incl;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-#pragma unroll
-    for (int j = 0; j < kPairThreads / dev::kWave; ++j) {
-        before += j < w ? S.wsum[j] : 0u;
-        total += S.wsum[j];
-    }
-    S.pre[tid] = before + incl - n;   // faces past nf: the total
     constexpr uint32_t kChunk = kPairThreads * kPairRounds;
     for (uint64_t c0 = 0; c0 < total; c0 += kChunk) {
 #pragma unroll
@@ -194,11 +168,11 @@ __device__ __forceinline__ void bin_pairs(const float *aabb, int64_t F, const de
             const uint32_t v = (uint32_t)v64;
             face[r] = -1;
             if (v64 < total) {
-                int k = 0;   // the last face whose pairs start at or before v (the faces with none end the list)
+                int k = kOne ? k0 : 0;   // the last face whose pairs start at or before v (the faces with none end the list)
 #pragma unroll
-                for (int step = kPairThreads / 2; step >= 1; step >>= 1)
+                for (int step = kOne ? 0 : kPairThreads / 2; step >= 1; step >>= 1)
                     if (k + step < nf && S.pre[k + step] <= v) k += step;
-                const uint32_t u = v - S.pre[k], nx = S.nx[k], ny = S.ny[k];
+                const uint32_t u = v - (kOne ? 0u : S.pre[k]), nx = S.nx[k], ny = S.ny[k];
                 const uint32_t q = u / nx, z = q / ny;
                 const uint32_t b = S.bin0[k] + (z * (uint32_t)g.B + (q - z * ny)) * (uint32_t)g.B + (u - q * nx);
                 uint32_t h = (b * 2654435761u) >> 21;   // 11 bits: kPairTable slots
@@ -235,6 +209,52 @@ __device__ __forceinline__ void bin_pairs(const float *aabb, int64_t F, const de
                 if (face[r] >= 0) ids[val[slot[r]] + rank[r]] = face[r];
         }
         __syncthreads();
+    }
+}
+
+// kScatter false: count[bin] += the faces' pairs.  true: count holds the totals
+// of the count pass and is used up (down to zero) as the cursor; the pairs go
+// to ids at off[bin] + the place taken.  The faces' sum has to fit 32 bits:
+// bin_pair_faces gives nf > 1 to faces of at most 512 bins.  A batch keeps its
+// plan's nf while its faces may grow (kPlanned): with a face above kPairFaceMax
+// the workgroup takes its faces one by one.
+constexpr uint32_t kPairFaceMax = UINT32_MAX / kPairThreads;
+template <int D, bool kScatter, bool kPlanned>
+__device__ __forceinline__ void bin_pairs(const float *aabb, int64_t F, const dev::BinGrid &g, int64_t f0, int nf,
+                                          uint32_t *count, const uint32_t *off, int32_t *ids, PairLds &S) {
+    const int tid = threadIdx.x, lane = dev::lane_id(), w = tid / dev::kWave;
+    uint32_t n = 0;
+    if (tid < nf && f0 + tid < F) {
+        int lo[3], hi[3];
+        face_bin_range<D>(aabb, F, f0 + tid, g, lo, hi);
+        uint32_t m[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) m[a] = (uint32_t)max(0, hi[a] - lo[a] + 1);
+        n = m[0] * m[1] * m[2];   // at most B^D <= 2^31
+        S.bin0[tid] = ((uint32_t)lo[2] * (uint32_t)g.B + (uint32_t)lo[1]) * (uint32_t)g.B + (uint32_t)lo[0];
+        S.nx[tid] = m[0];
+        S.ny[tid] = m[1];
+    }
+    const uint32_t incl = dev::wave_inclusive_sum(n);
+    const bool wide = kPlanned && nf > 1 && __ballot(n > kPairFaceMax) != 0ull;
+    if (lane == dev::kWave - 1) S.wsum[w] = wide ? UINT32_MAX : incl;   // (a sum is at most 2^31)
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+    bool single = false;
+#pragma unroll
+    for (int j = 0; j < kPairThreads / dev::kWave; ++j) {
+        if (kPlanned) single = single || S.wsum[j] == UINT32_MAX;
+        before += j < w ? S.wsum[j] : 0u;
+        total += S.wsum[j];
+    }
+    if (!single) {
+        S.pre[tid] = before + incl - n;   // faces past nf: the total
+        bin_pair_chunks<kScatter, false>(g, f0, nf, 0, total, count, off, ids, S);
+    } else {
+        S.pre[tid] = n;
+        __syncthreads();
+        for (int k0 = 0; k0 < nf; ++k0)
+            bin_pair_chunks<kScatter, true>(g, f0, nf, k0, S.pre[k0], count, off, ids, S);
     }
     __syncthreads();   // before the next faces' sums
 }
