@@ -895,6 +895,22 @@ __device__ __forceinline__ float near_reach2(const float *r, float R) {
     return fine ? reach * reach : __builtin_inff();   // a NaN coordinate: not fine
 }
 
+// The two short tests of the own-bin pass for the face of record r (reach2: its near_reach2) and the point m: true
+// where near_l2 certainly accepts (sure2: 0.9999 R^2); maybe: false where it certainly refuses.
+template <int D>
+__device__ __forceinline__ bool own_short(const float *r, const float *m, float reach2, float sure2, bool &maybe) {
+    float d2 = 0.0f, w2 = 0.0f;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        const float d = fmaxf(fmaxf(r[D * D + a] - m[a], m[a] - r[D * D + D + a]), 0.0f);
+        d2 += d * d;
+        const float w = m[a] - r[a];
+        w2 += w * w;
+    }
+    maybe = !(d2 > reach2);                             // (a NaN on either side keeps the face)
+    return reach2 < __builtin_inff() && w2 <= sure2;   // the short acceptance holds where the bound does
+}
+
 // Own-bin flag pass, the paper's face detection as printed (Sec. II-C-2 with
 // Algorithm 1, bins of Sec. II-C-3): a cell looks only at the faces of the one
 // bin that holds its centre (bin index function of the binning) and is
@@ -912,6 +928,12 @@ __device__ __forceinline__ float near_reach2(const float *r, float R) {
 // 81,920 faces in 16^3 bins (up to 1,000 a bin), h = 0.05, two passes: 1,121 us
 // with a cell per lane and near_l2 for every face; 366 with the box test before
 // it; 136 with a face per lane; 121 with the corner test.
+// A bin of at most as many faces as the wave has cells there leaves lanes idle
+// that way: it takes a cell per lane, with the same tests for each of its faces.
+// Whole calls over 32^3 roots, two passes, one cell length: 320 faces in 16^3
+// bins 325 us with near_l2 for every face, 663 with a face per lane, 267 with the
+// rule; 80 faces in 4^3 bins 425, 821, 325; 5,120 faces in 16^3 bins 471, 495, 352
+// (411 with the line at half as many faces, 353 at twice as many).
 // Writes every cell flag and the block's pass mark (0 or 1).
 constexpr int kOwnCells = 4;
 template <int D>
@@ -954,8 +976,27 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
             }
         };
         float rn[RF];
-        int32_t f = id_at((uint64_t)s0 + (uint32_t)lane), fn = id_at((uint64_t)s0 + dev::kWave + (uint32_t)lane);
+        int32_t f = id_at((uint64_t)s0 + (uint32_t)lane);
         rec_at(f, rn);
+        if (s1 - s0 <= (uint32_t)__popcll(cells)) {   // at most a face per cell: a cell per lane
+            const float reach2l = near_reach2<D>(rn, A.h);
+            for (uint64_t left = __ballot(f >= 0); left && (cells & ~flagged); left &= left - 1ull) {
+                const int j = __builtin_ctzll(left);
+                auto of_face = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j)); };
+                float r[RF];
+#pragma unroll
+                for (int k = 0; k < D * D + 2 * D; ++k) r[k] = of_face(rn[k]);
+                const float reach2 = of_face(reach2l);
+                bool maybe, hit = false;
+                if (((cells & ~flagged) >> lane) & 1ull) {
+                    hit = own_short<D>(r, m, reach2, sure2, maybe);
+                    if (!hit && maybe) hit = dev::near_l2<D>(r, m, A.h);
+                }
+                flagged |= __ballot(hit);
+            }
+            continue;
+        }
+        int32_t fn = id_at((uint64_t)s0 + dev::kWave + (uint32_t)lane);
         for (uint64_t c0 = s0; c0 < s1 && cells; c0 += dev::kWave) {
             float r[RF];
 #pragma unroll
@@ -965,7 +1006,6 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
             rec_at(f, rn);
             fn = id_at(c0 + 2 * dev::kWave + (uint32_t)lane);
             const float reach2 = near_reach2<D>(r, A.h);
-            const bool clear = has && reach2 < __builtin_inff();   // the short acceptance holds where the bound does
             for (uint64_t left = cells; left;) {
                 int c[kOwnCells];
                 bool sure[kOwnCells], maybe[kOwnCells];
@@ -974,18 +1014,12 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
                 for (int u = 0; u < kOwnCells; ++u) {
                     c[u] = left ? __builtin_ctzll(left) : c[0];   // the last few: one cell several times
                     left &= left - 1ull;
-                    float d2 = 0.0f, w2 = 0.0f;
                     mc[u][2] = 0.0f;
 #pragma unroll
-                    for (int a = 0; a < D; ++a) {
+                    for (int a = 0; a < D; ++a)
                         mc[u][a] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m[a]), c[u]));
-                        const float d = fmaxf(fmaxf(r[D * D + a] - mc[u][a], mc[u][a] - r[D * D + D + a]), 0.0f);
-                        d2 += d * d;
-                        const float w = mc[u][a] - r[a];
-                        w2 += w * w;
-                    }
-                    sure[u] = clear && w2 <= sure2;
-                    maybe[u] = has && !(d2 > reach2);   // (a NaN on either side keeps the face)
+                    sure[u] = own_short<D>(r, mc[u], reach2, sure2, maybe[u]) && has;
+                    maybe[u] = maybe[u] && has;
                 }
 #pragma unroll
                 for (int u = 0; u < kOwnCells; ++u) {
