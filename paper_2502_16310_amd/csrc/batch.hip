@@ -1395,7 +1395,7 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
                 p *= std::min((double)X.bins.B, std::floor((double)bt->host[b].max_extent[a] * X.bins.s[a]) + 2.0);
             per_face = std::max(per_face, p);
         }
-        bt->bin_faces = bin_pair_faces(all_faces, per_face, ncu);
+        bt->bin_faces = bin_pair_faces(all_faces, per_face, bt->nb_total, ncu);
     }
     const int64_t fper_wg = (int64_t)kFaceFlagWaves * bt->fflag_g;
     for (int b = 0; b < bt->nb; ++b) {

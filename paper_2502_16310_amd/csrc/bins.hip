@@ -61,7 +61,8 @@ void launch_pairs(agal_context ctx, agal_geom g, const dev::BinGrid &grid, uint3
     double per_face = 1.0;
     for (int a = 0; a < g->dim; ++a)
         per_face *= std::min((double)grid.B, std::floor((double)g->max_extent[a] * grid.s[a]) + 2.0);
-    const int nf = bin_pair_faces(g->F, per_face, ctx->n_cu);
+    const int64_t nb = (int64_t)grid.B * grid.B * (g->dim == 3 ? grid.B : 1);
+    const int nf = bin_pair_faces(g->F, per_face, nb, ctx->n_cu);
     const unsigned wgs = (unsigned)std::min<int64_t>((g->F + nf - 1) / nf, 1 << 20);
     if (g->dim == 3)
         hipLaunchKernelGGL((k_bin_pairs<3, kScatter>), dim3(wgs), dim3(kPairThreads), 0, s, g->aabb, g->F, grid, nf,
