@@ -71,8 +71,8 @@ struct BodyDev {
     uint32_t hmask;
     int hshift;
     unsigned long long *nmask;
-    uint32_t *lwork, *loff, *lblk, *nblk;
-    uint64_t *lcells;
+    uint32_t *lwork, *loff, *nblk;
+    uint64_t *lword;
     int32_t *list;
     uint32_t list_cap;
     uint32_t *blk_start, *blk_count, *blk_off;
@@ -740,8 +740,8 @@ __global__ __launch_bounds__(64) void k_b_link_faces(const BodyDev *bodies, int 
     }
     const BlockFind B = body_find<D>(X, n);
     const int64_t f0 = (int64_t)(it - wg_pre[b]) * kLinkFaceG;
-    link_faces_wave<D, kScatter>(X.aabb, X.F, G, B, X.per_face, X.lwork, X.loff, X.lwork + X.cap[X.L], X.list,
-                                 X.lblk, X.list_cap, f0, kScatter ? nullptr : &ctl->overflow);
+    link_faces_wave<D, kScatter>(X.aabb, X.F, G, B, X.per_face, X.lwork, X.loff, X.lwork + X.cap[X.L], X.lword,
+                                 X.list_cap, f0, kScatter ? nullptr : &ctl->overflow);
 }
 
 template <int D, int Q>
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const BodyDev &X = bodies[b];
     if (X.Q != Q || !X.lists) return;
     const LinkArgs<D, Q> A = body_link_args<D, Q>(X, cnt[b * kLv + X.L]);
-    links_nodes_entries<D, Q>(A, X.lblk, X.lcells, X.nmask, it - wg_pre[b], wg_pre[b + 1] - wg_pre[b]);
+    links_nodes_entries<D, Q>(A, X.list, X.lword, X.nmask, it - wg_pre[b], wg_pre[b + 1] - wg_pre[b]);
 }
 
 // Node counts per block (the links scan lays out the rows), and the list
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const uint32_t local = it - wg_pre[b];
     if (X.Q != Q || !X.lists || (int64_t)local * row_nodes(Q) >= (int64_t)nodes[b]) return;
     const LinkArgs<D, Q> A = body_link_args<D, Q>(X, cnt[b * kLv + X.L]);
-    links_rows_nodes<D, Q>(A, X.lcells, X.nblk, X.key, nodes[b], local);
+    links_rows_nodes<D, Q>(A, X.lword, X.nblk, X.key, nodes[b], local);
 }
 
 template <int D, int Q>
@@ -1298,8 +1298,7 @@ static agal_status plan(agal_batch bt, const agal_tune_opts &opt, hipStream_t us
             AGAL_TRY(own(bt, &X.lwork, (size_t)2 * nL));
             AGAL_TRY(own(bt, &X.loff, (size_t)nL + 1));
             AGAL_TRY(own(bt, &X.list, (size_t)list_cap));
-            AGAL_TRY(own(bt, &X.lblk, (size_t)list_cap));
-            AGAL_TRY(own(bt, &X.lcells, (size_t)list_cap));
+            AGAL_TRY(own(bt, &X.lword, (size_t)list_cap));
             AGAL_TRY(own(bt, &X.nblk, (size_t)X.cap_nodes));
             bt->any_lists = true;
         } else {

@@ -2183,10 +2183,11 @@ __device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, true> &
 // the new bits go out with one device atomic per block at the window's end
 // (device-scope atomics are performed past the per-XCD L2, so one per hit
 // costs memory-side traffic).
-// mask: one 64-bit word per block, zeroed; lblk: the block of each entry;
-// lcells (written): its mask of cells, 0 for an entry without a face or block.
+// mask: one 64-bit word per block, zeroed.  lword: on entry each entry's block
+// (high half) and face, on return its mask of cells, 0 for an entry without a face
+// or block; list (written): its face.
 template <int D, int Q>
-__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, const uint32_t *lblk, uint64_t *lcells,
+__device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, int32_t *list, uint64_t *lword,
                                                     unsigned long long *mask, int64_t wg, int64_t nwg) {
     constexpr int NP = (Q - 1) / 2;
     constexpr int RF = dev::kRecFloats<D>;
@@ -2206,12 +2207,15 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
     for (int64_t w = wg; w * 64 < (int64_t)total; w += nwg) {
         const uint32_t e = (uint32_t)(w * 64) + (uint32_t)lane;
         uint32_t bits = 0, b = 0;
+        bool known = false;   // its block is one of the level
         unsigned long long cells = 0ull;   // of this lane's entry, not given up yet
         int bc[3] = {0, 0, 0};
         if (e < total) {
-            const int32_t f = A.list[e];
-            b = lblk[e];
-            if (f >= 0 && f < A.faces.F && (int64_t)b < A.n) {
+            const uint64_t word = lword[e];
+            const int32_t f = (int32_t)(uint32_t)word;
+            b = (uint32_t)(word >> 32);
+            known = (int64_t)b < A.n;
+            if (f >= 0 && f < A.faces.F && known) {
                 float r[RF];
                 dev::load_rec<D>(A.faces.rec, f, r);
                 dev::decode_key<D>(A.keys[b], A.level, A.R[0], A.R[1], bc);
@@ -2222,12 +2226,13 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, con
                 link_stage<D>(S, lane, f, r, A.dx, A.eps, c0, bits);
                 cells = code_cells<D>(bits) & reach_cells<D>(S, lane, A.dx);
             }
-            lcells[e] = cells;
+            list[e] = f;
+            lword[e] = cells;
         }
         s_bc[lane][0] = bc[0];
         s_bc[lane][1] = bc[1];
         s_bc[lane][2] = bc[2];
-        const bool live = e < total && (int64_t)b < A.n;
+        const bool live = known;
         const uint32_t prev_b = (uint32_t)__shfl_up((int)b, 1, dev::kWave);
         const bool head = live && (lane == 0 || prev_b != b);
         const uint64_t heads = __ballot(head);
@@ -2325,7 +2330,7 @@ constexpr int row_nodes(int q) { return q > 19 ? 28 : 32; }   // nodes per wave 
 constexpr int kRowTiles = 32;   // consecutive waves of the row pass on one XCD
 
 template <int D, int Q>
-__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint64_t *lcells, const uint32_t *nblk,
+__device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const uint64_t *lword, const uint32_t *nblk,
                                                  const uint64_t *node_key, uint32_t nn, int64_t chunk) {
     constexpr int kRowNodes = row_nodes(Q);
     constexpr int CELLS = D == 3 ? 64 : 16;
@@ -2441,7 +2446,7 @@ __device__ __forceinline__ void links_rows_nodes(const LinkArgs<D, Q> &A, const 
     for (uint64_t c0 = e0; c0 < e1; c0 += kLinkCap) {
         const int n = (int)min<uint64_t>(kLinkCap, e1 - c0);
         if (lane < n) {
-            const uint64_t cells = lcells[c0 + lane];   // 0: not a face and block, or none of the cells reaches the face
+            const uint64_t cells = lword[c0 + lane];   // 0: not a face and block, or none of the cells reaches the face
             S.code[lane] = (uint32_t)cells;
             S.code[kLinkCap + lane] = (uint32_t)(cells >> 32);
             if (cells) {
@@ -3040,7 +3045,7 @@ constexpr int kLinkFaceG = 16;
 template <int D, bool kScatter>
 __device__ __forceinline__ void link_faces_wave(const float *aabb, int64_t F, const LinkFaceGrid &G,
                                                 const BlockFind &B, int64_t max_coords, uint32_t *cnt,
-                                                const uint32_t *loff, uint32_t *cursor, int32_t *list, uint32_t *lblk,
+                                                const uint32_t *loff, uint32_t *cursor, uint64_t *lword,
                                                 uint32_t cap, int64_t f0, uint32_t *over = nullptr) {
     __shared__ int s_i[kLinkFaceG][8];   // per face: first block per axis, positions per axis, pair prefix
     const int lane = dev::lane_id();
@@ -3093,10 +3098,7 @@ __device__ __forceinline__ void link_faces_wave(const float *aabb, int64_t F, co
         if (idx < 0) continue;
         if constexpr (kScatter) {
             const uint32_t pos = loff[idx] + atomicAdd(&cursor[idx], 1u);
-            if (pos < cap) {
-                list[pos] = (int32_t)(f0 + k);
-                lblk[pos] = (uint32_t)idx;
-            }
+            if (pos < cap) lword[pos] = ((uint64_t)idx << 32) | (uint32_t)(f0 + k);   // one store of scattered 8 B
         } else {
             atomicAdd(&cnt[idx], 1u);
         }

@@ -86,15 +86,15 @@ __global__ void k_link_blocks(const uint32_t *keys, int64_t n, BlockFind B, uint
 template <int D, bool kScatter>
 __global__ __launch_bounds__(64) void k_link_faces(const float *aabb, int64_t F, LinkFaceGrid G, BlockFind B,
                                                    int64_t max_coords, uint32_t *cnt, const uint32_t *loff,
-                                                   uint32_t *cursor, int32_t *list, uint32_t *lblk, uint32_t cap) {
-    link_faces_wave<D, kScatter>(aabb, F, G, B, max_coords, cnt, loff, cursor, list, lblk, cap,
+                                                   uint32_t *cursor, uint64_t *lword, uint32_t cap) {
+    link_faces_wave<D, kScatter>(aabb, F, G, B, max_coords, cnt, loff, cursor, lword, cap,
                                  (int64_t)blockIdx.x * kLinkFaceG);
 }
 
 template <int D, int Q>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_nodes(LinkArgs<D, Q> A, const uint32_t *lblk, uint64_t *lcells,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_nodes(LinkArgs<D, Q> A, int32_t *list, uint64_t *lword,
                                                     unsigned long long *mask) {
-    links_nodes_entries<D, Q>(A, lblk, lcells, mask, blockIdx.x, gridDim.x);
+    links_nodes_entries<D, Q>(A, list, lword, mask, blockIdx.x, gridDim.x);
 }
 
 template <int D>
@@ -109,8 +109,8 @@ __global__ __launch_bounds__(256) void k_node_map(const unsigned long long *mask
 
 template <int D, int Q>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_links_rows(
-    LinkArgs<D, Q> A, const uint64_t *lcells, const uint32_t *nblk, uint32_t nn) {
-    links_rows_nodes<D, Q>(A, lcells, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
+    LinkArgs<D, Q> A, const uint64_t *lword, const uint32_t *nblk, uint32_t nn) {
+    links_rows_nodes<D, Q>(A, lword, nblk, A.node_key, nn, (int64_t)dev::xcd_tile<kRowTiles>(blockIdx.x, gridDim.x));
 }
 
 template <int D, int Q>
@@ -278,7 +278,7 @@ agal_status list_count(agal_geom g, agal_forest fo, const float eps[3], int64_t 
         G.NB[a] = a < D ? (fo->roots[a] << L) : 1;
     }
     hipLaunchKernelGGL((k_link_faces<D, false>), dim3(fgrid), dim3(64), 0, s, g->aabb, g->F, G, B, max_coords,
-                       LB.lwork, nullptr, nullptr, nullptr, nullptr, 0u);
+                       LB.lwork, nullptr, nullptr, nullptr, 0u);
     AGAL_TRY_HIP(hipGetLastError());
     return AGAL_OK;
 }
@@ -307,9 +307,10 @@ inline LinkMode link_mode(agal_geom g, agal_forest fo) {
 }
 
 // List mode: candidate lists, node pass, scan, row pass (rows written once).
-// A list bound above kListNoWait entries is replaced by the exact length (one
-// more host wait) rather than allocated.
-constexpr int64_t kListNoWait = int64_t(1) << 26;
+// A list bound of more than 512 MiB (an entry is its face and one 64-bit word) is
+// replaced by the exact length (one more host wait, ~10 us) rather than
+// allocated: the lists themselves are often many times shorter.
+constexpr int64_t kListNoWait = (int64_t(512) << 20) / (sizeof(int32_t) + sizeof(uint64_t));   // entries
 
 template <int D, int Q>
 agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_links lk, int64_t max_coords,
@@ -320,16 +321,15 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
     LinkArgs<D, Q> A = link_args<D, Q>(g, bn, fo);
     CallScratch st{ctx, s};
     ListBuild<D> LB;
-    uint32_t *lblk = nullptr, *noff = nullptr, *nblk = nullptr;
+    uint32_t *noff = nullptr, *nblk = nullptr;
     int32_t *list = nullptr;
-    uint64_t *lcells = nullptr;
+    uint64_t *lword = nullptr;
     Slab arrays;
     arrays.add(&noff, (size_t)n + 1);
     if (list_cap <= kListNoWait) {
         // the bound is small enough to allocate: no host wait
         arrays.add(&list, (size_t)list_cap);
-        arrays.add(&lblk, (size_t)list_cap);
-        arrays.add(&lcells, (size_t)list_cap);
+        arrays.add(&lword, (size_t)list_cap);
     }
     const unsigned fgrid = (unsigned)((g->F + kLinkFaceG - 1) / kLinkFaceG);
     const unsigned bgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
@@ -344,12 +344,11 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
             list_cap = total;
             Slab lists;
             lists.add(&list, (size_t)list_cap);
-            lists.add(&lblk, (size_t)list_cap);
-            lists.add(&lcells, (size_t)list_cap);
+            lists.add(&lword, (size_t)list_cap);
             AGAL_TRY(st.get(lists));
         }
         hipLaunchKernelGGL((k_link_faces<D, true>), dim3(fgrid), dim3(64), 0, s, g->aabb, g->F, LB.G, LB.B,
-                           max_coords, nullptr, LB.loff, LB.lwork + n, list, lblk, (uint32_t)list_cap);
+                           max_coords, nullptr, LB.loff, LB.lwork + n, lword, (uint32_t)list_cap);
     }
     AGAL_TRY_HIP(hipGetLastError());
     A.loff = LB.loff;
@@ -361,7 +360,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         const int64_t want = (list_cap + 63) / 64;
         const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(want, (int64_t)ctx->n_cu * 4 * 8));
         ProfScope prof(ctx, "q_nodes", s);
-        hipLaunchKernelGGL((k_links_nodes<D, Q>), dim3(grid), dim3(64), 0, s, A, lblk, lcells, nmask);
+        hipLaunchKernelGGL((k_links_nodes<D, Q>), dim3(grid), dim3(64), 0, s, A, list, lword, nmask);
     }
     AGAL_TRY_HIP(hipGetLastError());
     uint32_t nn = 0;
@@ -376,7 +375,7 @@ agal_status links_forward_lists(agal_geom g, agal_bins bn, agal_forest fo, agal_
         const unsigned mgrid = (unsigned)std::min<int64_t>((n + 255) / 256, 8192);
         hipLaunchKernelGGL((k_node_map<D>), dim3(mgrid), dim3(256), 0, s, nmask, noff, LL.keys, n, nblk, lk->key);
         hipLaunchKernelGGL((k_links_rows<D, Q>), dim3((unsigned)(((int64_t)nn + row_nodes(Q) - 1) / row_nodes(Q))), dim3(64), 0, s, A,
-                           lcells, nblk, nn);
+                           lword, nblk, nn);
     }
     AGAL_TRY_HIP(hipGetLastError());
     return AGAL_OK;
