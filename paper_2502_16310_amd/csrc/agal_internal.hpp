@@ -81,23 +81,31 @@ inline void dev_free(const Allocator &a, T *&p, hipStream_t s) {
 // array, then get() the block that owns them.  A call through the allocator
 // callbacks costs the host 3 to 4 us (a Python callback and torch's allocator),
 // as much as several small kernels run for, so a call that needs a dozen arrays
-// at one point asks once.
+// at one point asks once.  Nothing here allocates on the host or throws: the
+// callers are C entries.
 class Slab {
   public:
     template <class T>
     void add(T **p, size_t count) {
-        req_.push_back({p, total_});
-        total_ = (total_ + (count ? count : 1) * sizeof(T) + 255) & ~size_t(255);
+        if (count == 0) count = 1;
+        const size_t room = SIZE_MAX - 255 - total_;
+        if (n_ == kMax || count > room / sizeof(T)) {
+            fits_ = false;
+            return;
+        }
+        req_[n_++] = {p, total_};
+        total_ = (total_ + count * sizeof(T) + 255) & ~size_t(255);
     }
     // *base: the allocation to release (null on failure, the arrays untouched)
     agal_status get(const Allocator &a, void **base, hipStream_t s) {
         char *b = nullptr;
         *base = nullptr;
+        if (!fits_) return fail(AGAL_ENOMEM, "device allocation beyond the address space or of more than %d arrays", kMax);
         AGAL_TRY(dev_alloc(a, &b, total_, s));
         *base = b;
-        for (const Req &r : req_) {
-            void *p = b + r.at;
-            std::memcpy(r.p, &p, sizeof p);
+        for (int i = 0; i < n_; ++i) {
+            void *p = b + req_[i].at;
+            std::memcpy(req_[i].p, &p, sizeof p);
         }
         return AGAL_OK;
     }
@@ -107,7 +115,11 @@ class Slab {
         void *p;   // the pointer variable to set
         size_t at;
     };
-    std::vector<Req> req_;
+    static constexpr int kMax = 32;   // a forest diff adds the most: three arrays per level and one
+    static_assert(kMax >= 3 * (kMaxLevels + 1) + 1, "arrays of a forest diff");
+    Req req_[kMax];
+    int n_ = 0;
+    bool fits_ = true;
     size_t total_ = 0;
 };
 

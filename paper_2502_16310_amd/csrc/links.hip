@@ -24,7 +24,6 @@
 // counts and a copy kernel then lay the nodes out in canonical order.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "agal_internal.hpp"
 #include "device.hpp"
@@ -141,12 +140,11 @@ LinkArgs<D, Q> link_args(agal_geom g, agal_bins bn, agal_forest fo) {
 struct CallScratch {
     agal_context ctx;
     hipStream_t s;
-    std::vector<void *> ptrs;
+    void *blocks[4] = {};   // list mode takes the most: arrays, lists beyond the unseen limit, node blocks
+    int n = 0;
     agal_status get(Slab &arrays) {
-        void *base = nullptr;
-        AGAL_TRY(arrays.get(ctx->mem, &base, s));
-        ptrs.push_back(base);
-        return AGAL_OK;
+        if (n == 4) return fail(AGAL_ESTATE, "more than 4 blocks of scratch in one call");
+        return arrays.get(ctx->mem, &blocks[n++], s);
     }
     template <class T>
     agal_status get(T **p, size_t count) {
@@ -155,7 +153,7 @@ struct CallScratch {
         return get(one);
     }
     ~CallScratch() {
-        for (void *p : ptrs) dev_free(ctx->mem, p, s);
+        for (void *p : blocks) dev_free(ctx->mem, p, s);
     }
 };
 

@@ -15,7 +15,6 @@
 // faces (LDS broadcast reads) and stops once flagged.
 #include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "agal_internal.hpp"
 #include "device.hpp"
