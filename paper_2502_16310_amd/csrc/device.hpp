@@ -13,6 +13,9 @@
 
 #include <cstdint>
 
+// Arithmetic compiled for the host too: tests on the CPU run this source itself.
+#define AGAL_HD __host__ __device__ __forceinline__
+
 namespace agal {
 
 // Lattice directions (Sec. II-C-1 links follow the discrete velocity set).
@@ -39,9 +42,9 @@ namespace dev {
 constexpr int kWave = 64;
 constexpr float kEps = 9.5367431640625e-07f;  // 2^-20: margin of every candidate query box
 
-__device__ __forceinline__ float fminf_(float a, float b) { return a < b ? a : b; }
-__device__ __forceinline__ float fmaxf_(float a, float b) { return a > b ? a : b; }
-__device__ __forceinline__ float fabsf_(float a) { return a < 0.0f ? -a : a; }
+AGAL_HD float fminf_(float a, float b) { return a < b ? a : b; }
+AGAL_HD float fmaxf_(float a, float b) { return a > b ? a : b; }
+AGAL_HD float fabsf_(float a) { return a < 0.0f ? -a : a; }
 
 // Bin of coordinate x along one axis: floor((x - lo) * s) clamped to [0, B-1];
 // clamped in float before the integer conversion.
@@ -130,7 +133,7 @@ __device__ __forceinline__ uint32_t encode_key(const int c[3], int level, int Rx
 }
 
 // Cell centre coordinate: lo + (float)(2g + 1) * (0.5f * dx).
-__device__ __forceinline__ float cell_centre(float lo, int g, float dx) {
+AGAL_HD float cell_centre(float lo, int g, float dx) {
     return lo + (float)(2 * g + 1) * (0.5f * dx);
 }
 
@@ -159,13 +162,13 @@ __device__ __forceinline__ int64_t lower_bound_u32(const uint32_t *keys, int64_t
 // the definition (separated only on a strict '>'); axes are visited cheapest
 // first, which cannot change an OR of independent tests.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool sep3(float p0, float p1, float p2, float r) {
+AGAL_HD bool sep3(float p0, float p1, float p2, float r) {
     float mn = fminf_(fminf_(p0, p1), p2);
     float mx = fmaxf_(fmaxf_(p0, p1), p2);
     return (mn > r) || (mx < -r);
 }
 
-__device__ __forceinline__ bool sat_triangle(const float v[9], const float m[3], float h) {
+AGAL_HD bool sat_triangle(const float v[9], const float m[3], float h) {
     float A0 = v[0] - m[0], A1 = v[1] - m[1], A2 = v[2] - m[2];
     float B0 = v[3] - m[0], B1 = v[4] - m[1], B2 = v[5] - m[2];
     float C0 = v[6] - m[0], C1 = v[7] - m[1], C2 = v[8] - m[2];
@@ -205,7 +208,7 @@ __device__ __forceinline__ bool sat_triangle(const float v[9], const float m[3],
     return true;
 }
 
-__device__ __forceinline__ bool sat_segment(const float v[4], const float m[2], float h) {
+AGAL_HD bool sat_segment(const float v[4], const float m[2], float h) {
     float A0 = v[0] - m[0], A1 = v[1] - m[1];
     float B0 = v[2] - m[0], B1 = v[3] - m[1];
     if (fminf_(A0, B0) > h || fmaxf_(A0, B0) < -h) return false;
@@ -234,15 +237,15 @@ __device__ __forceinline__ bool sat_segment(const float v[4], const float m[2], 
 //   edges), near when ((p - v0) . n)^2 <= R2 (n.n).
 // Dot products are (x0 y0 + x1 y1) + x2 y2, cross products
 // (a1 b2 - a2 b1, a2 b0 - a0 b2, a0 b1 - a1 b0).
-__device__ __forceinline__ float dot3_(const float *a, const float *b) { return (a[0] * b[0] + a[1] * b[1]) + a[2] * b[2]; }
-__device__ __forceinline__ void cross3_(const float *a, const float *b, float *c) {
+AGAL_HD float dot3_(const float *a, const float *b) { return (a[0] * b[0] + a[1] * b[1]) + a[2] * b[2]; }
+AGAL_HD void cross3_(const float *a, const float *b, float *c) {
     c[0] = a[1] * b[2] - a[2] * b[1];
     c[1] = a[2] * b[0] - a[0] * b[2];
     c[2] = a[0] * b[1] - a[1] * b[0];
 }
 
 template <int D>
-__device__ __forceinline__ bool edge_near_l2(const float *a, const float *b, const float *p, float R2) {
+AGAL_HD bool edge_near_l2(const float *a, const float *b, const float *p, float R2) {
     float w[3] = {0.0f, 0.0f, 0.0f}, e[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -271,7 +274,7 @@ __device__ __forceinline__ bool edge_near_l2(const float *a, const float *b, con
 }
 
 template <int D>
-__device__ __forceinline__ bool near_l2(const float *v, const float *p, float R) {
+AGAL_HD bool near_l2(const float *v, const float *p, float R) {
     const float R2 = R * R;
     if constexpr (D == 2) {
         return edge_near_l2<2>(v, v + 2, p, R2);

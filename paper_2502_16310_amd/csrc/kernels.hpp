@@ -880,7 +880,7 @@ __device__ __forceinline__ void flag_wave(const FlagArgs<D> &A, int64_t first) {
 // that corner, to the other end when that is nearer, or to the line between,
 // which is nearer still.  r: the face's record.
 template <int D>
-__device__ __forceinline__ float near_reach2(const float *r, float R) {
+AGAL_HD float near_reach2(const float *r, float R) {
     float m2 = 0.0f;
     bool fine = R <= 1e8f;
 #pragma unroll
@@ -909,7 +909,7 @@ __device__ __forceinline__ float near_reach2(const float *r, float R) {
 // The two short tests of the own-bin pass for the face of record r (reach2: its near_reach2) and the point m: true
 // where near_l2 certainly accepts (sure2: 0.9999 R^2); maybe: false where it certainly refuses.
 template <int D>
-__device__ __forceinline__ bool own_short(const float *r, const float *m, float reach2, float sure2, bool &maybe) {
+AGAL_HD bool own_short(const float *r, const float *m, float reach2, float sure2, bool &maybe) {
     float d2 = 0.0f, w2 = 0.0f;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
@@ -1161,7 +1161,7 @@ __device__ __forceinline__ uint32_t dpp_inclusive_sum(uint32_t v) {
 // axis that is zero (edge along a coordinate axis) separates nothing there either.
 constexpr int kSatWords = 13;   // float4 per face: 9 edge axes (a, c, w), normal, v0, box
 
-__device__ __forceinline__ void sat_axes(const float *r, float h, const float eps[3], int part, float4 *out) {
+AGAL_HD void sat_axes(const float *r, float h, const float eps[3], int part, float4 *out) {
     const float b[3] = {r[3] - r[0], r[4] - r[1], r[5] - r[2]}, c[3] = {r[6] - r[0], r[7] - r[1], r[8] - r[2]};
     float R = 0.0f;
 #pragma unroll
@@ -1200,7 +1200,7 @@ __device__ __forceinline__ void sat_axes(const float *r, float h, const float ep
     }
 }
 
-__device__ __forceinline__ float sat_gap(const float4 *ax, const float m[3], float &delta) {
+AGAL_HD float sat_gap(const float4 *ax, const float m[3], float &delta) {
     const float4 v = ax[10], n = ax[9], bc = ax[11], bw = ax[12];
     const float p[3] = {m[0] - v.x, m[1] - v.y, m[2] - v.z};
     const float box = fmaxf(fmaxf(fabsf(p[0] - bc.x) - bw.x, fabsf(p[1] - bc.y) - bw.y), fabsf(p[2] - bc.z) - bw.z);
@@ -1567,7 +1567,7 @@ struct LinkStaged {
 
 // Corners (3D: and normal) of record r at place pos.
 template <int D, int CAP, bool kN>
-__device__ __forceinline__ void link_stage_face(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r) {
+AGAL_HD void link_stage_face(LinkStaged<D, CAP, kN> &S, int pos, int32_t f, const float *r) {
     S.id[pos] = f;
 #pragma unroll
     for (int k = 0; k < D * D; ++k) S.f[k][pos] = r[k];
@@ -1594,7 +1594,7 @@ __device__ __forceinline__ void link_stage_face(LinkStaged<D, CAP, kN> &S, int p
 // smallest denormal numbers.  A refined star of 7.3 M nodes: the pass
 // that finds nodes 395 -> 390 us; with the row pass's two lanes per node, rows 966 -> 920.
 template <int D, int CAP>
-__device__ __forceinline__ void link_stage(LinkStaged<D, CAP, true> &S, int pos, int32_t f, const float *r,
+AGAL_HD void link_stage(LinkStaged<D, CAP, true> &S, int pos, int32_t f, const float *r,
                                            const float dx[3], const float eps[3], const float c0[3], uint32_t code) {
     link_stage_face<D>(S, pos, f, r);
     if constexpr (D == 3) {
@@ -1620,14 +1620,14 @@ __device__ __forceinline__ void link_stage(LinkStaged<D, CAP, true> &S, int pos,
 }
 
 // x, negated when by is negative.
-__device__ __forceinline__ double flip_sign(double x, double by) {
-    return __longlong_as_double(__double_as_longlong(x) ^ (__double_as_longlong(by) & LLONG_MIN));
+AGAL_HD double flip_sign(double x, double by) {
+    return __builtin_bit_cast(double, __builtin_bit_cast(int64_t, x) ^ (__builtin_bit_cast(int64_t, by) & INT64_MIN));
 }
-__device__ __forceinline__ float flip_sign(float x, float by) {
-    return __uint_as_float(__float_as_uint(x) ^ (__float_as_uint(by) & 0x80000000u));
+AGAL_HD float flip_sign(float x, float by) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) ^ (__builtin_bit_cast(uint32_t, by) & 0x80000000u));
 }
 // The smaller of two numbers, NaN if one is (v_minimum3_f32).
-__device__ __forceinline__ float min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+AGAL_HD float min_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 
 // FP32 filter of staged face j for a link origin o over all direction pairs.
 // With T = o - a, E1 = b - a, E2 = c - a the solution of o + t D = a + u E1 +
@@ -1656,7 +1656,7 @@ __device__ __forceinline__ float min_nan(float a, float b) { return __builtin_el
 // now 301; row pass 787, now 756; large faces (walk mode, 768 faces on 192^3
 // cells) 294, now 284.
 template <int D, int NP, bool kSure, int CAP, bool kN>
-__device__ __forceinline__ uint32_t link_filter(const LinkStaged<D, CAP, kN> &S, int j, const float o[3], const float dx[3],
+AGAL_HD uint32_t link_filter(const LinkStaged<D, CAP, kN> &S, int j, const float o[3], const float dx[3],
                                                 bool *sure) {
     // The pair-independent sums of margins are formed once: comparing
     // atn - (MD + MT) <= ad instead of atn <= (ad + MD) + MT (and so on) moves
@@ -1758,7 +1758,7 @@ __device__ __forceinline__ uint32_t link_filter(const LinkStaged<D, CAP, kN> &S,
 // Whether any direction pair can pass the filter for staged face j and the cell
 // at position i of the block it was staged for (3D; always in 2D).
 template <int D, int CAP>
-__device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, true> &S, int j, const float i[3], const float dx[3]) {
+AGAL_HD bool link_reach(const LinkStaged<D, CAP, true> &S, int j, const float i[3], const float dx[3]) {
     if constexpr (D == 3) {
         const float s = ((S.f[12][j] + i[0] * (S.f[9][j] * dx[0])) + i[1] * (S.f[10][j] * dx[1])) +
                         i[2] * (S.f[11][j] * dx[2]);
@@ -1785,7 +1785,7 @@ __device__ __forceinline__ bool link_reach(const LinkStaged<D, CAP, true> &S, in
 // ~130 instructions of a decision: the row pass of a refined star's 7.3 M nodes
 // 838 -> 811 us, of 1.7 M nodes of D3Q19 168 -> 162.
 template <int D, int CAP, bool kN>
-__device__ __forceinline__ double link_decide(const LinkStaged<D, CAP, kN> &S, int j, const double o[3], const float dir[3]) {
+AGAL_HD double link_decide(const LinkStaged<D, CAP, kN> &S, int j, const double o[3], const float dir[3]) {
     const double nan = __builtin_nan("");
     if constexpr (D == 3) {
         const double a0 = S.f[0][j], a1 = S.f[1][j], a2 = S.f[2][j];
@@ -2117,7 +2117,7 @@ __device__ __forceinline__ void links_wave(const LinkArgs<D, Q> &A, int64_t firs
 // same FP32 expressions as link_box.  Per lane (the block need not be
 // wave-uniform).
 template <int D, int Q>
-__device__ __forceinline__ uint32_t link_code_at(const LinkArgs<D, Q> &A, const int bc[3], const float *bb) {
+AGAL_HD uint32_t link_code_at(const LinkArgs<D, Q> &A, const int bc[3], const float *bb) {
     uint32_t c = 0;
 #pragma unroll
     for (int a = 0; a < D; ++a)
@@ -2132,7 +2132,7 @@ __device__ __forceinline__ uint32_t link_code_at(const LinkArgs<D, Q> &A, const 
 
 // Cells (bit x + 4 y + 16 z) of a block that a face's near code covers.
 template <int D>
-__device__ __forceinline__ uint64_t code_cells(uint32_t c) {
+AGAL_HD uint64_t code_cells(uint32_t c) {
     const uint32_t y = (c >> 4) & 15u, z = (c >> 8) & 15u;
     const uint32_t rows = ((y & 1u) | ((y & 2u) << 3) | ((y & 4u) << 6) | ((y & 8u) << 9)) * (c & 15u);   // 16 bits
     if constexpr (D == 2) return rows;
@@ -2143,7 +2143,7 @@ __device__ __forceinline__ uint64_t code_cells(uint32_t c) {
 // Cells of its block that staged face j passes link_reach for (3D; all in 2D):
 // the same sums, each formed once for the cells that share it.
 template <int D, int CAP>
-__device__ __forceinline__ uint64_t reach_cells(const LinkStaged<D, CAP, true> &S, int j, const float dx[3]) {
+AGAL_HD uint64_t reach_cells(const LinkStaged<D, CAP, true> &S, int j, const float dx[3]) {
     if constexpr (D == 2) {
         return ~0ull;
     } else {
