@@ -96,9 +96,22 @@ __global__ void k_init_roots(uint32_t *keys, uint8_t *leaf, uint8_t *mark, int64
 // unmarked ones leaving at once, in place of a launch that listed the marked
 // keys, one that placed their children and one for the table (20,480 faces, 3
 // passes: 33 us in 8 launches, 20 us in 3; 327,680 faces, 4 passes: 69 -> 60).
+// Where most of many parents are unmarked, as in a large root grid around a small
+// body, a thread per (parent, child) is mostly threads that leave: a level of more
+// than kGrowByChild parents takes a thread per parent, and a wave then goes through
+// the children of its marked ones (whole calls, 1,280 faces: 200^3 roots, two
+// passes 834 -> 644 us, 128^3 383 -> 348; 5,000^2 roots 9,231 -> 9,048; lines at 2^14,
+// 2^16 and 2^20 parents within 2 % of one another, those above 2^18 being the rarer).
+constexpr int64_t kGrowByChild = int64_t(1) << 18;
+__host__ __device__ inline int64_t whole_waves(int64_t n) { return (n + dev::kWave - 1) & ~int64_t(dev::kWave - 1); }
+// Threads of a segment; its parts start at whole waves.
+template <int D>
+int64_t grow_threads(const GrowSeg &g) {
+    return whole_waves(g.cn) + whole_waves(g.pn > kGrowByChild ? g.pn : g.pn << D);
+}
 struct GrowArgs {
     GrowSeg seg[kMaxLevels + 1];
-    int64_t pre[kMaxLevels + 2];   // prefix of cn + (pn << D)
+    int64_t pre[kMaxLevels + 2];   // prefix of the segments' threads (grow_threads)
     int nseg;
     uint32_t *table;               // of segment 0's child level (null: none)
     int tlevel, R0, R1;
@@ -112,17 +125,33 @@ __global__ void k_grow(GrowArgs a) {
         int k = 0;
         while (k + 1 < a.nseg && a.pre[k + 1] <= i) ++k;
         const GrowSeg &g = a.seg[k];
-        const int64_t j = i - a.pre[k];
-        if (j < g.cn) {
-            grow_old_item<D>(g, j);
+        const int64_t j = i - a.pre[k], t = j - whole_waves(g.cn);
+        if (t < 0) {
+            if (j < g.cn) grow_old_item<D>(g, j);
             continue;
         }
-        uint32_t key = 0;
-        const int64_t p = grow_child_item<D>(g, j - g.cn, key);
-        if (p >= 0 && k == 0 && a.table) {
-            int c[3];
-            dev::decode_key<D>(key, a.tlevel, a.R0, a.R1, c);
-            a.table[((int64_t)c[2] * (a.R1 << a.tlevel) + c[1]) * (a.R0 << a.tlevel) + c[0]] = (uint32_t)p;
+        auto child = [&](int64_t u) {
+            uint32_t key = 0;
+            const int64_t p = grow_child_item<D>(g, u, key);
+            if (p >= 0 && k == 0 && a.table) {
+                int c[3];
+                dev::decode_key<D>(key, a.tlevel, a.R0, a.R1, c);
+                a.table[((int64_t)c[2] * (a.R1 << a.tlevel) + c[1]) * (a.R0 << a.tlevel) + c[0]] = (uint32_t)p;
+            }
+        };
+        if (g.pn <= kGrowByChild) {
+            if (t < g.pn << D) child(t);
+            continue;
+        }
+        // 64 parents a wave: the marked ones' lanes in order, then 64 >> D of them at a time
+        const int lane = dev::lane_id();
+        const bool marked = t < g.pn && g.pm[t] != 0;
+        const uint64_t mm = __ballot(marked);
+        const int n = __popcll(mm), below = dev::lanes_below(mm);
+        const int order = __builtin_amdgcn_ds_permute((marked ? below : n + lane - below) << 2, lane);
+        for (int w0 = 0; w0 < n; w0 += dev::kWave >> D) {
+            const int w = w0 + (lane >> D), src = __shfl(order, w & (dev::kWave - 1), dev::kWave);
+            if (w < n) child(((t - lane + src) << D) | (lane & ((1 << D) - 1)));
         }
     }
     AGAL_GRID_STRIDE(i, a.nzero) a.zero[i] = 0u;
@@ -409,7 +438,7 @@ agal_status refine_impl(agal_geom g, agal_bins bn, agal_forest fo, hipStream_t s
             gs.nleaf = N.leaf;
             gs.nmark = N.mark;
             gs.ncf = m < l || next_by_face ? N.cf : nullptr;
-            ga.pre[ga.nseg + 1] = ga.pre[ga.nseg] + gs.cn + (gs.pn << D);
+            ga.pre[ga.nseg + 1] = ga.pre[ga.nseg] + grow_threads<D>(gs);
             gone[ga.nseg++] = C.base;
             C = N;
         }
