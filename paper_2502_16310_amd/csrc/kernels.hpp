@@ -76,7 +76,7 @@ __device__ __forceinline__ uint32_t import_face(const float *verts, int64_t Nv, 
 // ===========================================================================
 // Spatial binning (paper Sec. II-C-3)
 // ===========================================================================
-constexpr int kCanonCap = 2048;      // ids per LDS segment in the rank sort
+constexpr int kCanonCap = 2048;      // ids per LDS segment of the canonical sorts
 constexpr int kBigThreads = 1024;
 
 template <int D>
@@ -302,7 +302,9 @@ struct CanonLds {
 // kRankCap: a bin per wave, an id per lane, every id broadcast to the wave from
 // its register (a bin of 50 took each of its ids 50 LDS reads before).  Larger
 // bins are left as they are.  NT threads (a wave, or the workgroup), t of them
-// the caller; a thread's ids are loaded together.
+// the caller; a thread's ids are loaded together.  kLaneRank 8 / 16 / 32, small and
+// medium kernel: 327,680 faces in bins of ~21 ids 29 / 30 / 30 us, of ~15 36 / 35 /
+// 27, of ~8 64 / 50 / 48; 20,480 faces in bins of ~8 13 / 10 / 9.
 constexpr int kLaneRank = 16;
 template <int NT, class Sync>
 __device__ __forceinline__ void rank_sort_segment(int32_t *ids, const uint32_t *s_off, uint32_t s0, uint32_t s1,
@@ -1106,8 +1108,11 @@ __device__ __forceinline__ void prop_spread_item(const uint32_t *keys, int64_t n
 // 63, 35 -> 30.
 // Faces per wave G (4, 8 or 16) is picked per launch: small face counts take
 // small G so that the pass still has several waves per SIMD to hide the table
-// and flag reads (measured before the short form: 20,480 faces 68 -> 54 us with
-// G = 4; 327,680 faces 295 us with G = 16, 438 us with G = 4).
+// and flag reads.  All levels of a call with G = 4 / 8 / 16: 20,480 faces 29 / 32 /
+// 43 us, 40,500 38.5 / 34 / 41, 81,920 68 / 61 / 59, 327,680 255 / 195 / 176; six
+// bodies in a batch, whose faces have more cells each, 136 / 149 / 203.  (So the
+// step from 4 to 8 could come at half as many faces for one body, for ~4 us; the
+// batch's, which counts the faces of all bodies, would lose more.)
 constexpr int kFaceFlagWaves = 4;   // waves per workgroup
 constexpr int kFaceFlagInts = 10;   // per-face words of the wave's face table
 inline int face_flag_g(int64_t faces, int n_cu) {
@@ -2301,10 +2306,10 @@ __device__ __forceinline__ void links_nodes_entries(const LinkArgs<D, Q> &A, int
 // Row pass of list mode: one wave per row_nodes(Q) consecutive nodes (node k:
 // block nblk[k], node key written beforehand), two lanes per node.  28 nodes
 // per wave keep the best-key table at 6 KB and the wave's LDS at 8.6 KB, so
-// that 18 waves fit a CU (64 nodes: 9 waves and 14 % slower; 16, 20, 24, 32
-// and 48 measured too: fewer nodes per wave stage the same entries more often,
-// which costs more than the extra waves gain).
-// D3Q19 and D2Q9 rows leave room for the 32 nodes that two lanes each allow: 1.7 M nodes of D3Q19 150.5 -> 146.5 us.
+// that 18 waves fit a CU.  With the node map, a refined star's 7.3 M nodes of
+// D3Q27 take 730 us with 24 nodes per wave (the same entries staged more often),
+// 667 with 28 and 697 with 32 (fewer waves); D3Q19 and D2Q9 rows leave room for
+// the 32 nodes that two lanes each allow: 1.7 M nodes of D3Q19 141 -> 137.5.
 // Runs of 32 consecutive waves go to one XCD, as neighbours share faces and list entries:
 // -> 142.8 us, a refined star 750 -> 741 (runs of 128 and 512 the same).
 // row_nodes(Q) * Q words stay a multiple of four for the 16-byte row stores.  The wave stages

@@ -3,21 +3,22 @@
 //
 // Forward (list mode, the default):
 //  * candidate lists: every face lists the finest-level blocks whose link box
-//    (block +- one cell) its bounding box meets, found through a hash table of
-//    the blocks' parents (a refined block's 2^D children are consecutive in
-//    the level); count, exclusive scan, scatter;
-//  * node pass: one wave64 per block (four blocks per wave in 2D), one lane
-//    per cell, decides which cells have at least one link, stopping at the
-//    first certain hit; an exclusive scan of the per-block node counts gives
-//    every block its first output row;
-//  * row pass: the same waves compute, for the node cells only, the best hit
-//    per direction and write each node's row once, at its final place.
-//    A wave stages its block's candidate faces in LDS (vertices, FP32 normal,
-//    near code), each lane marks the staged faces near its own cell, and
-//    (lane, face) pairs go through an FP32 filter with rounding margins over
-//    all directions at once; whatever passes is decided, and its t computed,
-//    in FP64 with the textbook segment-triangle expressions (FP64 runs at the
-//    FP32 rate on this chip, and only near actual hits).
+//    (block +- one cell) its bounding box meets, found through a table of the
+//    blocks' parents, dense or, for large grids, hashed (a refined block's 2^D
+//    children are consecutive in the level); count, exclusive scan, scatter;
+//  * node pass: 64 list entries per wave64, one per lane: the cells of the
+//    entry's block near its face, and from which a direction can reach its
+//    plane, as a mask; the (entry, cell) pairs then decide which cells have at
+//    least one link, a cell leaving with its first certain hit.  The masks stay
+//    in the list; an exclusive scan of the per-block node counts gives every
+//    block its first output row;
+//  * row pass: a wave per 28 or 32 consecutive nodes computes the best hit per
+//    direction and writes each node's row once, at its final place.  It stages
+//    the list entries of its blocks in LDS (vertices, FP32 normal, mask), and
+//    every (node, entry) pair of the masks goes through an FP32 filter with
+//    rounding margins over all directions at once; whatever passes is decided,
+//    and its t computed, in FP64 with the textbook segment-triangle expressions
+//    (FP64 runs at the FP32 rate on this chip, and only near actual hits).
 // Walk mode (a face too large for the lists, or lists switched off): one pass
 // walks the bins under each block and writes its nodes into the block's own
 // slot range of a staging buffer (block * 4^D rows); an exclusive scan of the

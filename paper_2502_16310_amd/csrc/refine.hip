@@ -1,18 +1,24 @@
 // Near-wall refinement (paper Sec. II-C-1, II-C-2; forest layout Sec. II-A).
 //
-// Level by level: every cell of every block of the tested level checks the
-// faces of the bins its query box overlaps (the paper's "primary mode of
-// access": one level at a time, the block's cells processed together); a
-// block with a flagged cell is marked, 2:1 balance marks the coarser
+// Level by level (the paper's "primary mode of access"): every cell of every
+// block of the tested level that a face comes within the distance of is flagged;
+// a block with a flagged cell is marked, 2:1 balance marks the coarser
 // neighbours that must follow, and marked blocks are replaced by 2^D children
 // merged into the next level's sorted key list.
 //
-// Mapping on CDNA: one wave64 per 4x4x4 block (one lane per cell; four 4x4
-// blocks per wave in 2D).  The wave walks the bins under the block's query
-// box, culls each face against the box by its bounding box (lane-parallel,
-// one face per lane), compacts the survivors with a ballot into LDS, then
-// every lane runs the separating-axis test of its cell against the staged
-// faces (LDS broadcast reads) and stops once flagged.
+// Mapping on CDNA, picked per level:
+//  * face-centric, where the level's block grid fits a dense table and no face
+//    spans too many cells: a wave64 takes 4 to 16 faces, their axes set up in
+//    LDS, and one (face, nearby cell) pair per lane at a time; a short form of
+//    the separating-axis test decides all but the pairs within its rounding,
+//    and the table gives the block.
+//  * cell-centric: one wave64 per 4x4x4 block (one lane per cell; four 4x4
+//    blocks per wave in 2D).  The wave walks the bins under the block's query
+//    box, culls each face against the box by its bounding box (lane-parallel,
+//    one face per lane), compacts the survivors with a ballot into LDS, then
+//    every lane runs the separating-axis test of its cell against the staged
+//    faces (LDS broadcast reads) and stops once flagged.
+//  * own-bin (the paper's printed form): a cell looks at its own bin's faces.
 #include <algorithm>
 #include <cmath>
 
