@@ -947,12 +947,20 @@ AGAL_HD bool own_short(const float *r, const float *m, float reach2, float sure2
 // bins 325 us with near_l2 for every face, 663 with a face per lane, 267 with the
 // rule; 80 faces in 4^3 bins 425, 821, 325; 5,120 faces in 16^3 bins 471, 495, 352
 // (411 with the line at half as many faces, 353 at twice as many).
+// Faces without a bound (slivers, specks) need near_l2 for every cell.  By face,
+// the lanes take its branches each their own way; by cell, the cells of a block
+// mostly go together: so they too go by cell, from LDS, unless few cells are left
+// (in 2D, where near_l2 costs no more than the short tests, with the others of
+// their 64).  4,000 slivers in one bin, 16^3 roots: 19.7 ms with near_l2 for every
+// face by cell, 28.6 by face, 22.2 by the rule; with a third of the faces flat
+// 19.5, 20.1, 12.5.
 // Writes every cell flag and the block's pass mark (0 or 1).
 constexpr int kOwnCells = 4;
 template <int D>
 __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t first) {
     constexpr int CELLS = D == 3 ? 64 : 16;
     constexpr int RF = dev::kRecFloats<D>;
+    __shared__ float s_v[64][D * D];
     const int lane = dev::lane_id();
     const int64_t blk = first + lane / CELLS;
     const bool valid = blk < A.n;
@@ -988,25 +996,50 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
                 for (int k = 0; k < RF; ++k) r[k] = __builtin_nanf("");
             }
         };
-        float rn[RF];
-        int32_t f = id_at((uint64_t)s0 + (uint32_t)lane);
-        rec_at(f, rn);
-        if (s1 - s0 <= (uint32_t)__popcll(cells)) {   // at most a face per cell: a cell per lane
-            const float reach2l = near_reach2<D>(rn, A.h);
-            for (uint64_t left = __ballot(f >= 0); left && (cells & ~flagged); left &= left - 1ull) {
-                const int j = __builtin_ctzll(left);
+        // a cell per lane: the faces held by the lanes of `faces`, one after the other
+        auto by_cell = [&](uint64_t faces, const float (&rl)[RF]) {
+            bool todo = ((cells >> lane) & 1ull) != 0ull;
+            dev::wave_sync();
+#pragma unroll
+            for (int k = 0; k < D * D; ++k) s_v[lane][k] = rl[k];
+            dev::wave_sync();
+            for (; faces && __ballot(todo); faces &= faces - 1ull) {
+                const int j = __builtin_ctzll(faces);
+                float v[D * D];
+#pragma unroll
+                for (int k = 0; k < D * D; ++k) v[k] = s_v[j][k];
+                if (todo && dev::near_l2<D>(v, m, A.h)) todo = false;
+            }
+            flagged |= cells & ~__ballot(todo);
+            cells &= ~flagged;
+        };
+        // the same for faces with a bound, by the short tests first
+        auto by_cell_bounded = [&](uint64_t faces, const float (&rl)[RF], float reach2l) {
+            bool todo = ((cells >> lane) & 1ull) != 0ull;
+            for (; faces && __ballot(todo); faces &= faces - 1ull) {
+                const int j = __builtin_ctzll(faces);
                 auto of_face = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j)); };
                 float r[RF];
 #pragma unroll
-                for (int k = 0; k < D * D + 2 * D; ++k) r[k] = of_face(rn[k]);
-                const float reach2 = of_face(reach2l);
-                bool maybe, hit = false;
-                if (((cells & ~flagged) >> lane) & 1ull) {
-                    hit = own_short<D>(r, m, reach2, sure2, maybe);
-                    if (!hit && maybe) hit = dev::near_l2<D>(r, m, A.h);
+                for (int k = 0; k < D * D + 2 * D; ++k) r[k] = of_face(rl[k]);
+                if (todo) {
+                    bool maybe;
+                    if (own_short<D>(r, m, of_face(reach2l), sure2, maybe)) todo = false;
+                    else if (maybe && dev::near_l2<D>(r, m, A.h)) todo = false;
                 }
-                flagged |= __ballot(hit);
             }
+            flagged |= cells & ~__ballot(todo);
+            cells &= ~flagged;
+        };
+        float rn[RF];
+        int32_t f = id_at((uint64_t)s0 + (uint32_t)lane);
+        rec_at(f, rn);
+        if (s1 - s0 <= (uint32_t)__popcll(cells)) {
+            const float reach2 = near_reach2<D>(rn, A.h);
+            const bool bounded = reach2 < __builtin_inff();
+            by_cell_bounded(__ballot(f >= 0 && bounded), rn, reach2);
+            const uint64_t wide = __ballot(f >= 0 && !bounded);
+            if (wide) by_cell(wide, rn);
             continue;
         }
         int32_t fn = id_at((uint64_t)s0 + dev::kWave + (uint32_t)lane);
@@ -1014,11 +1047,20 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
             float r[RF];
 #pragma unroll
             for (int k = 0; k < RF; ++k) r[k] = rn[k];
-            const bool has = f >= 0;
+            bool has = f >= 0;
             f = fn;
             rec_at(f, rn);
             fn = id_at(c0 + 2 * dev::kWave + (uint32_t)lane);
             const float reach2 = near_reach2<D>(r, A.h);
+            const uint64_t wide = __ballot(has && !(reach2 < __builtin_inff()));
+            if (wide) {
+                const uint64_t faces = D == 3 ? wide : __ballot(has);
+                if (5 * __popcll(faces) <= 8 * __popcll(cells)) {
+                    by_cell(faces, r);
+                    has = has && !((faces >> lane) & 1ull);
+                    if (!__ballot(has)) continue;
+                }
+            }
             for (uint64_t left = cells; left;) {
                 int c[kOwnCells];
                 bool sure[kOwnCells], maybe[kOwnCells];
