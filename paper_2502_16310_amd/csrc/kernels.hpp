@@ -1022,9 +1022,10 @@ __device__ __forceinline__ void flag_own_bin_wave(const FlagArgs<D> &A, int64_t 
                 float r[RF];
 #pragma unroll
                 for (int k = 0; k < D * D + 2 * D; ++k) r[k] = of_face(rl[k]);
+                const float reach2 = of_face(reach2l);   // (with the whole wave: the face's lane may be done)
                 if (todo) {
                     bool maybe;
-                    if (own_short<D>(r, m, of_face(reach2l), sure2, maybe)) todo = false;
+                    if (own_short<D>(r, m, reach2, sure2, maybe)) todo = false;
                     else if (maybe && dev::near_l2<D>(r, m, A.h)) todo = false;
                 }
             }
